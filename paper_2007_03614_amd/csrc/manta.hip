@@ -1576,8 +1576,9 @@ struct DevBufs {
     Alloc al{g_alloc, g_release, g_ctx};
     std::vector<void*> p;
     size_t left() const { return SIZE_MAX; }
+    void charge(size_t) {}
     template <class T>
-    T* get(size_t n) {
+    T* get(size_t n, bool = true) {
         const size_t bytes = std::max<size_t>(n, 1) * sizeof(T);
         void* q = al.get(bytes);
         if (!q) throw Fail{SIM_ENOMEM, fmt("device allocation of %zu bytes failed", bytes)};
@@ -1592,22 +1593,71 @@ struct DevBufs {
 
 namespace {
 // Device memory of one routing call carved out of a fixed region (the
-// no-allocation entry point): 256-byte aligned pieces, SIM_EINVAL past its end.
+// no-allocation entry point): 256-byte aligned pieces.  A call is refused
+// (SIM_EINVAL) by what it is charged against `cap`; a form of the label kernel
+// whose own arrays differ takes them uncharged and charges those that the
+// documented limit is stated in, so the same calls fit whichever form runs.
 struct ScratchBufs {
     char* base;
-    size_t cap, used = 0;
-    size_t left() const { return cap - used; }
+    size_t cap, phys, used = 0, charged = 0;
+    size_t left() const { return cap - charged; }
+    static size_t padded(size_t bytes) { return (std::max<size_t>(bytes, 1) + 255) & ~(size_t)255; }
+    void charge(size_t bytes) {
+        charged += padded(bytes);
+        if (charged > cap) refuse();
+    }
     template <class T>
-    T* get(size_t n) {
-        const size_t bytes = (std::max<size_t>(n, 1) * sizeof(T) + 255) & ~(size_t)255;
-        if (used + bytes > cap)
-            throw Fail{SIM_EINVAL, fmt("the call needs more than the %zu bytes of scratch of "
-                                       "sim_shortest_routes_noalloc", cap)};
+    T* get(size_t n, bool counted = true) {
+        const size_t bytes = padded(std::max<size_t>(n, 1) * sizeof(T));
+        if (counted) charge(bytes);
+        if (used + bytes > phys) refuse();
         T* q = (T*)(base + used);
         used += bytes;
         return q;
     }
+    [[noreturn]] void refuse() const {
+        throw Fail{SIM_EINVAL, fmt("the call needs more than the %zu bytes of scratch of "
+                                   "sim_shortest_routes_noalloc", cap)};
+    }
 };
+
+// The in-edges of every node in records of four (RouteIn): record v is node
+// v's first, further ones follow the nodes'.
+std::vector<RouteIn> route_in_records(const sim_network* net, const float* cost) {
+    const int V = net->n_nodes, E = net->n_edges;
+    std::vector<RouteIn> rec(V, RouteIn{{-1, -1, -1, -1}, {0.f, 0.f, 0.f, 0.f}});
+    std::vector<int> last(V), fill(V, 0);
+    for (int v = 0; v < V; ++v) last[v] = v;
+    for (int e = 0; e < E; ++e) {
+        const int v = net->edge_to[e];
+        if (fill[v] == 4) {                       // the fourth moves on to a new record
+            const int more = (int)rec.size();
+            rec.push_back(RouteIn{{rec[last[v]].tail[3], -1, -1, -1}, {rec[last[v]].cost[3], 0.f, 0.f, 0.f}});
+            rec[last[v]].tail[3] = -2 - more;
+            last[v] = more;
+            fill[v] = 1;
+        }
+        rec[last[v]].tail[fill[v]] = net->edge_from[e];
+        rec[last[v]].cost[fill[v]++] = cost[e];
+    }
+    return rec;
+}
+
+// Workgroup size and dynamic LDS of k_route_tree: lists of at most
+// kRouteTreeList entries (and no more than the nodes), so that as many
+// workgroups as the labels allow share a CU.  A round has four lanes for each
+// of some 80 nodes on the 10,040-node city, 130 on the 40,000-node lattice,
+// where a CU holds one workgroup.  End to end with 256, 512 and 1,024
+// threads: city 8.4, 7.5, 8.0 ms, lattice 4.1, 3.5, 3.1 ms.
+struct RouteTreeShape {
+    int nt, list;
+    size_t lds;
+};
+RouteTreeShape route_tree_shape(int V) {
+    const size_t labels = 4 * (size_t)((V + 3) / 4 * 4);
+    const int list = (int)std::min<size_t>((size_t)std::min(V + 1, kRouteTreeList), (kRouteTreeLds - labels) / 4);
+    return RouteTreeShape{V <= 16384 ? 512 : 1024, list, labels + 4 * (size_t)list};
+}
 
 // The routes of Sec. II-C on the GPU; B provides the call's device buffers.
 template <class B>
@@ -1648,74 +1698,102 @@ void shortest_routes_impl(B& b, const sim_network* net, const float* edge_cost, 
         }
         const int nd = (int)dests.size();
         if ((double)nd * V * 4.0 > 16e9) throw Fail{SIM_EUNSUPPORTED, "labels of all destinations above 16 GB"};
+        int max_deg = 0;
+        for (int v = 0; v < V; ++v) max_deg = std::max(max_deg, out_off[v + 1] - out_off[v]);
+        // Which label kernel: whole trees in one workgroup's LDS where the
+        // labels fit; the in-edge records are bounded by the out-degree.
+        const bool tree = V <= kRouteTreeNodes && max_deg <= kRouteTreeDeg;
         int* d_off = b.template get<int>(V + 1);
         int* d_oe = b.template get<int>(E);
-        int* d_to = b.template get<int>(E);
-        float* d_cost = b.template get<float>(E);
         int* d_dest = b.template get<int>(nd);
-        float* d_dist = b.template get<float>((size_t)nd * V);
-        int* d_slot = b.template get<int>(n_queries);
+        int* d_tab = b.template get<int>((size_t)nd * V);   // labels, or the tree's out-edges
         int* d_o = b.template get<int>(n_queries);
-        int* d_d = b.template get<int>(n_queries);
         int* d_len = b.template get<int>(n_queries);
         HIP_OK(hipMemcpy(d_off, out_off.data(), 4 * (size_t)(V + 1), hipMemcpyHostToDevice));
         HIP_OK(hipMemcpy(d_oe, out_edge.data(), 4 * (size_t)E, hipMemcpyHostToDevice));
-        HIP_OK(hipMemcpy(d_to, net->edge_to, 4 * (size_t)E, hipMemcpyHostToDevice));
-        HIP_OK(hipMemcpy(d_cost, edge_cost, 4 * (size_t)E, hipMemcpyHostToDevice));
         HIP_OK(hipMemcpy(d_dest, dests.data(), 4 * (size_t)nd, hipMemcpyHostToDevice));
-        HIP_OK(hipMemcpy(d_slot, slot.data(), 4 * (size_t)n_queries, hipMemcpyHostToDevice));
         HIP_OK(hipMemcpy(d_o, origin, 4 * (size_t)n_queries, hipMemcpyHostToDevice));
-        HIP_OK(hipMemcpy(d_d, dest, 4 * (size_t)n_queries, hipMemcpyHostToDevice));
-        int max_deg = 0;
-        for (int v = 0; v < V; ++v) max_deg = std::max(max_deg, out_off[v + 1] - out_off[v]);
-        const dim3 gd(std::min(nd, 2048));
-        if (V > kRouteMaxNodes) {   // labels in global memory, relaxed from a frontier
-            std::vector<int> in_off(V + 1, 0), in_edge(E), fill_in(V, 0);
-            for (int e = 0; e < E; ++e) ++in_off[net->edge_to[e] + 1];
-            for (int v = 0; v < V; ++v) in_off[v + 1] += in_off[v];
-            for (int e = 0; e < E; ++e) in_edge[in_off[net->edge_to[e]] + fill_in[net->edge_to[e]]++] = e;
-            int* d_ioff = b.template get<int>(V + 1);
-            int* d_iedge = b.template get<int>(E);
-            int* d_from = b.template get<int>(E);
-            HIP_OK(hipMemcpy(d_ioff, in_off.data(), 4 * (size_t)(V + 1), hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(d_iedge, in_edge.data(), 4 * (size_t)E, hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(d_from, net->edge_from, 4 * (size_t)E, hipMemcpyHostToDevice));
-            // frontier (2 V) and marks (V) per workgroup, as many workgroups as fit
-            const size_t per_wg = 3 * 4 * (size_t)V + 512;
-            const int g = (int)std::max<size_t>(1, std::min<size_t>({(size_t)nd, (size_t)1024, b.left() / per_wg}));
-            int* d_fq = b.template get<int>((size_t)g * 2 * V);
-            int* d_mk = b.template get<int>((size_t)g * V);
-            hipLaunchKernelGGL(k_route_dist_global, dim3(g), dim3(kRouteNT), 0, 0, V, d_ioff, d_iedge, d_from, d_cost,
-                               d_dest, nd, d_dist, d_fq, d_mk);
-        } else if (max_deg <= 8) {   // padded adjacency, slot-major: [j * V + v]
-            const int km = max_deg <= 4 ? 4 : 8;
-            std::vector<int> pto((size_t)km * V);
-            std::vector<float> pcost((size_t)km * V);
-            for (int v = 0; v < V; ++v)
-                for (int j = 0; j < km; ++j) {
-                    const int k = out_off[v] + j;
-                    const bool has = k < out_off[v + 1];
-                    pto[(size_t)j * V + v] = has ? net->edge_to[out_edge[k]] : v;
-                    pcost[(size_t)j * V + v] = has ? edge_cost[out_edge[k]] : INFINITY;
-                }
-            int* d_pto = b.template get<int>((size_t)km * V);
-            float* d_pcost = b.template get<float>((size_t)km * V);
-            HIP_OK(hipMemcpy(d_pto, pto.data(), 4 * (size_t)km * V, hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(d_pcost, pcost.data(), 4 * (size_t)km * V, hipMemcpyHostToDevice));
-            if (km == 4 && V <= 10 * kRouteNT)   // adjacency in registers
-                hipLaunchKernelGGL((k_route_dist_regs<4, 10>), gd, dim3(kRouteNT), 0, 0, V, d_pto, d_pcost, d_dest, nd,
-                                   d_dist);
-            else if (km == 4)
-                hipLaunchKernelGGL(k_route_dist_padded<4>, gd, dim3(kRouteNT), 0, 0, V, d_pto, d_pcost, d_dest, nd, d_dist);
-            else
-                hipLaunchKernelGGL(k_route_dist_padded<8>, gd, dim3(kRouteNT), 0, 0, V, d_pto, d_pcost, d_dest, nd, d_dist);
+        // per form: the queries' destinations, and the edges' heads and costs
+        const RouteTreeShape sh = tree ? route_tree_shape(V) : RouteTreeShape{0, 0, 0};
+        RouteOut* d_out = nullptr;
+        int *d_qoff = nullptr, *d_qord = nullptr, *d_to = nullptr, *d_slot = nullptr, *d_d = nullptr;
+        float *d_cost = nullptr, *d_dist = (float*)d_tab;
+        if (tree) {
+            b.charge(4 * (size_t)E);              // heads, costs
+            b.charge(4 * (size_t)E);
+            b.charge(4 * (size_t)n_queries);      // destination slot and node of each query
+            b.charge(4 * (size_t)n_queries);
+            if (V > kRouteMaxNodes) {
+                b.charge(4 * (size_t)(V + 1));    // the tree's own arrays are charged as those of the form below
+                b.charge(4 * (size_t)E);
+                b.charge(4 * (size_t)E);
+                b.charge(8 * (size_t)V);
+                b.charge(4 * (size_t)V);
+            } else {
+                b.charge(4 * (size_t)(max_deg <= 4 ? 4 : 8) * V);
+                b.charge(4 * (size_t)(max_deg <= 4 ? 4 : 8) * V);
+            }
+            double sum = 0.0;
+            for (int e = 0; e < E; ++e) sum += (double)edge_cost[e];
+            const float step = (float)(kRouteTreeStep * sum / E);
+            std::vector<RouteOut> out(E);
+            for (int k = 0; k < E; ++k) out[k] = RouteOut{net->edge_to[out_edge[k]], edge_cost[out_edge[k]]};
+            const std::vector<RouteIn> in = route_in_records(net, edge_cost);
+            std::vector<int> qoff(nd + 1, 0), qord(n_queries), at(nd);
+            for (int q = 0; q < n_queries; ++q) ++qoff[slot[q] + 1];
+            for (int k = 0; k < nd; ++k) {
+                at[k] = qoff[k];
+                qoff[k + 1] += qoff[k];
+            }
+            for (int q = 0; q < n_queries; ++q) qord[at[slot[q]]++] = q;
+            d_out = b.template get<RouteOut>(E, false);
+            RouteIn* d_in = b.template get<RouteIn>(in.size(), false);
+            d_qoff = b.template get<int>(nd + 1, false);
+            d_qord = b.template get<int>(n_queries, false);
+            HIP_OK(hipMemcpy(d_out, out.data(), sizeof(RouteOut) * (size_t)E, hipMemcpyHostToDevice));
+            HIP_OK(hipMemcpy(d_in, in.data(), sizeof(RouteIn) * in.size(), hipMemcpyHostToDevice));
+            HIP_OK(hipMemcpy(d_qoff, qoff.data(), 4 * (size_t)(nd + 1), hipMemcpyHostToDevice));
+            HIP_OK(hipMemcpy(d_qord, qord.data(), 4 * (size_t)n_queries, hipMemcpyHostToDevice));
+            HIP_OK(hipFuncSetAttribute((const void*)k_route_tree, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)kRouteTreeLds));
+            hipLaunchKernelGGL(k_route_tree, dim3(nd), dim3(sh.nt), sh.lds, 0, V, d_in, d_off, d_out, d_dest, sh.list,
+                               step, d_tab, d_qoff, d_qord, d_o, d_len);
         } else {
-            hipLaunchKernelGGL(k_route_dist, gd, dim3(kRouteNT), 0, 0, V, d_off, d_oe, d_to, d_cost, d_dest, nd, d_dist);
+            d_to = b.template get<int>(E);
+            d_cost = b.template get<float>(E);
+            d_slot = b.template get<int>(n_queries);
+            d_d = b.template get<int>(n_queries);
+            HIP_OK(hipMemcpy(d_to, net->edge_to, 4 * (size_t)E, hipMemcpyHostToDevice));
+            HIP_OK(hipMemcpy(d_cost, edge_cost, 4 * (size_t)E, hipMemcpyHostToDevice));
+            HIP_OK(hipMemcpy(d_slot, slot.data(), 4 * (size_t)n_queries, hipMemcpyHostToDevice));
+            HIP_OK(hipMemcpy(d_d, dest, 4 * (size_t)n_queries, hipMemcpyHostToDevice));
+            if (V > kRouteMaxNodes) {   // labels in global memory, relaxed from a frontier
+                std::vector<int> in_off(V + 1, 0), in_edge(E), fill_in(V, 0);
+                for (int e = 0; e < E; ++e) ++in_off[net->edge_to[e] + 1];
+                for (int v = 0; v < V; ++v) in_off[v + 1] += in_off[v];
+                for (int e = 0; e < E; ++e) in_edge[in_off[net->edge_to[e]] + fill_in[net->edge_to[e]]++] = e;
+                int* d_ioff = b.template get<int>(V + 1);
+                int* d_iedge = b.template get<int>(E);
+                int* d_from = b.template get<int>(E);
+                HIP_OK(hipMemcpy(d_ioff, in_off.data(), 4 * (size_t)(V + 1), hipMemcpyHostToDevice));
+                HIP_OK(hipMemcpy(d_iedge, in_edge.data(), 4 * (size_t)E, hipMemcpyHostToDevice));
+                HIP_OK(hipMemcpy(d_from, net->edge_from, 4 * (size_t)E, hipMemcpyHostToDevice));
+                // frontier (2 V) and marks (V) per workgroup, as many workgroups as fit
+                const size_t per_wg = 3 * 4 * (size_t)V + 512;
+                const int g = (int)std::max<size_t>(1, std::min<size_t>({(size_t)nd, (size_t)1024, b.left() / per_wg}));
+                int* d_fq = b.template get<int>((size_t)g * 2 * V);
+                int* d_mk = b.template get<int>((size_t)g * V);
+                hipLaunchKernelGGL(k_route_dist_global, dim3(g), dim3(kRouteNT), 0, 0, V, d_ioff, d_iedge, d_from,
+                                   d_cost, d_dest, nd, d_dist, d_fq, d_mk);
+            } else {
+                hipLaunchKernelGGL(k_route_dist, dim3(std::min(nd, 2048)), dim3(kRouteNT), 0, 0, V, d_off, d_oe, d_to,
+                                   d_cost, d_dest, nd, d_dist);
+            }
+            HIP_OK(hipGetLastError());
+            hipLaunchKernelGGL(k_route_walk, dim3(std::max(1, std::min(4096, (n_queries + 255) / 256))), dim3(256), 0,
+                               0, V, d_off, d_oe, d_to, d_cost, d_dist, d_slot, d_o, d_d, n_queries, 0, d_len,
+                               (const int64_t*)nullptr, (int*)nullptr);
         }
-        HIP_OK(hipGetLastError());
-        const int gw = std::max(1, std::min(4096, (n_queries + 255) / 256));
-        hipLaunchKernelGGL(k_route_walk, dim3(gw), dim3(256), 0, 0, V, d_off, d_oe, d_to, d_cost, d_dist, d_slot, d_o,
-                           d_d, n_queries, 0, d_len, (const int64_t*)nullptr, (int*)nullptr);
         HIP_OK(hipGetLastError());
         std::vector<int> len(n_queries);
         HIP_OK(hipMemcpy(len.data(), d_len, 4 * (size_t)n_queries, hipMemcpyDeviceToHost));
@@ -1730,8 +1808,16 @@ void shortest_routes_impl(B& b, const sim_network* net, const float* edge_cost, 
         int64_t* d_roff = b.template get<int64_t>(n_queries + 1);
         int* d_re = b.template get<int>((size_t)route_off[n_queries]);
         HIP_OK(hipMemcpy(d_roff, route_off, 8 * (size_t)(n_queries + 1), hipMemcpyHostToDevice));
-        hipLaunchKernelGGL(k_route_walk, dim3(gw), dim3(256), 0, 0, V, d_off, d_oe, d_to, d_cost, d_dist, d_slot, d_o,
-                           d_d, n_queries, 1, d_len, (const int64_t*)d_roff, d_re);
+        if (tree) {
+            HIP_OK(hipFuncSetAttribute((const void*)k_route_write, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       2 * kRouteTreeNodes));
+            hipLaunchKernelGGL(k_route_write, dim3(nd), dim3(256), 2 * (size_t)V, 0, V, d_tab, d_out, d_oe, d_dest,
+                               d_qoff, d_qord, d_o, (const int64_t*)d_roff, d_re);
+        } else {
+            hipLaunchKernelGGL(k_route_walk, dim3(std::max(1, std::min(4096, (n_queries + 255) / 256))), dim3(256), 0,
+                               0, V, d_off, d_oe, d_to, d_cost, d_dist, d_slot, d_o, d_d, n_queries, 1, d_len,
+                               (const int64_t*)d_roff, d_re);
+        }
         HIP_OK(hipGetLastError());
         HIP_OK(hipMemcpy(route_edges, d_re, 4 * (size_t)route_off[n_queries], hipMemcpyDeviceToHost));
     }
@@ -1741,7 +1827,12 @@ void shortest_routes_impl(B& b, const sim_network* net, const float* edge_cost, 
 // copy until the process ends.  Host code reaches a device's copy through the
 // address hipGetSymbolAddress returns on that device, never through the name.
 constexpr size_t kRouteScratchBytes = (size_t)64 << 20;
-__device__ __align__(256) unsigned char scratch[kRouteScratchBytes];
+// At most kRouteTreeDeg out-edges a node, the arrays of k_route_tree take at
+// most 54 bytes a node more than those a call is charged for up to
+// kRouteMaxNodes nodes, and 38 above (in-edge records of 32 bytes, at most
+// one a node and one for each three edges): below 1.6 MB.
+constexpr size_t kRouteScratchSlack = (size_t)2 << 20;
+__device__ __align__(256) unsigned char scratch[kRouteScratchBytes + kRouteScratchSlack];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
@@ -1775,7 +1866,7 @@ extern "C" sim_status sim_shortest_routes_noalloc(const sim_network* net, const 
                                                   const int32_t* origin, const int32_t* dest, int64_t* route_off,
                                                   int32_t* route_edges, int64_t capacity, int64_t* n_route_edges) {
     return guarded(nullptr, [&] {
-        ScratchBufs b{(char*)route_scratch(), kRouteScratchBytes};
+        ScratchBufs b{(char*)route_scratch(), kRouteScratchBytes, kRouteScratchBytes + kRouteScratchSlack};
         shortest_routes_impl(b, net, edge_cost, n_queries, origin, dest, route_off, route_edges, capacity,
                              n_route_edges);
     });
