@@ -15,6 +15,7 @@
 
 #include "../../include/manta.h"
 #include "routing.hpp"
+#include "small_steps.hpp"
 #include "step_kernels.hpp"
 
 static_assert(manta::cNumCounters == SIM_N_COUNTERS, "device counters and sim_state.counters differ");
@@ -94,6 +95,15 @@ struct sim_handle {
     std::vector<void*> snaps;
     size_t snap_bytes = 0;
     int nq = 0;
+    // many steps per launch on a small network (k_small_steps)
+    bool small = false;
+    Small sm{};
+    size_t small_lds = 0;
+    int small_veh = 0;                // vehicles of the largest scenario
+    int small_max_dep = -1;
+    std::vector<int> small_due;       // [scenario][step]: vehicles due by then
+    std::vector<int> small_n;         // [scenario]: vehicles
+    int* arrived = nullptr;           // pinned, written by the device: [scenario] arrivals at the end of a launch
     // host copies of the static inputs needed for state I/O
     std::vector<int64_t> roff;
     std::vector<int32_t> redges, dep, lanes, lane_base, conn_off, conn_to, ins_lane;
@@ -123,6 +133,8 @@ struct sim_handle {
         graph = nullptr;
         exec_k = nullptr;
         graph_k = nullptr;
+        if (arrived) (void)hipHostFree(arrived);
+        arrived = nullptr;
         for (void* p : bufs) al.put(p);
         bufs.clear();
         for (void* p : snaps) al.put(p);
@@ -362,6 +374,114 @@ void capture_graph(sim_handle* h) {
         (which ? h->graph_k : h->graph) = g;
         HIP_OK(hipGraphInstantiate(which ? &h->exec_k : &h->exec, g, nullptr, nullptr, 0));
     }
+}
+
+// ---- many steps per launch on a small network --------------------------------
+// Whether k_small_steps can run the handle, and what it needs.  range: the
+// scenarios' first edge, lane, queue, node and vehicle, with the end of the
+// last.  max_edge: vehicles an edge may hold (one tile must hold it).
+void plan_small(sim_handle* h, const std::vector<SmallRange>& range, long long max_edge) {
+    Dev& d = h->d;
+    const int ns = (int)range.size() - 1;
+    if (ns < 1 || ns > kSmallScen || ns > h->g_big_max) return;
+    int lanes = 1, nodes = 0, nv = 0;
+    for (int k = 0; k < ns; ++k) {
+        const SmallRange &a = range[k], &b = range[k + 1];
+        if (b.edge - a.edge > kSmallEdges || b.lane - a.lane > kSmallLanes) return;
+        if (d.imode == 1 && b.node - a.node > kSmallNodes) return;
+        lanes = std::max(lanes, b.lane - a.lane);
+        if (d.imode == 1) nodes = std::max(nodes, b.node - a.node);
+        nv = std::max(nv, b.veh - a.veh);
+        h->small_n.push_back(b.veh - a.veh);
+    }
+    int dev = 0, lds_max = 0;
+    HIP_OK(hipGetDevice(&dev));
+    HIP_OK(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev));
+    hipFuncAttributes fa;
+    const void* f = d.v0_spread != 0.0f ? (const void*)k_small_steps<kSmallNT, true>
+                                        : (const void*)k_small_steps<kSmallNT, false>;
+    HIP_OK(hipFuncGetAttributes(&fa, f));
+    const size_t tables = small_table_bytes(lanes, nodes);
+    const long long room = (long long)lds_max - (long long)fa.sharedSizeBytes - (long long)tables - 64;
+    // no larger than the vehicles there are; the exits of a step share the tile's space (14 bytes a lane)
+    const int cap = (int)std::min<long long>(room / kTileBytesPerVeh, std::max({nv, kTileCapLds, lanes}));
+    if (cap < kTileCapLds || cap < lanes / 4 || (max_edge > cap && nv > cap)) return;
+    lanes = (lanes + 3) / 4 * 4;
+    h->small_lds = (size_t)cap * kTileBytesPerVeh + 64 + small_table_bytes(lanes, nodes);
+    if (h->small_lds + fa.sharedSizeBytes > (size_t)lds_max) return;
+    HIP_OK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max - (int)fa.sharedSizeBytes));
+    h->small_veh = nv;
+    h->small_max_dep = d.max_dep;
+    const int stride = std::max(1, d.max_dep + 1);
+    if (ns > 1 && (long long)ns * stride > (16ll << 20)) return;
+    if (ns > 1 || nv > kSmallActive) {
+        h->small_due.assign((size_t)ns * stride, 0);
+        for (int k = 0; k < ns; ++k) {
+            int* due = &h->small_due[(size_t)k * stride];
+            for (int i = range[k].veh; i < range[k + 1].veh; ++i) due[h->dep[i]]++;
+            for (int t = 1; t < stride; ++t) due[t] += due[t - 1];
+        }
+    }
+    Small& sm = h->sm;
+    sm.n_scen = ns;
+    sm.range = h->upload(range.data(), range.size());
+    sm.due = ns > 1 ? h->upload(h->small_due.data(), h->small_due.size()) : d.due;
+    sm.due_stride = ns > 1 ? stride : 0;
+    sm.q0 = h->upload(h->qoff.data(), h->qoff.size());
+    if (ns > 1) {
+        const size_t NV = (size_t)std::max(h->n_veh, 1);
+        sm.extra = Slots{h->dev<float>(NV), h->dev<float>(NV), h->dev<uint32_t>(NV), h->dev<int32_t>(NV),
+                         h->dev<uint32_t>(NV), h->dev<int32_t>(NV), h->dev<int32_t>(NV)};
+        sm.n = h->dev<int>(ns + 1);
+        sm.moved = h->dev<unsigned long long>((size_t)ns * kSmallWords);
+        sm.active = h->dev<unsigned long long>((size_t)ns * kSmallWords);
+    }
+    sm.cap = cap;
+    sm.lanes = lanes;
+    sm.nodes = nodes;
+    if (nv > kSmallActive) {
+        void* dp = nullptr;
+        HIP_OK(hipHostMalloc((void**)&h->arrived, sizeof(int) * (size_t)ns, hipHostMallocDefault));
+        HIP_OK(hipHostGetDevicePointer(&dp, h->arrived, 0));
+        for (int k = 0; k < ns; ++k) h->arrived[k] = 0;
+        sm.arrived = (int*)dp;
+    }
+    h->small = true;
+}
+
+// How many of the next `want` steps k_small_steps should take.  One workgroup
+// stages a scenario's vehicles tile by tile, so it is the faster way only
+// while a scenario has few on the road.  Known without waiting for the device:
+// at most the vehicles due by then less those that had arrived when the last
+// launch to finish wrote its count.
+int small_steps_ahead(const sim_handle* h, int want) {
+    if (!h->small) return 0;
+    const int most = std::min(want, kSmallSteps);
+    if (h->small_veh <= kSmallActive) return most;
+    const int ns = h->sm.n_scen, stride = h->small_max_dep + 1;
+    std::vector<int> here(ns);
+    for (int k = 0; k < ns; ++k) here[k] = ((volatile const int*)h->arrived)[k];
+    auto fits = [&](int s) {
+        for (int k = 0; k < ns; ++k)
+            if (h->small_n[k] > 0 &&
+                h->small_due[(size_t)k * stride + std::min(h->t + s - 1, stride - 1)] - here[k] > kSmallActive)
+                return false;
+        return true;
+    };
+    if (fits(most)) return most;
+    int lo = 0, hi = most;                        // fits(lo), not fits(hi)
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) / 2;
+        (fits(mid) ? lo : hi) = mid;
+    }
+    return lo >= 64 ? lo : 0;
+}
+
+void launch_small(sim_handle* h, const Dev& d, int steps) {
+    const auto f = d.v0_spread != 0.0f ? k_small_steps<kSmallNT, true> : k_small_steps<kSmallNT, false>;
+    hipLaunchKernelGGL(f, dim3(h->sm.n_scen), dim3(kSmallNT), h->small_lds, h->stream, d, h->sm, steps);
+    if (h->sm.n_scen > 1)
+        hipLaunchKernelGGL(k_small_gather, dim3(h->sm.n_scen), dim3(kSmallNT), 0, h->stream, d, h->sm, steps);
 }
 
 template <class F>
@@ -716,6 +836,22 @@ sim_status create_impl(const sim_network* net, const sim_routes* r, const sim_id
             std::vector<double> neg1(NV, -1.0);
             HIP_OK(hipMemcpy(d.tau_in, neg1.data(), sizeof(double) * NV, hipMemcpyHostToDevice));
             HIP_OK(hipMemcpy(d.t_arr, neg1.data(), sizeof(double) * NV, hipMemcpyHostToDevice));
+            {   // scenarios: edges, lanes, queues, nodes and vehicles in one piece each
+                const int np = d.edge_period, ns = std::max(1, E / np);
+                std::vector<SmallRange> range(ns + 1);
+                bool whole = ns * np == E && net->n_nodes % ns == 0;
+                for (int k = 0, q = 0, i = 0; k <= ns && whole; ++k) {
+                    range[k] = SmallRange{k * np, h->lane_base[k * np], 0, net->n_nodes / ns * k, 0};
+                    while (q < NQ && qlane[q] < range[k].lane) ++q;
+                    while (i < N && h->redges[h->roff[i]] < range[k].edge) ++i;
+                    range[k].queue = q;
+                    range[k].veh = i;
+                }
+                for (int k = 0; k < ns && whole; ++k)
+                    for (int i = range[k].veh; i < range[k + 1].veh; ++i)
+                        whole = whole && h->redges[h->roff[i]] >= range[k].edge;
+                if (whole && range[ns].veh == N) plan_small(h, range, max_edge);
+            }
             HIP_OK(hipDeviceSynchronize());
             capture_graph(h);
         } catch (...) {
@@ -754,6 +890,13 @@ sim_status sim_step(sim_handle* h, int32_t n) {
                 if (!p) throw Fail{SIM_ENOMEM, "no device memory for a checkpoint"};
                 h->snaps.push_back(p);
                 save_state(h, p);
+            }
+            const int to_rec = rec ? (h->t / h->rec_every + 1) * h->rec_every - h->t : n - q;
+            if (const int s = small_steps_ahead(h, std::min(n - q, to_rec))) {
+                launch_small(h, h->d, s);
+                h->t += s;
+                q += s;
+                continue;
             }
             // kGraphSteps at once unless a checkpoint falls strictly inside them
             const bool batch = n - q >= kGraphSteps &&
@@ -1039,6 +1182,12 @@ sim_status sim_write_state(sim_handle* h, const sim_state* in) {
         }
         HIP_OK(hipDeviceSynchronize());
         h->t = t;
+        if (h->arrived) {
+            std::vector<int> arr(h->sm.n_scen, 0);
+            for (int k = 0, i = 0; k < h->sm.n_scen; ++k)
+                for (const int end = i + h->small_n[k]; i < end; ++i) arr[k] += in->status[i] == kArrived;
+            for (int k = 0; k < h->sm.n_scen; ++k) h->arrived[k] = arr[k];
+        }
         for (void* p : h->snaps) h->al.put(p);
         h->snaps.clear();
         h->rec_broken = (t != 0);
@@ -1184,13 +1333,21 @@ sim_status sim_backward(sim_handle* h, const double* dL_dmean_tt, double* dL_dpa
             HIP_OK(e);
             HIP_OK(hipGraphInstantiate(&ge[which], gg[which], nullptr, nullptr, 0));
         };
+        // the traced re-run of a small network: one launch per segment
+        const bool small = h->small && h->sm.n_scen == 1 && h->small_veh <= kSmallActive;
         try {
-            for (int wch = 0; wch < 4; ++wch) capture(wch);
+            for (int wch = small ? 2 : 0; wch < 4; ++wch) capture(wch);
             bool a_is_in = true;                       // lx/lv are lam[0]/lam[1]
             for (int sg = nseg - 1; sg >= 0; --sg) {
                 const int t0 = sg * R, t1 = std::min(T, t0 + R);
                 load_state(h, h->snaps[sg], t0);
                 for (int t = t0; t < t1;) {
+                    if (small) {
+                        const int m = std::min(t1 - t, kSmallSteps);
+                        launch_small(h, traced, m);
+                        t += m;
+                        continue;
+                    }
                     const bool batch = t1 - t >= kGraphSteps;
                     HIP_OK(hipGraphLaunch(ge[batch ? 1 : 0], h->stream));
                     t += batch ? kGraphSteps : 1;

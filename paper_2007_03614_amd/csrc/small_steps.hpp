@@ -1,0 +1,282 @@
+// Many steps of a small network in one launch.
+//
+// A step of the whole network is four launches that hand over through device
+// memory: on a few hundred edges each lasts 4 to 14 us of launch, drain and
+// dependent round trips to memory, whatever it has to do.  Here one workgroup
+// runs every phase of one scenario (an ensemble: one workgroup each, as
+// scenarios never touch) for as many steps as the launch is given, with a
+// workgroup barrier where the four kernels have a launch boundary, the lanes'
+// tables in LDS and the rest in the caches of one XCD.  The phases are the
+// device functions of the four kernels, so the results are the same bit for
+// bit.  What bounds it: the chain of dependent steps of one workgroup.
+//
+// Measured per step, four launches against this: a 50-vehicle ring 17.6 and
+// 9.8 us, the 10x10 grid with 365 vehicles on the road 28.2 and 18.7, 32
+// scenarios of it with 4,500 on the road 28.5 and 17.1.
+#pragma once
+#include "step_kernels.hpp"
+
+namespace manta {
+
+constexpr int kSmallNT = 512;            // threads per workgroup
+constexpr int kSmallEdges = 1024;        // a scenario's edges, lanes and (case 1) nodes at most
+constexpr int kSmallLanes = 1024;
+constexpr int kSmallNodes = 1024;
+constexpr int kSmallSteps = 1024;        // steps of one launch at most
+constexpr int kSmallWords = kSmallSteps / 64;
+constexpr int kSmallScen = 256;          // scenarios at most: one workgroup per CU
+constexpr int kSmallActive = 3072;       // a scenario's vehicles on the road at most (a bound, see small_steps_ahead)
+
+struct SmallRange {                      // what scenario k owns starts here (and ends at the next one's)
+    int edge, lane, queue, node, veh;
+};
+
+struct Small {
+    int n_scen;
+    const SmallRange* range;             // [n_scen + 1]
+    const int* due;                      // [n_scen][due_stride]: own vehicles with departure step <= t
+    int due_stride;
+    const int* q0;                       // first index of each departure queue
+    Slots extra;                         // ensembles: the last step's layout, scenario k at its first vehicle
+    int* n;                              // ensembles: [n_scen] vehicles after the run, then the step reached
+    unsigned long long* moved;           // ensembles: [n_scen][kSmallWords] steps in which a vehicle moved
+    unsigned long long* active;          //   and steps that began with one
+    int* arrived;                        // host memory: [n_scen] arrivals so far (null: not wanted)
+    int cap, lanes, nodes;               // tile capacity, and the tables' entries in LDS
+};
+
+// LDS of the tables behind the tile: 60 bytes a lane, 8 a node
+__host__ __device__ inline size_t small_table_bytes(int lanes, int nodes) {
+    return (size_t)lanes * (sizeof(LaneRear) + sizeof(LanePost) + 8 + 5 * 4) + (size_t)nodes * 8;
+}
+
+__device__ inline Slots slots_at(const Slots& s, int o) {
+    return Slots{s.x + o, s.v + o, s.vid + o, s.edge + o, s.meta + o, s.nxt + o, s.gl + o};
+}
+
+// first slot of [0, n) on edge e or a later one
+__device__ inline int first_slot_of(const int32_t* edge, int n, int e) {
+    int lo = 0, hi = n;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (edge[mid] < e) lo = mid + 1;
+        else hi = mid;
+    }
+    return lo;
+}
+
+// what the kernels of the next step expect to find cleared
+__device__ inline void small_end_step(const Dev& d, int t) {
+    d.ctl->t_a = t;
+    d.ctl->t_b = t - 1;
+    d.ctl->n_big[0] = d.ctl->n_big[1] = 0;
+    d.ctl->big_done = 0;
+    d.ctl->n_defer = 0;
+    for (int k = 0; k < 2 * kTileGroups; ++k) tile_counters(d)[k * kTileCtrStride] = 0;
+}
+
+template <int NT, bool kSpread>
+__global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps) {
+    extern __shared__ __align__(16) char lds[];
+    __shared__ Scan4 wsh4[NT / 64];
+    __shared__ int wsh[2 * (NT / 64)];
+    __shared__ unsigned shc[cNumCounters];
+    __shared__ ClassParams scp[16];
+    __shared__ float slen[16];
+    __shared__ uint32_t dtask[2 * NT];
+    __shared__ int dcount[2];
+    __shared__ int smoved, sdep, stot;
+    const int tid = threadIdx.x, k = blockIdx.x;
+    const DrawQ dq{dtask, dcount, 2 * NT};
+    const SmallRange r0 = sm.range[k], r1 = sm.range[k + 1];
+    const int nl = r1.lane - r0.lane;
+    // the tile, where the exits of a step are kept once its tiles are done; then the lanes' tables
+    LaneTabs tb;
+    char* p = lds + (size_t)sm.cap * kTileBytesPerVeh + 64;
+    tb.rear = (LaneRear*)p;
+    p += sizeof(LaneRear) * (size_t)sm.lanes;
+    tb.post = (LanePost*)p;
+    p += sizeof(LanePost) * (size_t)sm.lanes;
+    tb.win = (unsigned long long*)p;
+    p += 8 * (size_t)sm.lanes;
+    tb.win_node = (unsigned long long*)p;
+    p += 8 * (size_t)sm.nodes;
+    tb.req_stamp = (int*)p;
+    tb.exit_stamp = tb.req_stamp + sm.lanes;
+    tb.enter_stamp = tb.exit_stamp + sm.lanes;
+    tb.lane_off = tb.enter_stamp + sm.lanes;
+    tb.lane_newcnt = tb.lane_off + sm.lanes;
+    tb.lane0 = r0.lane;
+    tb.node0 = r0.node;
+    double* const xtt = (double*)lds;
+    uint32_t* const xid = (uint32_t*)(xtt + sm.lanes);
+    uint16_t* const xnc = (uint16_t*)(xid + sm.lanes);
+
+    if (tid < cNumCounters) shc[tid] = 0;
+    if (tid < 2) dcount[tid] = 0;
+    if (tid == 0) smoved = sdep = 0;
+    if (tid < 16) {
+        scp[tid] = d.cp[tid];
+        slen[tid] = d.cp[tid].len;
+    }
+    for (int i = tid; i < nl; i += NT) {
+        tb.rear[i] = d.rear[r0.lane + i];
+        tb.post[i] = LanePost{-1, 0, 0, 0.0f};
+        tb.win[i] = ~0ull;
+        tb.req_stamp[i] = tb.exit_stamp[i] = tb.enter_stamp[i] = -1;
+    }
+    for (int i = tid; i < sm.nodes; i += NT) tb.win_node[i] = ~0ull;
+    const StepHead sh = step_head(d.ctl);
+    const int t0 = sh.t_a, par0 = t0 & 1;
+    const int n_all = par0 ? sh.n1 : sh.n0;
+    const bool alone = sm.n_scen == 1;
+    const int a0 = alone ? 0 : first_slot_of(d.s[par0].edge, n_all, r0.edge);
+    int n = (alone ? n_all : first_slot_of(d.s[par0].edge, n_all, r1.edge)) - a0;
+    __syncthreads();
+    // vehicles that have left the departure queues
+    int dep = 0;
+    for (int q = r0.queue + tid; q < r1.queue; q += NT) dep += d.qhead[q] - sm.q0[q];
+    if (dep) atomicAdd(&sdep, dep);
+    __syncthreads();
+    const int dep0 = sdep;
+    dep = dep0;
+    __syncthreads();
+    if (tid == 0) sdep = 0;
+    CounterAcc acc;
+    acc.zero();
+    unsigned long long act_sum = 0, denied = 0, grid_steps = 0, mv_bits = 0, ac_bits = 0;
+    int run = alone ? d.ctl->stall_run : 0;
+    Slots S = slots_at(d.s[par0], a0);
+    for (int j = 0; j < nsteps; ++j) {
+        const int t = t0 + j;
+        // an ensemble's scenarios write no buffer that another may still read as its first layout
+        const Slots B = alone ? d.s[(t + 1) & 1] : slots_at((nsteps - 1 - j) & 1 ? d.s[par0 ^ 1] : sm.extra, r0.veh);
+        if (d.trace && tid == 0) d.nact_hist[t % d.trace_period] = n;
+        tile_pieces<NT, kSpread, false>(d, tb, S, lds, sm.cap, 0, n, t, acc, wsh4, wsh, scp, dq, &smoved);
+        admit_items<NT, false>(d, tb, S, t, 0, 1, r0.lane, r1.lane, r0.queue, r1.queue);
+        __syncthreads();
+        int nnew = 0;
+        for (int e0 = r0.edge; e0 < r1.edge; e0 += NT) {
+            const int e = e0 + tid;
+            EdgeC ce{0.0f, 0.0f, r0.lane, 0};
+            int c = 0;
+            if (e < r1.edge) {
+                ce = d.ec[e];
+                const int l = ce.lane_base - r0.lane;
+                const unsigned was = acc.c[cDeparted];
+                c = commit_edge(d, tb, S, e, ce, t, acc, xid + l, xtt + l, xnc + l, &smoved);
+                if (acc.c[cDeparted] != was) atomicAdd(&sdep, (int)(acc.c[cDeparted] - was));
+            }
+            const Scan4 sc = wg_exclusive_scan4<NT>(Scan4{c, -1, -1, -1}, wsh4);
+            int o = nnew + sc.s;
+            for (int l = ce.lane_base - r0.lane, q = 0; q < ce.lanes; ++q) {
+                tb.lane_off[l + q] = o;
+                o += xnc[l + q];
+            }
+            if (tid == NT - 1) stot = nnew + sc.s + c;
+            __syncthreads();
+            nnew = stot;
+        }
+        for (int i = tid; i < max(n, nl); i += NT)
+            scatter_item(d, tb, S, B, i < n ? i : -1, i < nl ? r0.lane + i : -1, nnew, t, slen, [](int) { return 0; });
+        if (d.imode == 1)
+            for (int i = tid; i < sm.nodes; i += NT) tb.win_node[i] = ~0ull;
+        if (tid == 0) {
+            act_sum += (unsigned long long)n;
+            dep += sdep;
+            sdep = 0;
+            const int due = d.max_dep < 0 ? 0 : sm.due[(size_t)k * sm.due_stride + min(t, d.max_dep)];
+            if (due > dep) denied += (unsigned long long)(due - dep);
+            const bool mv = smoved != 0;
+            smoved = 0;
+            if (alone) {
+                run = n > 0 && !mv ? run + 1 : 0;
+                grid_steps += run >= kGridlockSteps ? 1ull : 0ull;
+            } else {
+                mv_bits |= (unsigned long long)mv << (j & 63);
+                ac_bits |= (unsigned long long)(n > 0) << (j & 63);
+                if ((j & 63) == 63 || j == nsteps - 1) {
+                    sm.moved[(size_t)k * kSmallWords + (j >> 6)] = mv_bits;
+                    sm.active[(size_t)k * kSmallWords + (j >> 6)] = ac_bits;
+                    mv_bits = ac_bits = 0;
+                }
+            }
+        }
+        __syncthreads();
+        n = nnew;
+        S = B;
+    }
+    for (int i = tid; i < nl; i += NT) d.rear[r0.lane + i] = tb.rear[i];
+    if (tid == 0) {
+        atomicAdd(&d.counters[cActiveSum * kCounterCopies], act_sum);
+        if (denied) atomicAdd(&d.counters[cInsertDenied * kCounterCopies], denied);
+        atomicAdd(&d.ctl->n_departed, dep - dep0);
+        if (sm.arrived) sm.arrived[k] = dep - n;
+        if (alone) {
+            if (grid_steps) d.counters[cGridlock * kCounterCopies] += grid_steps;
+            d.ctl->stall_run = run;
+            d.ctl->n_act[(t0 + nsteps) & 1] = n;
+            small_end_step(d, t0 + nsteps);
+        } else {
+            sm.n[k] = n;
+            if (k == 0) sm.n[sm.n_scen] = t0 + nsteps;
+        }
+    }
+    flush_counters_lds(d, acc, shc);
+}
+
+// Ensembles: the scenarios' last layouts, one after another, and the end of
+// the run (control block, gridlock detector over all scenarios).
+__global__ void __launch_bounds__(kSmallNT) k_small_gather(Dev d, Small sm, int nsteps) {
+    __shared__ int scnt[kSmallScen + 1];
+    __shared__ unsigned long long smv[kSmallWords], sac[kSmallWords];
+    const int tid = threadIdx.x, k = blockIdx.x;
+    for (int i = tid; i < sm.n_scen; i += kSmallNT) scnt[i] = sm.n[i];
+    if (tid < kSmallWords) smv[tid] = sac[tid] = 0;
+    __syncthreads();
+    int o = 0, total = 0;
+    for (int i = 0; i < sm.n_scen; ++i) {
+        if (i == k) o = total;
+        total += scnt[i];
+    }
+    const int t = sm.n[sm.n_scen];
+    const Slots A = slots_at(sm.extra, sm.range[k].veh), B = slots_at(d.s[t & 1], o);
+    for (int i = tid; i < scnt[k]; i += kSmallNT) {
+        B.x[i] = A.x[i];
+        B.v[i] = A.v[i];
+        B.vid[i] = A.vid[i];
+        B.edge[i] = A.edge[i];
+        B.meta[i] = A.meta[i];
+        B.nxt[i] = A.nxt[i];
+    }
+    if (k != 0) return;
+    const int nw = (nsteps + 63) / 64;
+    for (int i = tid; i < sm.n_scen * nw; i += kSmallNT) {
+        const int s = i / nw, w = i % nw;
+        atomicOr(&smv[w], sm.moved[(size_t)s * kSmallWords + w]);
+        atomicOr(&sac[w], sm.active[(size_t)s * kSmallWords + w]);
+    }
+    __syncthreads();
+    if (tid != 0) return;
+    int run = d.ctl->stall_run;
+    unsigned long long grid_steps = 0;
+    for (int w = 0; w < nw; ++w) {
+        const int m = min(64, nsteps - 64 * w);
+        const unsigned long long all = m == 64 ? ~0ull : (1ull << m) - 1ull;
+        const unsigned long long stalled = sac[w] & ~smv[w] & all;
+        if (stalled == 0ull) {
+            run = 0;
+            continue;
+        }
+        for (int j = 0; j < m; ++j) {
+            run = (stalled >> j) & 1ull ? run + 1 : 0;
+            grid_steps += run >= kGridlockSteps ? 1ull : 0ull;
+        }
+    }
+    if (grid_steps) d.counters[cGridlock * kCounterCopies] += grid_steps;
+    d.ctl->stall_run = run;
+    d.ctl->n_act[t & 1] = total;
+    small_end_step(d, t);
+}
+
+}  // namespace manta

@@ -276,6 +276,27 @@ struct Dev {
     int big_cap;                // vehicles per workgroup region
 };
 
+// The tables of one step by lane (and by node, case 1).  The kernels of the
+// whole network index them by global lane; the kernel that keeps one
+// scenario in a workgroup holds its own lanes' tables in LDS, the first
+// being lane0 (node0).
+struct LaneTabs {
+    LaneRear* rear;
+    LanePost* post;
+    int* req_stamp;
+    unsigned long long* win;
+    int* exit_stamp;
+    int* enter_stamp;
+    int* lane_off;
+    int* lane_newcnt;
+    unsigned long long* win_node;
+    int lane0, node0;
+};
+__device__ inline LaneTabs lane_tabs(const Dev& d) {
+    return LaneTabs{d.rear, d.post, d.req_stamp, d.win, d.exit_stamp, d.enter_stamp, d.lane_off, d.lane_newcnt,
+                    d.win_node, 0, 0};
+}
+
 // k_tile_step's tile counters: after the movement stamps, 128-byte aligned
 // (the stamps take 256 bytes), in the same allocation
 __host__ __device__ inline int* tile_counters(const Dev& d) { return d.moved_at + kMovedSlots; }
@@ -632,10 +653,9 @@ __device__ inline void finish_pending(const TileBuf& b, int q, int dir, const fl
 // kSpread: the per-driver limits may be on (a kernel of its own, so that the
 // common case carries none of their code)
 template <int NT, bool kSpread>
-__device__ inline void process_tile(const Dev& d, const TileBuf& b, int a0, int n, int t, int par,
-                                    CounterAcc& acc, Scan4* wsh4, const ClassParams* scp, const DrawQ& dq,
+__device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slots& S, const TileBuf& b, int a0, int n,
+                                    int t, CounterAcc& acc, Scan4* wsh4, const ClassParams* scp, const DrawQ& dq,
                                     int* smoved) {
-    const Slots S = d.s[par];
     const int tid = threadIdx.x;
     const int dir = (t % 2 == 0) ? -1 : 1;
 
@@ -880,7 +900,7 @@ __device__ inline void process_tile(const Dev& d, const TileBuf& b, int a0, int 
         const int look_i = lw_base(b.lbf[q]) + min(lam, lw_lanes(b.lbf[q]) - 1);
         const bool pre = f >= 0 && (mv != 0 || q == rs);
         LaneRear rp{0.0f, 0.0f, -1, 0u};
-        if (pre) rp = d.rear[look_i];
+        if (pre) rp = tb.rear[look_i - tb.lane0];
         int j, newpos, lane_start;
         bool quiet = false;
         if (!mv) {
@@ -962,7 +982,7 @@ __device__ inline void process_tile(const Dev& d, const TileBuf& b, int a0, int 
             s = b.L[q] - xi;
             vl = 0.0f;
         } else {
-            const LaneRear r = pre ? rp : d.rear[look_i];
+            const LaneRear r = pre ? rp : tb.rear[look_i - tb.lane0];
             if (r.stamp == t) {
                 kind = kLook;
                 s = (b.L[q] - xi) + r.xm;
@@ -1061,7 +1081,7 @@ __device__ inline void process_tile(const Dev& d, const TileBuf& b, int a0, int 
                     lp.start = a0 + fr;
                     lp.cnt = r - fr + 1;
                     lp.rear_xm = xnew - scp[m_cls(b.meta[q])].len;
-                    d.post[gl] = lp;
+                    tb.post[gl - tb.lane0] = lp;
                 }
                 if (front && xnew >= b.L[q] && !(b.fl[q] & F_WHOLD)) {
                     const int f = b.nxt[q];
@@ -1088,7 +1108,7 @@ __device__ inline void process_tile(const Dev& d, const TileBuf& b, int a0, int 
                         ob.key = ((unsigned long long)(uint32_t)hs << 32) | ob.vid;
                     }
                     d.outbox[gl] = ob;
-                    d.req_stamp[gl] = t;
+                    tb.req_stamp[gl - tb.lane0] = t;
                 }
             }
         }
@@ -1187,7 +1207,8 @@ __device__ inline void tile_step(const Dev& d) {
             return;
         }
         if (cnt <= kTileCapLds) {
-            process_tile<kTileNT, kSpread>(d, carve(lds, kTileCapLds), a0, cnt, t, par, acc, wsh4, scp, dq, &smoved);
+            process_tile<kTileNT, kSpread>(d, lane_tabs(d), d.s[par], carve(lds, kTileCapLds), a0, cnt, t, acc, wsh4, scp,
+                                           dq, &smoved);
         } else {
             if (threadIdx.x == 0) {
                 const int q = atomicAdd(&d.ctl->n_big[par], 1);
@@ -1241,9 +1262,53 @@ __global__ void __launch_bounds__(kTileNT) __attribute__((amdgpu_waves_per_eu(6)
     tile_step<true>(d);
 }
 
+// The slots [a0, a1) of whole edges, cut at edge boundaries into pieces of at
+// most cap vehicles staged in LDS; only a single edge larger than that runs
+// from the workgroup's global-memory scratch (kScratch: there may be one).
+template <int NT, bool kSpread, bool kScratch>
+__device__ __forceinline__ void tile_pieces(const Dev& d, const LaneTabs& tb, const Slots& S, char* lds, int cap,
+                                            int a0, int a1, int t, CounterAcc& acc, Scan4* wsh4, int* wsh,
+                                            const ClassParams* scp, const DrawQ& dq, int* smoved) {
+    const int32_t* edge = S.edge;
+    int pos = a0;
+    while (pos < a1) {
+        const int lim = min(a1, pos + cap);
+        int end;
+        if (lim == a1) {
+            end = a1;
+        } else {
+            // last edge start in (pos, lim]
+            end = -1;
+            for (int base = lim; base > pos && end < 0; base -= NT) {
+                const int s = base - (int)threadIdx.x;
+                const bool f = (s > pos) && (s < a1) && edge[s] != edge[s - 1];
+                const unsigned long long bal = __ballot(f);
+                const int wave = threadIdx.x >> 6;
+                __syncthreads();
+                if ((threadIdx.x & 63) == 0) wsh[wave] = bal ? (base - wave * 64 - (__ffsll((long long)bal) - 1)) : -1;
+                __syncthreads();
+                int m = -1;
+                for (int w = 0; w < NT / 64; ++w) m = max(m, wsh[w]);
+                __syncthreads();
+                end = m;
+            }
+            if (end < 0) end = first_edge_start<NT>(edge, lim, a1, wsh);   // one edge beyond the LDS
+        }
+        const int cnt = end - pos;
+        if (cnt <= cap) {
+            process_tile<NT, kSpread>(d, tb, S, carve(lds, cap), pos, cnt, t, acc, wsh4, scp, dq, smoved);
+        } else if (kScratch && cnt <= d.big_cap) {
+            char* mine = d.big + (size_t)blockIdx.x * tile_bytes(d.big_cap);
+            process_tile<NT, kSpread>(d, tb, S, carve(mine, d.big_cap), pos, cnt, t, acc, wsh4, scp, dq, smoved);
+        } else if (threadIdx.x == 0) {             // more vehicles than the edge can physically hold
+            atomicOr(&d.ctl->err, kErrTileTooBig);
+        }
+        pos = end;
+    }
+}
+
 // Tiles above kTileCapLds: 1,024-thread workgroups with kBigCapLds vehicles
-// of LDS; a tile is cut at edge boundaries into pieces that fit, and only a
-// single edge larger than the LDS runs from the global-memory scratch.
+// of LDS.
 __device__ __forceinline__ void big_tiles(const Dev& d, int t, int par, int nbig) {
     __shared__ __align__(16) char lds[kBigCapLds * kTileBytesPerVeh + 64];
     __shared__ Scan4 wsh4[kBigNT / 64];
@@ -1264,57 +1329,26 @@ __device__ __forceinline__ void big_tiles(const Dev& d, int t, int par, int nbig
     acc.zero();
     for (int k = blockIdx.x; k < nbig; k += gridDim.x) {
         const int a0 = d.big_list[2 * k], a1 = d.big_list[2 * k + 1];
-        int pos = a0;
-        while (pos < a1) {
-            const int lim = min(a1, pos + kBigCapLds);
-            int end;
-            if (lim == a1) {
-                end = a1;
-            } else {
-                // last edge start in (pos, lim]
-                end = -1;
-                for (int base = lim; base > pos && end < 0; base -= kBigNT) {
-                    const int s = base - (int)threadIdx.x;
-                    const bool f = (s > pos) && (s < a1) && edge[s] != edge[s - 1];
-                    const unsigned long long bal = __ballot(f);
-                    const int wave = threadIdx.x >> 6;
-                    __syncthreads();
-                    if ((threadIdx.x & 63) == 0) wsh[wave] = bal ? (base - wave * 64 - (__ffsll((long long)bal) - 1)) : -1;
-                    __syncthreads();
-                    int m = -1;
-                    for (int w = 0; w < kBigNT / 64; ++w) m = max(m, wsh[w]);
-                    __syncthreads();
-                    end = m;
-                }
-                if (end < 0) end = first_edge_start<kBigNT>(edge, lim, a1, wsh);   // one edge beyond the LDS
-            }
-            const int cnt = end - pos;
-            if (threadIdx.x == 0) atomicAdd(&d.ctl->big_updates, (unsigned long long)cnt);
-            if (cnt <= kBigCapLds) {
-                process_tile<kBigNT, true>(d, carve(lds, kBigCapLds), pos, cnt, t, par, acc, wsh4, scp, dq, &smoved);
-            } else {
-                char* mine = d.big + (size_t)blockIdx.x * tile_bytes(d.big_cap);
-                process_tile<kBigNT, true>(d, carve(mine, d.big_cap), pos, cnt, t, par, acc, wsh4, scp, dq, &smoved);
-            }
-            pos = end;
-        }
+        if (threadIdx.x == 0) atomicAdd(&d.ctl->big_updates, (unsigned long long)(a1 - a0));
+        tile_pieces<kBigNT, true, true>(d, lane_tabs(d), d.s[par], lds, kBigCapLds, a0, a1, t, acc, wsh4, wsh, scp, dq,
+                                  &smoved);
     }
     flush_counters_lds(d, acc, shc);
     publish_moved(d, &smoved, t);
 }
 
 // ---- admission -------------------------------------------------------------
-__device__ inline bool transfer_eligible(const Dev& d, const Outbox& ob, int t) {
-    const LanePost p = d.post[ob.target];
+__device__ inline bool transfer_eligible(const LaneTabs& tb, const Outbox& ob, int t) {
+    const LanePost p = tb.post[ob.target - tb.lane0];
     return p.stamp != t || (p.rear_xm - ob.xp >= 0.0f);
 }
 
 // An eligible request lowers the lane's 64-bit key with atomicMin; the
 // smallest key wins whatever the order of the atomics.  The lane is marked
 // claimed for this step.
-__device__ inline void claim(const Dev& d, int gl, unsigned long long key, int t) {
-    atomicMin(&d.win[gl], key);
-    d.enter_stamp[gl] = t;   // every claimant stores the same step
+__device__ inline void claim(const LaneTabs& tb, int gl, unsigned long long key, int t) {
+    atomicMin(&tb.win[gl - tb.lane0], key);
+    tb.enter_stamp[gl - tb.lane0] = t;   // every claimant stores the same step
 }
 
 // Grid barrier of k_big_admit: every workgroup is resident (one per CU at
@@ -1357,8 +1391,8 @@ __device__ inline void defer_item(const Dev& d, int k, int item) {
 // in a big tile is left out (that tile's workgroup writes its request and
 // admits it), and a target lane in a big tile is left to that tile's
 // workgroup.
-template <int NT, bool kDefer>
-__device__ inline void admit_request(const Dev& d, int i, int t) {
+template <bool kDefer>
+__device__ inline void admit_request(const Dev& d, const LaneTabs& tb, const Slots& S, int i, int t) {
     if (kDefer && d.big_lane[i].x == t) return;
     const Outbox ob = d.outbox[i];
     if (ob.target < 0) return;                    // an arrival
@@ -1369,13 +1403,13 @@ __device__ inline void admit_request(const Dev& d, int i, int t) {
             return;
         }
     }
-    bool ok = transfer_eligible(d, ob, t);
+    bool ok = transfer_eligible(tb, ob, t);
     if (d.imode == 1) {
         // case 1: only after standing stop_steps at the line (the key's
         // step is the held-since step, t if not held); one crossing per
         // node, its (in, out) pairs served round-robin after the last
         // served one: key = (distance in the cycle, held since, source lane)
-        const int e = d.s[t & 1].edge[ob.slot], f = ob.nxt;
+        const int e = S.edge[ob.slot], f = ob.nxt;
         const int node = d.efrom[f], nmv = d.nm[node];
         const int pr = d.pair_base[e] + d.out_idx[f];
         int dd = (pr - d.rr[node] - 1) % nmv;
@@ -1387,17 +1421,17 @@ __device__ inline void admit_request(const Dev& d, int i, int t) {
         d.outbox[i].key = nk;
         d.outbox[i].elig = ok ? 1 + node : 0;
         d.outbox[i].tl_cls = ob.tl_cls | ((uint32_t)pr << 16);
-        if (ok) atomicMin(&d.win_node[node], nk);
+        if (ok) atomicMin(&tb.win_node[node - tb.node0], nk);
         return;
     }
     d.outbox[i].elig = ok ? 1 : 0;
-    if (ok) claim(d, ob.target, ob.key, t);
+    if (ok) claim(tb, ob.target, ob.key, t);
 }
 
 // Admission of a due departure-queue head (departure step hd.x, id hd.y):
 // it claims the queue's lane if the lane's rear leaves it s0 at x = 0.
 template <bool kDefer>
-__device__ inline void admit_head(const Dev& d, int q, int2 hd, int t) {
+__device__ inline void admit_head(const Dev& d, const LaneTabs& tb, int q, int2 hd, int t) {
     const int gl = d.qlane[q];
     if (kDefer) {
         const int2 bl = d.big_lane[gl];
@@ -1406,13 +1440,13 @@ __device__ inline void admit_head(const Dev& d, int q, int2 hd, int t) {
             return;
         }
     }
-    const LanePost p = d.post[gl];
+    const LanePost p = tb.post[gl - tb.lane0];
     if (p.stamp != t || p.rear_xm >= d.qs0[q])
-        claim(d, gl, (1ull << 63) | ((unsigned long long)(uint32_t)hd.x << 32) | (uint32_t)hd.y, t);
+        claim(tb, gl, (1ull << 63) | ((unsigned long long)(uint32_t)hd.x << 32) | (uint32_t)hd.y, t);
 }
 
-// One item per lane (its front may have asked to leave the edge this step)
-// and one per departure queue, over workgroups wg of nwg.  A request is
+// One item per lane of [l0, l1) (its front may have asked to leave the edge
+// this step) and one per departure queue of [q00, q1), over workgroups wg of nwg.  A request is
 // eligible if it does not overlap the target lane's rear after the move; a
 // due queue head if the lane's rear leaves it s0 at x = 0.  Each thread takes
 // its items four at a time and loads their stamps (queue heads) together, so
@@ -1421,34 +1455,34 @@ __device__ inline void admit_head(const Dev& d, int q, int2 hd, int t) {
 // per-thread array is indexed by a runtime value (which would put it in
 // scratch memory).
 template <int NT, bool kDefer>
-__device__ inline void admit_items(const Dev& d, int t, int wg, int nwg) {
+__device__ inline void admit_items(const Dev& d, const LaneTabs& tb, const Slots& S, int t, int wg, int nwg, int l0,
+                                   int l1, int q00, int q1) {
     constexpr int kU = 4;
-    const int nl = d.n_lanes_total, nq = d.nq;
     const int stride = nwg * NT;
-    for (int i0 = wg * NT + threadIdx.x; i0 < nl; i0 += kU * stride) {
+    for (int i0 = l0 + wg * NT + (int)threadIdx.x; i0 < l1; i0 += kU * stride) {
         unsigned due = 0;
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             const int i = i0 + u * stride;
-            if (i < nl && d.req_stamp[i] == t) due |= 1u << u;
+            if (i < l1 && tb.req_stamp[i - tb.lane0] == t) due |= 1u << u;
         }
         while (due) {
             const int u = __builtin_ctz(due);
             due &= due - 1;
-            admit_request<NT, kDefer>(d, i0 + u * stride, t);
+            admit_request<kDefer>(d, tb, S, i0 + u * stride, t);
         }
     }
-    for (int q0 = wg * NT + threadIdx.x; q0 < nq; q0 += kU * stride) {
+    for (int q0 = q00 + wg * NT + (int)threadIdx.x; q0 < q1; q0 += kU * stride) {
         unsigned due = 0;
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             const int q = q0 + u * stride;
-            if (q < nq && d.qhd[q].x <= t) due |= 1u << u;
+            if (q < q1 && d.qhd[q].x <= t) due |= 1u << u;
         }
         while (due) {
             const int q = q0 + __builtin_ctz(due) * stride;
             due &= due - 1;
-            admit_head<kDefer>(d, q, d.qhd[q], t);
+            admit_head<kDefer>(d, tb, q, d.qhd[q], t);
         }
     }
 }
@@ -1458,7 +1492,7 @@ __device__ inline void admit_items(const Dev& d, int t, int wg, int nwg) {
 // itself done and waits until every workgroup has (the admission workgroups
 // after listing their items, the other big tiles after writing their
 // requests and rears), like the grid barrier and bounded the same way.
-__device__ inline void admit_big_tile(const Dev& d, int t, int par, int k) {
+__device__ inline void admit_big_tile(const Dev& d, const LaneTabs& tb, int t, int par, int k) {
     grid_barrier(d, &d.ctl->big_done, true);
     const int a0 = d.big_list[2 * k], a1 = d.big_list[2 * k + 1];
     const int32_t* edge = d.s[par].edge;
@@ -1467,7 +1501,8 @@ __device__ inline void admit_big_tile(const Dev& d, int t, int par, int k) {
         if (s == a0 || edge[s - 1] != e) {
             const EdgeC c = d.ec[e];
             for (int l = 0; l < c.lanes; ++l)
-                if (d.req_stamp[c.lane_base + l] == t) admit_request<kBigNT, false>(d, c.lane_base + l, t);
+                if (d.req_stamp[c.lane_base + l] == t)
+                    admit_request<false>(d, tb, d.s[par], c.lane_base + l, t);
         }
     }
     const int nd = __hip_atomic_load(&d.ctl->n_defer, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1476,8 +1511,8 @@ __device__ inline void admit_big_tile(const Dev& d, int t, int par, int k) {
         const unsigned long long en = __hip_atomic_load(&d.big_defer[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if ((int)(en >> 32) != k) continue;
         const int item = (int)(uint32_t)en;
-        if (item < nl) admit_request<kBigNT, false>(d, item, t);
-        else admit_head<false>(d, item - nl, d.qhd[item - nl], t);
+        if (item < nl) admit_request<false>(d, tb, d.s[par], item, t);
+        else admit_head<false>(d, tb, item - nl, d.qhd[item - nl], t);
     }
 }
 
@@ -1496,18 +1531,20 @@ __global__ void __launch_bounds__(kBigNT) k_big_admit(Dev d) {
     const int t = d.ctl->t_a, par = t & 1;
     const int nbig = par ? nb2.y : nb2.x;
     const bool all_big = nbig >= (int)gridDim.x;
+    const LaneTabs tb = lane_tabs(d);
+    const int nl = d.n_lanes_total, nq = d.nq;
     if (nbig == 0) {
-        admit_items<kBigNT, false>(d, t, blockIdx.x, gridDim.x);
+        admit_items<kBigNT, false>(d, tb, d.s[par], t, blockIdx.x, gridDim.x, 0, nl, 0, nq);
     } else if (all_big || (int)blockIdx.x < nbig) {
         big_tiles(d, t, par, nbig);                 // one call site: inlined, no call frame
         if (all_big) {
             grid_barrier(d, &d.ctl->big_done, true);
-            admit_items<kBigNT, false>(d, t, blockIdx.x, gridDim.x);
+            admit_items<kBigNT, false>(d, tb, d.s[par], t, blockIdx.x, gridDim.x, 0, nl, 0, nq);
         } else {
-            admit_big_tile(d, t, par, blockIdx.x);  // tile blockIdx.x
+            admit_big_tile(d, tb, t, par, blockIdx.x);  // tile blockIdx.x
         }
     } else {
-        admit_items<kBigNT, true>(d, t, blockIdx.x - nbig, gridDim.x - nbig);
+        admit_items<kBigNT, true>(d, tb, d.s[par], t, blockIdx.x - nbig, gridDim.x - nbig, 0, nl, 0, nq);
         __builtin_amdgcn_s_waitcnt(0);              // every wave's listed items and stores first
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -1526,35 +1563,31 @@ __global__ void __launch_bounds__(kBigNT) k_big_admit(Dev d) {
 // The edge's travel-time sum adds the exits in ascending vehicle id (at most
 // one per lane; kept in LDS and sorted there when an edge has several).
 // Lanes without a request cost three 4-byte stamps and their post-move count.
-__device__ inline void commit_block(const Dev& d, int blk, int t, int par, CounterAcc& acc, Scan4* wsh4,
-                                    uint32_t* xid, double* xtt, uint16_t* xnc, int* smoved) {
-    const Slots S = d.s[par];
-    const int e = blk * kEdgeBlock + (int)threadIdx.x;
-    uint32_t* myid = xid + threadIdx.x * kCommitLanes;
-    double* mytt = xtt + threadIdx.x * kCommitLanes;
-    uint16_t* mync = xnc + threadIdx.x * kCommitLanes;
-    int c = 0, nex = 0, nl = 0, base = 0;
-    if (e < d.n_edges) {
-        const EdgeC ce = d.ec[e];
-        nl = ce.lanes;
-        base = ce.lane_base;
+// Returns the edge's vehicles in the next layout, its lane counts in mync.
+// myid, mytt: room for one exit per lane.
+__device__ inline int commit_edge(const Dev& d, const LaneTabs& tb, const Slots& S, int e, const EdgeC& ce, int t,
+                                  CounterAcc& acc, uint32_t* myid, double* mytt, uint16_t* mync, int* smoved) {
+    int c = 0, nex = 0;
+    const int nl = ce.lanes, base = ce.lane_base;
+    {
         int node_win = -1;                         // case 1: lane index of this node's winning crossing
         if (d.imode == 1) {
-            const unsigned long long wn = d.win_node[d.efrom[e]];
+            const unsigned long long wn = tb.win_node[d.efrom[e] - tb.node0];
             if (wn != ~0ull) node_win = d.outbox[(int)(wn & ((1ull << 26) - 1))].target;
         }
         // each lane's three stamps are loaded one lane ahead
-        LanePost pn = d.post[base];
-        int rn = d.req_stamp[base], en = d.enter_stamp[base];
+        const int b0 = base - tb.lane0;
+        LanePost pn = tb.post[b0];
+        int rn = tb.req_stamp[b0], en = tb.enter_stamp[b0];
         for (int l = 0; l < nl; ++l) {
             const int gl = base + l;
             const LanePost p = pn;
             const bool req = rn == t;
             bool claimed = en == t;
             if (l + 1 < nl) {
-                pn = d.post[gl + 1];
-                rn = d.req_stamp[gl + 1];
-                en = d.enter_stamp[gl + 1];
+                pn = tb.post[b0 + l + 1];
+                rn = tb.req_stamp[b0 + l + 1];
+                en = tb.enter_stamp[b0 + l + 1];
             }
             const int pcnt = p.stamp == t ? p.cnt : 0;
             bool exits = false;
@@ -1573,10 +1606,10 @@ __device__ inline void commit_block(const Dev& d, int blk, int t, int par, Count
                 }
                 bool won;
                 if (d.imode == 1) {
-                    won = ob.target >= 0 && ob.elig && d.win_node[ob.elig - 1] == ob.key;
+                    won = ob.target >= 0 && ob.elig && tb.win_node[ob.elig - 1 - tb.node0] == ob.key;
                     if (won) d.rr[ob.elig - 1] = (int)((ob.tl_cls >> 16) & 255u);   // the pair just served
                 } else {
-                    won = ob.target >= 0 && ob.elig && d.win[ob.target] == ob.key;
+                    won = ob.target >= 0 && ob.elig && tb.win[ob.target - tb.lane0] == ob.key;
                 }
                 const bool arrived = ob.target < 0;
                 if (d.trace)
@@ -1603,7 +1636,7 @@ __device__ inline void commit_block(const Dev& d, int blk, int t, int par, Count
                 acc.c[cHolds] += exits ? 0u : 1u;
                 if (exits) *smoved = 1;                 // gridlock detector
                 if (exits) {
-                    d.exit_stamp[gl] = t;
+                    tb.exit_stamp[b0 + l] = t;
                     const double tau = ((double)t + (double)ob.phi) * (double)d.dt;
                     myid[nex] = ob.vid;
                     mytt[nex] = tau - tin;
@@ -1632,7 +1665,7 @@ __device__ inline void commit_block(const Dev& d, int blk, int t, int par, Count
             // claim lanes, and this node's crossing into the lane comes first
             const bool transfer_in = node_win == gl;
             if (claimed && !transfer_in) {
-                const unsigned long long w = d.win[gl];
+                const unsigned long long w = tb.win[b0 + l];
                 if (w >> 63) {
                     const int vid = (int)(uint32_t)w;
                     const int4 vq = d.vq[vid];     // vid is the head of queue vq.x
@@ -1657,12 +1690,12 @@ __device__ inline void commit_block(const Dev& d, int blk, int t, int par, Count
                     *smoved = 1;
                 }
             }
-            if (transfer_in && !claimed) d.enter_stamp[gl] = t;   // the scatter takes the crossing's record
+            if (transfer_in && !claimed) tb.enter_stamp[b0 + l] = t;   // the scatter takes the crossing's record
             claimed = claimed || transfer_in;
             // next layout: this lane's count (its offset follows the block scan)
             const int nc = pcnt - (exits ? 1 : 0) + (claimed ? 1 : 0);
             mync[l] = (uint16_t)nc;
-            d.lane_newcnt[gl] = nc;
+            tb.lane_newcnt[b0 + l] = nc;
             c += nc;
         }
         if (nex > 0) {
@@ -1682,11 +1715,27 @@ __device__ inline void commit_block(const Dev& d, int blk, int t, int par, Count
             d.tt_cnt[e] += (unsigned long long)nex;
         }
     }
-    // offsets of the edges in the workgroup, then of their lanes
+    return c;
+}
+
+// The edges of one block: one thread per edge, then the offsets of the edges
+// in the workgroup and of their lanes.
+__device__ inline void commit_block(const Dev& d, int blk, int t, int par, CounterAcc& acc, Scan4* wsh4,
+                                    uint32_t* xid, double* xtt, uint16_t* xnc, int* smoved) {
+    const int e = blk * kEdgeBlock + (int)threadIdx.x;
+    const LaneTabs tb = lane_tabs(d);
+    uint16_t* const mync = xnc + threadIdx.x * kCommitLanes;
+    EdgeC ce{0.0f, 0.0f, 0, 0};
+    int c = 0;
+    if (e < d.n_edges) {
+        ce = d.ec[e];
+        c = commit_edge(d, tb, d.s[par], e, ce, t, acc, xid + threadIdx.x * kCommitLanes,
+                        xtt + threadIdx.x * kCommitLanes, mync, smoved);
+    }
     const Scan4 run = wg_exclusive_scan4<kCommitNT>(Scan4{c, -1, -1, -1}, wsh4);
     int o = run.s;
-    for (int l = 0; l < nl; ++l) {
-        d.lane_off[base + l] = o;
+    for (int l = 0; l < ce.lanes; ++l) {
+        d.lane_off[ce.lane_base + l] = o;
         o += mync[l];
     }
     if (threadIdx.x == kCommitNT - 1) d.blk_sum[blk] = run.s + c;
@@ -1805,7 +1854,7 @@ __global__ void __launch_bounds__(kBigNT) k_blkscan(Dev d) {
 // ---- next layout -----------------------------------------------------------
 // One record of the next layout at slot dst, and the lane's rear for the
 // next step's look-ahead if it is the lane's last vehicle.
-__device__ inline void put_record(const Dev& d, const Slots& B, int dst, int nnew, float x, float v, uint32_t vid,
+__device__ inline void put_record(const Dev& d, const LaneTabs& tb, const Slots& B, int dst, int nnew, float x, float v, uint32_t vid,
                                   int edge, uint32_t meta, int nxt, bool is_rear, int gl, int t, const float* slen) {
     if (dst < 0 || dst >= nnew) {
         atomicOr(&d.ctl->err, kErrScatter);
@@ -1823,7 +1872,64 @@ __device__ inline void put_record(const Dev& d, const Slots& B, int dst, int nne
         lr.v = v;
         lr.stamp = t + 1;
         lr.vid = vid;
-        d.rear[gl] = lr;
+        tb.rear[gl - tb.lane0] = lr;
+    }
+}
+
+// The record in slot k (none: -1), and lane i (none: -1), which takes the
+// record that entered it if it was claimed this step.  Each round of loads of
+// the two is issued together: the record with its lane and the lane's claim
+// stamp; then the tables of the record's lane and the entry of a claimed lane.
+// off(edge): where the offsets of that edge's lanes count from.
+template <class Off>
+__device__ inline void scatter_item(const Dev& d, const LaneTabs& tb, const Slots& A, const Slots& B, int k, int i,
+                                    int nnew, int t, const float* slen, Off off) {
+    const bool hv = k >= 0;
+    float x = 0.0f, v = 0.0f;
+    uint32_t vid = 0, meta = 0;
+    int edge = 0, nxt = 0, gl = 0;
+    if (hv) {
+        meta = A.meta[k];
+        edge = A.edge[k];
+        x = A.x[k];
+        v = A.v[k];
+        vid = A.vid[k];
+        nxt = A.nxt[k];
+        gl = A.gl[k];
+    }
+    const int g0 = gl - tb.lane0, i0 = i - tb.lane0;
+    const bool claimed = i >= 0 && tb.enter_stamp[i0] == t;
+    LanePost lp{};
+    int ex = 0, ncnt = 0, loff = 0;
+    bool entered = false;
+    if (hv) {
+        lp = tb.post[g0];
+        ex = tb.exit_stamp[g0] == t ? 1 : 0;
+        ncnt = tb.lane_newcnt[g0];
+        entered = tb.enter_stamp[g0] == t;
+        loff = tb.lane_off[g0];
+    }
+    EntryRec en{};
+    int encnt = 0, enoff = 0;
+    if (claimed) {
+        en = d.ent[i];
+        encnt = tb.lane_newcnt[i0];
+        enoff = tb.lane_off[i0];
+    }
+    if (hv) {
+        const int r = k - lp.start;
+        if (lp.stamp != t) {
+            atomicOr(&d.ctl->err, kErrScatter);
+        } else if (!(ex && r == 0)) {         // unless the lane's front left the edge
+            const int nr = r - ex;
+            put_record(d, tb, B, off(edge) + loff + nr, nnew, x, v, vid, edge, meta, nxt, (nr == ncnt - 1) && !entered,
+                       gl, t, slen);
+        }
+    }
+    if (claimed) {                            // the entry is the lane's new rear
+        put_record(d, tb, B, off(en.edge) + enoff + encnt - 1, nnew, en.x, en.v, en.vid, en.edge, en.meta, en.nxt, true,
+                   i, t, slen);
+        tb.win[i0] = ~0ull;                   // lane free for the next step's claims
     }
 }
 
@@ -1853,59 +1959,12 @@ __device__ inline void scatter_items(const Dev& d, int* soff, Scan4* wsh4, int* 
         __syncthreads();                          // slen
     }
     const Slots A = d.s[par], B = d.s[par ^ 1];
-    // Item k is the record in slot k (k < nold) and lane k (k < nl), which
-    // takes the record that entered it if it was claimed this step.  Each
-    // round of loads of the two is issued together: the record with its lane
-    // and the lane's claim stamp; then the tables of the record's lane and
-    // the entry of a claimed lane.
+    const LaneTabs tb = lane_tabs(d);
+    // item k is the record in slot k (k < nold) and lane k (k < nl)
     const int nit = max(nold, nl);
     for (int k = blockIdx.x * kNT + threadIdx.x; k < nit; k += gridDim.x * kNT) {
-        const bool hv = k < nold;
-        float x = 0.0f, v = 0.0f;
-        uint32_t vid = 0, meta = 0;
-        int edge = 0, nxt = 0, gl = 0;
-        if (hv) {
-            meta = A.meta[k];
-            edge = A.edge[k];
-            x = A.x[k];
-            v = A.v[k];
-            vid = A.vid[k];
-            nxt = A.nxt[k];
-            gl = A.gl[k];
-        }
-        const bool claimed = k < nl && d.enter_stamp[k] == t;
-        LanePost lp{};
-        int ex = 0, ncnt = 0, loff = 0;
-        bool entered = false;
-        if (hv) {
-            lp = d.post[gl];
-            ex = d.exit_stamp[gl] == t ? 1 : 0;
-            ncnt = d.lane_newcnt[gl];
-            entered = d.enter_stamp[gl] == t;
-            loff = d.lane_off[gl];
-        }
-        EntryRec en{};
-        int encnt = 0, enoff = 0;
-        if (claimed) {
-            en = d.ent[k];
-            encnt = d.lane_newcnt[k];
-            enoff = d.lane_off[k];
-        }
-        if (hv) {
-            const int r = k - lp.start;
-            if (lp.stamp != t) {
-                atomicOr(&d.ctl->err, kErrScatter);
-            } else if (!(ex && r == 0)) {         // unless the lane's front left the edge
-                const int nr = r - ex;
-                put_record(d, B, boff[edge / kEdgeBlock] + loff + nr, nnew, x, v, vid, edge, meta, nxt,
-                           (nr == ncnt - 1) && !entered, gl, t, slen);
-            }
-        }
-        if (claimed) {                            // the entry is the lane's new rear
-            put_record(d, B, boff[en.edge / kEdgeBlock] + enoff + encnt - 1, nnew, en.x, en.v, en.vid, en.edge,
-                       en.meta, en.nxt, true, k, t, slen);
-            d.win[k] = ~0ull;                     // lane free for the next step's claims
-        }
+        scatter_item(d, tb, A, B, k < nold ? k : -1, k < nl ? k : -1, nnew, t, slen,
+                     [&](int edge) { return boff[edge / kEdgeBlock]; });
     }
 }
 
