@@ -404,7 +404,8 @@ void plan_small(sim_handle* h, const std::vector<SmallRange>& range, long long m
     const size_t tables = small_table_bytes(lanes, nodes);
     const long long room = (long long)lds_max - (long long)fa.sharedSizeBytes - (long long)tables - 64;
     // no larger than the vehicles there are; the exits of a step share the tile's space (14 bytes a lane)
-    const int cap = (int)std::min<long long>(room / kTileBytesPerVeh, std::max({nv, kTileCapLds, lanes}));
+    // (and a multiple of 4, which keeps the tables behind it aligned)
+    const int cap = (int)std::min<long long>(room / kTileBytesPerVeh, std::max({nv, kTileCapLds, lanes}) + 3) / 4 * 4;
     if (cap < kTileCapLds || cap < lanes / 4 || (max_edge > cap && nv > cap)) return;
     lanes = (lanes + 3) / 4 * 4;
     h->small_lds = (size_t)cap * kTileBytesPerVeh + 64 + small_table_bytes(lanes, nodes);

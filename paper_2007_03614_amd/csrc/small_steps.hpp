@@ -42,7 +42,7 @@ struct Small {
     unsigned long long* moved;           // ensembles: [n_scen][kSmallWords] steps in which a vehicle moved
     unsigned long long* active;          //   and steps that began with one
     int* arrived;                        // host memory: [n_scen] arrivals so far (null: not wanted)
-    int cap, lanes, nodes;               // tile capacity, and the tables' entries in LDS
+    int cap, lanes, nodes;               // tile capacity (a multiple of 4), and the tables' entries in LDS
 };
 
 // LDS of the tables behind the tile: 60 bytes a lane, 8 a node

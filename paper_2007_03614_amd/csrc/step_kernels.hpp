@@ -313,10 +313,9 @@ struct TileBuf {
                         //   Phase 2: start of the post-change lane's run
     int* mpref;         // movers before index q (n + 1 entries)
     int* lml;           // last mover (low 16 bits) and last stayer (high 16 bits) at or before q, or -1
-    int* rk;            // index of q's run (maximal group of one edge and lane in S_t)
-    uint32_t* run_el;   // per run: edge << 4 | lane; run_el[nruns] = ~0
-    int* run_st;        // per run: first index; run_st[nruns] = n
-    int* nruns;         // [1]
+    uint32_t* rk;       // q's run (maximal group of one edge and lane in S_t) | first run of its edge << 16
+    uint32_t* run_st;   // per run: first index; run_st[runs] = n.  An edge's first run also has the set of its
+                        //   lanes with a run, << 16
     float* xn;          // Phase 2 position
     uint32_t* fl;       // Phase 2 flags
     uint32_t* pel;      // post-change (edge, lane), permuted to the new order
@@ -336,7 +335,7 @@ __device__ inline int lw_lanes(uint32_t w) { return (int)(w >> kLaneBaseBits); }
 __device__ inline int lastm_of(const int* lml, int i) { return (int)(short)(lml[i] & 0xFFFF); }
 __device__ inline int lasts_of(const int* lml, int i) { return lml[i] >> 16; }
 
-constexpr int kTileBytesPerVeh = 80;   // 20 four-byte arrays (plus a few words within the 64-byte slack)
+constexpr int kTileBytesPerVeh = 76;   // 19 four-byte arrays (plus a few words within the 64-byte slack)
 __host__ __device__ inline size_t tile_bytes(int cap) { return (size_t)cap * kTileBytesPerVeh + 64; }
 
 __device__ inline TileBuf carve(char* base, int cap) {
@@ -352,10 +351,8 @@ __device__ inline TileBuf carve(char* base, int cap) {
     b.pm = (int*)take(cap);
     b.mpref = (int*)take(cap + 1);
     b.lml = (int*)take(cap);
-    b.rk = (int*)take(cap);
-    b.run_el = (uint32_t*)take(cap + 1);
-    b.run_st = (int*)take(cap + 1);
-    b.nruns = (int*)take(1);
+    b.rk = (uint32_t*)take(cap);
+    b.run_st = (uint32_t*)take(cap + 1);
     b.xn = (float*)take(cap);
     b.fl = (uint32_t*)take(cap);
     b.pel = (uint32_t*)take(cap);
@@ -370,27 +367,22 @@ __device__ inline TileBuf carve(char* base, int cap) {
 // flags of Phase 2
 constexpr uint32_t F_WHOLD = 1u, F_VEH = 2u;
 
-// Index of the first run whose key is not below `key`, where key is a lane
-// of the edge of run k0 or one past its last lane.  An edge has at most 8
-// lanes, so that run lies within 8 runs of k0: a few independent LDS reads
-// instead of a search of the tile.
-__device__ inline int run_lower(const TileBuf& b, int nruns, int k0, uint32_t key) {
-    int k = k0;
-    if (key > b.run_el[k0]) {
-#pragma unroll
-        for (int j = 1; j <= 8; ++j) {
-            const int kk = k0 + j;
-            if (kk <= nruns && b.run_el[kk] < key) k = kk;
-        }
-        return k + 1;
-    }
-#pragma unroll
-    for (int j = 1; j <= 8; ++j) {
-        const int kk = k0 - j;
-        if (kk >= 0 && b.run_el[kk] >= key) k = kk;
-    }
-    return k;
+// The runs of a vehicle's edge: its first run, the set of its lanes that have
+// one, and (as an edge's runs are in lane order) where any lane's run starts.
+// Two dependent LDS reads, and one for each lane asked for.
+struct EdgeRuns {
+    int k0;             // the edge's first run
+    uint32_t lanes;
+    int first;          // first index of the edge
+};
+__device__ inline EdgeRuns edge_runs(const TileBuf& b, uint32_t rkq) {
+    const int k0 = (int)(rkq >> 16);
+    const uint32_t w = b.run_st[k0];
+    return EdgeRuns{k0, w >> 16, (int)(w & 0xFFFFu)};
 }
+__device__ inline int run_start(const TileBuf& b, int k) { return (int)(b.run_st[k] & 0xFFFFu); }
+// the first run of the edge's lane l or a later one (l up to its lane count), or of the next edge
+__device__ inline int run_of_lane(const EdgeRuns& r, int l) { return r.k0 + __popc(r.lanes & ((1u << l) - 1u)); }
 
 // first index in [lo, hi), part of one run, that does not precede (x, id)
 // in the tile order (x descending, id descending)
@@ -442,11 +434,30 @@ __device__ inline int wave_incl_max(int x) {
     return x;
 }
 
-// exclusive workgroup scan of one Scan4 per thread (all NT threads take
-// part); wsh: NT/64 Scan4 in LDS
+// the same within each row of 16 lanes
+__device__ inline int row_incl_sum(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, kDppRowShr + 1, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, kDppRowShr + 2, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, kDppRowShr + 4, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, kDppRowShr + 8, 0xf, 0xf, false);
+    return x;
+}
+__device__ inline int row_incl_max(int x) {
+    x = max(x, __builtin_amdgcn_update_dpp(-1, x, kDppRowShr + 1, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(-1, x, kDppRowShr + 2, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(-1, x, kDppRowShr + 4, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(-1, x, kDppRowShr + 8, 0xf, 0xf, false));
+    return x;
+}
+
+// Exclusive workgroup scan of one Scan4 per thread (all NT threads take
+// part); wsh: NT/64 Scan4 in LDS, free again after the caller's next barrier.
+// The waves' totals are scanned by every wave at once, one per lane: a loop
+// over the waves before it would wait for one LDS read after another.
 template <int NT = kNT>
 __device__ inline Scan4 wg_exclusive_scan4(Scan4 v, Scan4* wsh) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    static_assert(NT / 64 <= 16, "the waves' totals fill one row of lanes");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     Scan4 inc;
     inc.s = wave_incl_sum(v.s);
     inc.a = wave_incl_max(v.a);
@@ -454,9 +465,15 @@ __device__ inline Scan4 wg_exclusive_scan4(Scan4 v, Scan4* wsh) {
     inc.c = wave_incl_max(v.c);
     if (lane == 63) wsh[wave] = inc;
     __syncthreads();
+    const Scan4 tot = wsh[min(lane, NT / 64 - 1)];
     Scan4 carry{0, -1, -1, -1};
-    for (int w = 0; w < wave; ++w) carry = scan4_op(carry, wsh[w]);
-    __syncthreads();
+    const Scan4 upto{row_incl_sum(tot.s), row_incl_max(tot.a), row_incl_max(tot.b), row_incl_max(tot.c)};
+    if (wave > 0) {
+        carry.s = __builtin_amdgcn_readlane(upto.s, wave - 1);
+        carry.a = __builtin_amdgcn_readlane(upto.a, wave - 1);
+        carry.b = __builtin_amdgcn_readlane(upto.b, wave - 1);
+        carry.c = __builtin_amdgcn_readlane(upto.c, wave - 1);
+    }
     Scan4 exc;
     exc.s = inc.s - v.s;
     exc.a = __builtin_amdgcn_update_dpp(-1, inc.a, kDppWaveShr1, 0xf, 0xf, false);   // lane 0 gets -1
@@ -705,42 +722,45 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
         }
     }
     __syncthreads();
+
+    // ---- runs of S_t (tile order: edge, lane, then x and id descending)
+    {
+        const int chunk = (n + NT - 1) / NT;
+        const int lo = min(n, tid * chunk), hi = min(n, lo + chunk);
+        Scan4 loc{0, -1, -1, -1};                 // run starts; the last edge start
+        for (int q = lo; q < hi; ++q) {
+            const uint32_t el = b.el[q], before = q > 0 ? b.el[q - 1] : ~0u;
+            loc.s += el != before ? 1 : 0;
+            if (el >> 4 != before >> 4) loc.a = q;
+        }
+        const Scan4 r = wg_exclusive_scan4<NT>(loc, wsh4);
+        int k = r.s - 1, es = r.a;
+        for (int q = lo; q < hi; ++q) {
+            const uint32_t el = b.el[q], before = q > 0 ? b.el[q - 1] : ~0u;
+            if (el >> 4 != before >> 4) es = q;
+            if (el != before) b.run_st[++k] = (uint32_t)q;
+            b.rk[q] = (uint32_t)k | ((uint32_t)es << 16);
+        }
+        if (hi == n && lo < hi) b.run_st[k + 1] = (uint32_t)n;
+        if (n == 0 && tid == 0) b.run_st[0] = 0u;
+    }
+    __syncthreads();
+    // each edge's first run takes the set of its lanes; rk refers to that run
+    // instead of the edge's first index (the low half stays, so that it may be
+    // read by others meanwhile)
+    for (int q = tid; q < n; q += NT) {
+        const uint32_t rkq = b.rk[q];
+        const uint32_t k = rkq & 0xFFFFu, k0 = b.rk[rkq >> 16] & 0xFFFFu;
+        if (q == 0 || b.el[q - 1] != b.el[q]) atomicOr(&b.run_st[k0], 1u << (16u + (b.el[q] & 15u)));
+        b.rk[q] = k | (k0 << 16);
+    }
     draw_run<NT>(d, dq, 0, t, b, u1, na, nb);
     if (kSpread && d.v0_spread != 0.0f)   // each driver's own limit on its edge (Sec. IV)
         for (int q = tid; q < n; q += NT) {
             const int e = (int)(b.el[q] >> 4);
             b.lim[q] = driver_limit(b.lim[q], d.v0_spread, d.seed, e, d.edge_period, draw_id(d, b.vid[q], e));
         }
-
-    // ---- runs of S_t (tile order: edge, lane, then x and id descending)
-    {
-        const int chunk = (n + NT - 1) / NT;
-        const int lo = min(n, tid * chunk), hi = min(n, lo + chunk);
-        int loc = 0;
-        for (int q = lo; q < hi; ++q) loc += (q == 0 || b.el[q] != b.el[q - 1]) ? 1 : 0;
-        const Scan4 r = wg_exclusive_scan4<NT>(Scan4{loc, -1, -1, -1}, wsh4);
-        int k = r.s - 1;
-        for (int q = lo; q < hi; ++q) {
-            if (q == 0 || b.el[q] != b.el[q - 1]) {
-                ++k;
-                b.run_el[k] = b.el[q];
-                b.run_st[k] = q;
-            }
-            b.rk[q] = k;
-        }
-        if (hi == n && lo < hi) {
-            b.run_el[k + 1] = ~0u;
-            b.run_st[k + 1] = n;
-            *b.nruns = k + 1;
-        }
-        if (n == 0 && tid == 0) {
-            b.run_el[0] = ~0u;
-            b.run_st[0] = 0;
-            *b.nruns = 0;
-        }
-    }
     __syncthreads();
-    const int nruns = *b.nruns;
 
     // ---- Phase 1: lane-change decisions (Eqs. (2)-(4)) against S_t
     for (int q = tid; q < n; q += NT) {
@@ -770,16 +790,18 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
             }
             const int lp = l + dir;
             if (lp >= 0 && lp < lw_lanes(b.lbe[q])) {
-                const uint32_t elp = (el & ~15u) | (uint32_t)lp;
-                const int kp = run_lower(b, nruns, b.rk[q], elp);
-                pos = b.run_st[kp];
-                if (b.run_el[kp] == elp) pos = run_insert(b, pos, b.run_st[kp + 1], xi, b.vid[q]);
-                const int la = (pos > 0 && b.el[pos - 1] == elp) ? pos - 1 : -1;
-                const int lb = (pos < n && b.el[pos] == elp) ? pos : -1;
+                const uint32_t rkq = b.rk[q];
+                const EdgeRuns er = edge_runs(b, rkq);
+                const int kp = run_of_lane(er, lp);
+                const bool used = (er.lanes >> lp) & 1u;
+                const int ps = run_start(b, kp), pe = used ? run_start(b, kp + 1) : ps;
+                pos = run_insert(b, ps, pe, xi, b.vid[q]);
+                const int la = pos > ps ? pos - 1 : -1;
+                const int lb = pos < pe ? pos : -1;
                 const uint32_t mask = f < 0 ? 0xFFu : m_mask(m);
                 bool desire = !allowed_l && (lane_distance(mask, lp) < lane_distance(mask, l));
                 const bool allowed_lp = lane_allowed(m, f, lp);
-                const int lc = (q > 0 && b.el[q - 1] == el) ? q - 1 : -1;
+                const int lc = q > run_start(b, (int)(rkq & 0xFFFFu)) ? q - 1 : -1;
                 // with no leader in its own lane a vehicle already has the free
                 // acceleration, which no leader in the other lane can beat
                 // (Eq. (1) only subtracts from it): no incentive to compute
@@ -887,12 +909,12 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
         uint32_t m = b.meta[q];
         const int f = b.nxt[q];
         const int lanes_e = lw_lanes(b.lbe[q]);
-        const uint32_t e0 = el & ~15u;
         // leader and position in the post-change order.  On an edge where no
         // vehicle changes lanes (most edges of a step) both stay as in S_t:
         // the leader is the vehicle before in the same run, the position q.
-        const int k0 = b.rk[q];
-        const int rs = b.run_st[k0];
+        const uint32_t rkq = b.rk[q];
+        const EdgeRuns er = edge_runs(b, rkq);
+        const int rs = run_start(b, (int)(rkq & 0xFFFFu));
         // the start-of-step rear of the lane it would look into with no leader
         // on the tile, loaded now so that the round trip overlaps the leader
         // search: for a lane's first vehicle and for the movers, the vehicles
@@ -904,9 +926,8 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
         int j, newpos, lane_start;
         bool quiet = false;
         if (!mv) {
-            const int es_q = b.run_st[run_lower(b, nruns, k0, e0)];
-            const int ee_q = b.run_st[run_lower(b, nruns, k0, e0 + 16u)];   // first slot of the next edge
-            quiet = b.mpref[ee_q] == b.mpref[es_q];
+            const int ee = run_start(b, er.k0 + __popc(er.lanes));           // first slot of the next edge
+            quiet = b.mpref[ee] == b.mpref[er.first];
             if (quiet) {
                 j = q > rs ? q - 1 : -1;
                 newpos = q;
@@ -923,17 +944,16 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
                 if (q > 0 && lasts_of(b.lml, q - 1) >= rs) c1 = lasts_of(b.lml, q - 1);
                 int mov_ahead = 0;
                 if (mu >= 0 && mu < lanes_e) {
-                    const uint32_t emu = e0 | (uint32_t)mu;
-                    const int kmu = run_lower(b, nruns, k0, emu);
-                    const int st = b.run_st[kmu];
-                    const int p2 = (b.run_el[kmu] == emu) ? run_insert(b, st, b.run_st[kmu + 1], xi, id) : st;
+                    const int kmu = run_of_lane(er, mu);
+                    const int st = run_start(b, kmu);
+                    const int p2 = (er.lanes >> mu) & 1u ? run_insert(b, st, run_start(b, kmu + 1), xi, id) : st;
                     if (p2 > 0 && lastm_of(b.lml, p2 - 1) >= st) c2 = lastm_of(b.lml, p2 - 1);
                     mov_ahead = b.mpref[p2] - b.mpref[st];
                 }
                 rank = ((q - rs) - (b.mpref[q] - b.mpref[rs])) + mov_ahead;
             } else {
                 const int p = b.pm[q] & 0xFFFF;
-                const int st = b.run_st[run_lower(b, nruns, k0, elam)];
+                const int st = run_start(b, run_of_lane(er, lam));
                 sl = st;
                 if (p > 0 && lasts_of(b.lml, p - 1) >= st) c1 = lasts_of(b.lml, p - 1);
                 if (q > 0 && lastm_of(b.lml, q - 1) >= rs) c2 = lastm_of(b.lml, q - 1);
@@ -945,14 +965,12 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
                 else if (b.x[c2] < b.x[j] || (b.x[c2] == b.x[j] && b.vid[c2] < b.vid[j])) j = c2;
             }
             // post-change vehicles of this edge in lanes below lam
-            const int es = b.run_st[run_lower(b, nruns, k0, e0)];
+            const int es = er.first;
             int below = sl - es;
             if (dir < 0) {
-                const int ee = b.run_st[run_lower(b, nruns, k0, elam + 1)];
-                below += b.mpref[ee] - b.mpref[sl];
+                below += b.mpref[run_start(b, run_of_lane(er, lam + 1))] - b.mpref[sl];
             } else if (lam >= 1) {
-                const int s0 = b.run_st[run_lower(b, nruns, k0, elam - 1)];
-                below -= b.mpref[sl] - b.mpref[s0];
+                below -= b.mpref[sl] - b.mpref[run_start(b, run_of_lane(er, lam - 1))];
             }
             newpos = es + below + rank;
             lane_start = es + below;
@@ -1770,25 +1788,7 @@ __global__ void __launch_bounds__(kCommitNT) k_commit(Dev d) {
 // written by k_commit, a previous kernel, so no fence is needed: no workgroup
 // waits for another inside a kernel, which on a GPU of several L2 caches
 // would cost a write-back of the L2 at every release.
-template <int NT>
-__device__ inline int scan_block_sums(const int* blk_sum, int nb, int* off, Scan4* wsh4, int* tot) {
-    const int chunk = (nb + NT - 1) / NT;
-    const int lo = min(nb, (int)threadIdx.x * chunk), hi = min(nb, lo + chunk);
-    int loc = 0;
-    for (int i = lo; i < hi; ++i) loc += blk_sum[i];
-    const Scan4 r = wg_exclusive_scan4<NT>(Scan4{loc, -1, -1, -1}, wsh4);
-    int o = r.s;
-    for (int i = lo; i < hi; ++i) {
-        off[i] = o;
-        o += blk_sum[i];
-    }
-    if (hi == nb && lo < hi) *tot = o;
-    __syncthreads();
-    return *tot;
-}
-
-// The same for many blocks (one workgroup, global output): the counts go
-// through `stage` (LDS, cap entries per round), read coalesced with every
+// The counts go through `stage` (LDS, cap entries per round), read coalesced with every
 // load of a thread in flight together, scanned there by contiguous chunks
 // and written back coalesced.  With tens of blocks per thread, reading each
 // thread's contiguous chunk straight from memory would wait for one load
