@@ -82,7 +82,8 @@ struct sim_handle {
     std::string err;
     Dev d{};
     int t = 0;
-    int n_veh = 0, n_edges = 0, n_lanes = 0, n_classes = 0;
+    int n_veh = 0, n_edges = 0, n_classes = 0;
+    int n_lanes = 0, lanes_real = 0;   // lane numbers (with gaps), and lanes
     int g_tile = 1, g_big = 1, g_scatter = 1, n_blk = 1;
     size_t scatter_lds = 0;   // dynamic LDS of k_scatter<true>: the block offsets
     int g_big_min = 1, g_big_max = 1, g_scatter_max = 1, g_scatter_res = 1;
@@ -265,7 +266,7 @@ void launch_step(sim_handle* h, hipStream_t s, hipEvent_t* ev = nullptr) {
         hipLaunchKernelGGL(d.v0_spread != 0.0f ? k_tile_step_v0spread : k_tile_step, dim3(h->g_tile), dim3(kTileNT),
                            0, s, d);
         hipLaunchKernelGGL(k_big_admit, dim3(h->g_big), dim3(kBigNT), 0, s, d);
-        hipLaunchKernelGGL(k_commit, dim3(h->n_blk), dim3(kCommitNT), 0, s, d);
+        hipLaunchKernelGGL(k_commit, dim3(h->n_blk), dim3(kLaneBlock), 0, s, d);
         if (lds_scan) {
             hipLaunchKernelGGL(k_scatter<true>, dim3(h->g_scatter), b, h->scatter_lds, s, d);
         } else {
@@ -278,10 +279,10 @@ void launch_step(sim_handle* h, hipStream_t s, hipEvent_t* ev = nullptr) {
                           0, s, ev[0], ev[1], 0, d);
     hipExtLaunchKernelGGL(k_big_admit, dim3(h->g_big), dim3(kBigNT), 0, s, ev[2], ev[3], 0, d);
     if (lds_scan) {
-        hipExtLaunchKernelGGL(k_commit, dim3(h->n_blk), dim3(kCommitNT), 0, s, ev[4], ev[5], 0, d);
+        hipExtLaunchKernelGGL(k_commit, dim3(h->n_blk), dim3(kLaneBlock), 0, s, ev[4], ev[5], 0, d);
         hipExtLaunchKernelGGL(k_scatter<true>, dim3(h->g_scatter), b, h->scatter_lds, s, ev[6], ev[7], 0, d);
     } else {   // the block scan is counted with commit
-        hipExtLaunchKernelGGL(k_commit, dim3(h->n_blk), dim3(kCommitNT), 0, s, ev[4], nullptr, 0, d);
+        hipExtLaunchKernelGGL(k_commit, dim3(h->n_blk), dim3(kLaneBlock), 0, s, ev[4], nullptr, 0, d);
         hipExtLaunchKernelGGL(k_blkscan, dim3(1), dim3(kBigNT), 0, s, nullptr, ev[5], 0, d);
         hipExtLaunchKernelGGL(k_scatter<false>, dim3(h->g_scatter), b, 0, s, ev[6], ev[7], 0, d);
     }
@@ -384,7 +385,7 @@ void plan_small(sim_handle* h, const std::vector<SmallRange>& range, long long m
     Dev& d = h->d;
     const int ns = (int)range.size() - 1;
     if (ns < 1 || ns > kSmallScen || ns > h->g_big_max) return;
-    int lanes = 1, nodes = 0, nv = 0;
+    int lanes = 1, nodes = 0, nv = 0, nq = 0;
     for (int k = 0; k < ns; ++k) {
         const SmallRange &a = range[k], &b = range[k + 1];
         if (b.edge - a.edge > kSmallEdges || b.lane - a.lane > kSmallLanes) return;
@@ -392,8 +393,10 @@ void plan_small(sim_handle* h, const std::vector<SmallRange>& range, long long m
         lanes = std::max(lanes, b.lane - a.lane);
         if (d.imode == 1) nodes = std::max(nodes, b.node - a.node);
         nv = std::max(nv, b.veh - a.veh);
+        nq = std::max(nq, b.queue - a.queue);
         h->small_n.push_back(b.veh - a.veh);
     }
+    lanes = (lanes + 3) / 4 * 4;
     int dev = 0, lds_max = 0;
     HIP_OK(hipGetDevice(&dev));
     HIP_OK(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev));
@@ -403,13 +406,12 @@ void plan_small(sim_handle* h, const std::vector<SmallRange>& range, long long m
     HIP_OK(hipFuncGetAttributes(&fa, f));
     const size_t tables = small_table_bytes(lanes, nodes);
     const long long room = (long long)lds_max - (long long)fa.sharedSizeBytes - (long long)tables - 64;
-    // no larger than the vehicles there are; the exits of a step share the tile's space (14 bytes a lane)
+    // no larger than the vehicles there are; the exits of a step (16 bytes a lane) and its claiming queues share
+    // the tile's space
     // (and a multiple of 4, which keeps the tables behind it aligned)
-    const int cap = (int)std::min<long long>(room / kTileBytesPerVeh, std::max({nv, kTileCapLds, lanes}) + 3) / 4 * 4;
-    if (cap < kTileCapLds || cap < lanes / 4 || (max_edge > cap && nv > cap)) return;
-    lanes = (lanes + 3) / 4 * 4;
+    const int cap = (int)std::min<long long>(room / kTileBytesPerVeh, std::max({nv, kTileCapLds, (16 * lanes + 4 * nq) / kTileBytesPerVeh + 1}) + 3) / 4 * 4;
+    if (cap < kTileCapLds || cap * kTileBytesPerVeh < 16 * lanes + 4 * nq || (max_edge > cap && nv > cap)) return;
     h->small_lds = (size_t)cap * kTileBytesPerVeh + 64 + small_table_bytes(lanes, nodes);
-    if (h->small_lds + fa.sharedSizeBytes > (size_t)lds_max) return;
     HIP_OK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max - (int)fa.sharedSizeBytes));
     h->small_veh = nv;
     h->small_max_dep = d.max_dep;
@@ -559,16 +561,25 @@ sim_status create_impl(const sim_network* net, const sim_routes* r, const sim_id
             h->n_classes = p->n_classes;
             Dev& d = h->d;
             // ---- network
+            // Lanes are numbered edge after edge, with gaps so that no edge lies
+            // across a multiple of kLaneBlock (a workgroup of k_commit has whole
+            // edges); the gaps never hold a vehicle.
             h->lanes.assign(E, 0);
             h->lane_base.assign(E + 1, 0);
+            long long real = 0, next = 0;
             for (int e = 0; e < E; ++e) {
-                h->lanes[e] = net->n_lanes[e];
-                h->lane_base[e + 1] = h->lane_base[e] + net->n_lanes[e];
+                const int n = net->n_lanes[e];
+                h->lanes[e] = n;
+                real += n;
+                if (real > kLanesMax) throw Fail{SIM_EUNSUPPORTED, fmt("%lld lanes or more: at most %d", real, kLanesMax)};
+                if (next / kLaneBlock != (next + n - 1) / kLaneBlock) next = (next + kLaneBlock - 1) / kLaneBlock * kLaneBlock;
+                h->lane_base[e] = (int)next;
+                next += n;
             }
-            const int NL = h->lane_base[E];
-            if (NL >= (1 << kLaneBaseBits))   // a lane index and a lane count share one word in the tiles
-                throw Fail{SIM_EUNSUPPORTED, fmt("%d lanes: at most %d", NL, (1 << kLaneBaseBits) - 1)};
+            h->lane_base[E] = (int)next;
+            const int NL = (int)((next + kLaneBlock - 1) / kLaneBlock * kLaneBlock);
             h->n_lanes = NL;
+            h->lanes_real = (int)real;
             const int NC = net->conn_off[E];
             h->conn_off.assign(net->conn_off, net->conn_off + E + 1);
             h->conn_to.assign(net->conn_to, net->conn_to + NC);
@@ -608,6 +619,11 @@ sim_status create_impl(const sim_network* net, const sim_routes* r, const sim_id
                 for (int e = 0; e < E; ++e)
                     ec[e] = EdgeC{net->length_m[e], net->speed_limit_mps[e], h->lane_base[e], h->lanes[e]};
                 d.ec = h->upload(ec.data(), ec.size());
+                std::vector<uint32_t> le(NL, ~0u);
+                for (int e = 0; e < E; ++e)
+                    for (int l = 0; l < h->lanes[e]; ++l)
+                        le[h->lane_base[e] + l] = (uint32_t)e | ((uint32_t)l << kLaneEdgeBits);
+                d.lane_edge = h->upload(le.data(), le.size());
             }
             // ---- classes (den = 2 sqrt(ab), rounded once in binary32)
             std::vector<ClassParams> cp(16);
@@ -692,12 +708,11 @@ sim_status create_impl(const sim_network* net, const sim_routes* r, const sim_id
                 qs0[q] = p->s0[h->cls[v0]];
             }
             d.roff = h->upload(h->roff.data(), N + 1);
-            d.redges = h->upload(h->redges.data(), (size_t)NR);
-            std::vector<uint8_t> rmask(std::max<int64_t>(NR, 1), 0xFFu);
+            std::vector<uint32_t> rnext(std::max<int64_t>(NR, 1), ~0u);
             for (int i = 0; i < N; ++i)
                 for (int64_t k = h->roff[i]; k + 1 < h->roff[i + 1]; ++k)
-                    rmask[k] = (uint8_t)h->mask_of(h->redges[k], h->redges[k + 1]);
-            d.rmask = h->upload(rmask.data(), rmask.size());
+                    rnext[k] = route_word(h->redges[k + 1], h->mask_of(h->redges[k], h->redges[k + 1]));
+            d.rnext = h->upload(rnext.data(), rnext.size());
             d.cls = h->upload(h->cls.data(), N);
             d.alpha = h->upload(r->alpha_s, N);
             d.due = h->upload(due.data(), due.size());
@@ -758,7 +773,7 @@ sim_status create_impl(const sim_network* net, const sim_routes* r, const sim_id
                 h->g_big_min = (int)std::max(1LL, std::min<long long>(h->g_big_max, (items + kBigNT - 1) / kBigNT));
                 h->g_big = h->g_big_min;
             }
-            h->n_blk = (E + kEdgeBlock - 1) / kEdgeBlock;
+            h->n_blk = NL / kLaneBlock;
             d.n_blk = h->n_blk;
             h->scatter_lds = h->n_blk <= kScanLdsMax ? sizeof(int) * (size_t)h->n_blk : 0;
             h->g_scatter_max = std::max(1, std::min(4096, (N + kNT - 1) / kNT));
@@ -1560,7 +1575,8 @@ sim_status sim_autotune_steps(sim_handle* h, const char* cache_path, int32_t ste
     if (!h || steps < 1) return SIM_EINVAL;
     return guarded(h, [&] {
         char key[160];
-        snprintf(key, sizeof(key), "manta-schedule E=%d L=%d N=%d S=%d", h->n_edges, h->n_lanes, h->n_veh, h->n_scen);
+        snprintf(key, sizeof(key), "manta-schedule E=%d L=%d N=%d S=%d", h->n_edges, h->lanes_real, h->n_veh,
+                 h->n_scen);
         if (cache_path) {
             if (FILE* f = fopen(cache_path, "r")) {
                 char line[256];

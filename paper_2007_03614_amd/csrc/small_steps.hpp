@@ -45,9 +45,9 @@ struct Small {
     int cap, lanes, nodes;               // tile capacity (a multiple of 4), and the tables' entries in LDS
 };
 
-// LDS of the tables behind the tile: 60 bytes a lane, 8 a node
+// LDS of the tables behind the tile: 64 bytes a lane, 8 a node
 __host__ __device__ inline size_t small_table_bytes(int lanes, int nodes) {
-    return (size_t)lanes * (sizeof(LaneRear) + sizeof(LanePost) + 8 + 5 * 4) + (size_t)nodes * 8;
+    return (size_t)lanes * (sizeof(LaneRear) + sizeof(LanePost) + 8 + 6 * 4) + (size_t)nodes * 8;
 }
 
 __device__ inline Slots slots_at(const Slots& s, int o) {
@@ -85,12 +85,12 @@ __global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps)
     __shared__ float slen[16];
     __shared__ uint32_t dtask[2 * NT];
     __shared__ int dcount[2];
-    __shared__ int smoved, sdep, stot;
+    __shared__ int smoved, sdep, stot, sreq, shead;
     const int tid = threadIdx.x, k = blockIdx.x;
     const DrawQ dq{dtask, dcount, 2 * NT};
     const SmallRange r0 = sm.range[k], r1 = sm.range[k + 1];
     const int nl = r1.lane - r0.lane;
-    // the tile, where the exits of a step are kept once its tiles are done; then the lanes' tables
+    // the tile, where the exits of a step and its claiming queues are kept once its tiles are done; then the lanes' tables
     LaneTabs tb;
     char* p = lds + (size_t)sm.cap * kTileBytesPerVeh + 64;
     tb.rear = (LaneRear*)p;
@@ -106,15 +106,16 @@ __global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps)
     tb.enter_stamp = tb.exit_stamp + sm.lanes;
     tb.lane_off = tb.enter_stamp + sm.lanes;
     tb.lane_newcnt = tb.lane_off + sm.lanes;
+    tb.req_list = tb.lane_newcnt + sm.lanes;
+    tb.n_req = &sreq;
     tb.lane0 = r0.lane;
     tb.node0 = r0.node;
-    double* const xtt = (double*)lds;
-    uint32_t* const xid = (uint32_t*)(xtt + sm.lanes);
-    uint16_t* const xnc = (uint16_t*)(xid + sm.lanes);
+    const Exits ex{(uint32_t*)(lds + 8 * (size_t)sm.lanes), (double*)lds, (uint32_t*)(lds + 12 * (size_t)sm.lanes)};
+    int* const heads = (int*)(lds + 16 * (size_t)sm.lanes);
 
     if (tid < cNumCounters) shc[tid] = 0;
     if (tid < 2) dcount[tid] = 0;
-    if (tid == 0) smoved = sdep = 0;
+    if (tid == 0) smoved = sdep = sreq = shead = 0;
     if (tid < 16) {
         scp[tid] = d.cp[tid];
         slen[tid] = d.cp[tid].len;
@@ -153,26 +154,64 @@ __global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps)
         const Slots B = alone ? d.s[(t + 1) & 1] : slots_at((nsteps - 1 - j) & 1 ? d.s[par0 ^ 1] : sm.extra, r0.veh);
         if (d.trace && tid == 0) d.nact_hist[t % d.trace_period] = n;
         tile_pieces<NT, kSpread, false>(d, tb, S, lds, sm.cap, 0, n, t, acc, wsh4, wsh, scp, dq, &smoved);
-        admit_items<NT, false>(d, tb, S, t, 0, 1, r0.lane, r1.lane, r0.queue, r1.queue);
+        for (int i = tid; i < nl; i += NT) {       // (the tile's space is free after its last barrier)
+            ex.vid[i] = ~0u;
+            ex.n[i] = 0u;
+        }
+        // admission: the listed requests, and the due queue heads, which are listed where they claim a lane
+        const int nr = sreq;
+        for (int i = tid; i < nr; i += NT) admit_request<false>(d, tb, S, tb.req_list[i], t);
+        for (int q = r0.queue + tid; q < r1.queue; q += NT) {
+            const int2 hd = d.qhd[q];
+            if (hd.x <= t && admit_head<false>(d, tb, q, hd, t)) heads[atomicAdd(&shead, 1)] = q;
+        }
         __syncthreads();
+        // commit: the requests, and from the next wavefront on the heads whose key won their lane (in case 1 this
+        // node's crossing into it comes first)
+        const int h0 = (nr + 63) & ~63, nh = shead;
+        for (int i = tid; i < h0 + nh; i += NT) {
+            if (i < nr) {
+                const int gl = tb.req_list[i];
+                const uint32_t le = d.lane_edge[gl];
+                const bool out = commit_request(d, tb, S, gl, (int)(le & kLaneEdgeMask), (int)(le >> kLaneEdgeBits),
+                                                gl - r0.lane, t, acc, ex, &smoved);
+                if (d.imode == 1 && out) {
+                    const int target = d.outbox[gl].target;
+                    if (target >= 0) tb.enter_stamp[target - r0.lane] = t;
+                }
+            } else if (i >= h0) {
+                const int q = heads[i - h0], gl = d.qlane[q];
+                const unsigned long long w = tb.win[gl - r0.lane];
+                if ((w >> 63) && (int)(uint32_t)w == d.qhd[q].y) {
+                    const uint32_t le = d.lane_edge[gl];
+                    const int e = (int)(le & kLaneEdgeMask);
+                    if (!crossing_into(d, tb, e, gl)) {
+                        commit_departure(d, tb, gl, e, (int)(le >> kLaneEdgeBits), t, acc, &smoved);
+                        atomicAdd(&sdep, 1);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        for (int i = tid; i < nr; i += NT) {
+            const int gl = tb.req_list[i], li = gl - r0.lane;
+            if (ex.vid[li] != ~0u) {
+                const uint32_t le = d.lane_edge[gl];
+                commit_travel_time(d, (int)(le & kLaneEdgeMask), (int)(le >> kLaneEdgeBits), li, ex);
+            }
+        }
+        // the lanes of the next layout
         int nnew = 0;
-        for (int e0 = r0.edge; e0 < r1.edge; e0 += NT) {
-            const int e = e0 + tid;
-            EdgeC ce{0.0f, 0.0f, r0.lane, 0};
+        for (int i0 = 0; i0 < nl; i0 += NT) {
+            const int i = i0 + tid;
             int c = 0;
-            if (e < r1.edge) {
-                ce = d.ec[e];
-                const int l = ce.lane_base - r0.lane;
-                const unsigned was = acc.c[cDeparted];
-                c = commit_edge(d, tb, S, e, ce, t, acc, xid + l, xtt + l, xnc + l, &smoved);
-                if (acc.c[cDeparted] != was) atomicAdd(&sdep, (int)(acc.c[cDeparted] - was));
+            if (i < nl) {
+                const LanePost p = tb.post[i];
+                c = (p.stamp == t ? p.cnt : 0) - (tb.exit_stamp[i] == t ? 1 : 0) + (tb.enter_stamp[i] == t ? 1 : 0);
+                tb.lane_newcnt[i] = c;
             }
             const Scan4 sc = wg_exclusive_scan4<NT>(Scan4{c, -1, -1, -1}, wsh4);
-            int o = nnew + sc.s;
-            for (int l = ce.lane_base - r0.lane, q = 0; q < ce.lanes; ++q) {
-                tb.lane_off[l + q] = o;
-                o += xnc[l + q];
-            }
+            if (i < nl) tb.lane_off[i] = nnew + sc.s;
             if (tid == NT - 1) stot = nnew + sc.s + c;
             __syncthreads();
             nnew = stot;
@@ -184,7 +223,7 @@ __global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps)
         if (tid == 0) {
             act_sum += (unsigned long long)n;
             dep += sdep;
-            sdep = 0;
+            sdep = sreq = shead = 0;
             const int due = d.max_dep < 0 ? 0 : sm.due[(size_t)k * sm.due_stride + min(t, d.max_dep)];
             if (due > dep) denied += (unsigned long long)(due - dep);
             const bool mv = smoved != 0;

@@ -8,15 +8,15 @@
 // stamped with the step they are valid for), the rear after the move
 // (admission), and the post-lane-change run of each lane (scatter).
 //
-// One step = 4 launches (5 on networks above 262,144 edges), all reading the
+// One step = 4 launches (5 on networks above 2.1M lanes), all reading the
 // step number from device memory, so a captured graph of one step can be
 // replayed for every step:
 //   k_tile_step   Phases 1-2 per tile of whole edges, staged in LDS
 //   k_big_admit   the same for tiles above 384 vehicles (1,024 threads), then
 //                 eligibility + atomicMin of a 64-bit priority key per lane
-//   k_commit      one thread per edge, over its lanes: winners, losers,
-//                 arrivals, departures, travel-time sums, new lane counts and
-//                 edge offsets within the workgroup
+//   k_commit      one thread per lane: winners, losers, arrivals, departures,
+//                 travel-time sums, new lane counts and lane offsets within the
+//                 workgroup
 //   (k_blkscan    offsets of the commit workgroups, on large networks)
 //   k_scatter     offsets of the commit workgroups (in LDS), the next layout
 //                 and the next look-ahead table; the step counter advances
@@ -42,13 +42,14 @@ constexpr int kTileCtrStride = 32;       // ints between two counters: one 128-b
 constexpr int kTileCtrInts = 2 * kTileGroups * kTileCtrStride;   // [step parity][group] counters
 constexpr int kTileWindowAuto = 192;     // largest window the per-step choice takes
 constexpr int kTileDrawTasks = 384;      // listed Philox blocks per tile round (more are computed in place)
-constexpr int kCommitLanes = 8;         // lanes of an edge at most
-constexpr int kCommitNT = 256;           // threads per commit workgroup
-constexpr int kEdgeBlock = kCommitNT;    // edges per commit workgroup (one thread per edge)
+constexpr int kLaneBlock = 256;          // lanes per commit workgroup (one thread per lane)
+constexpr int kLaneEdgeBits = 24;        // lane_edge: the lane's edge | its index on the edge << 24; ~0 past an edge's lanes
+constexpr uint32_t kLaneEdgeMask = (1u << kLaneEdgeBits) - 1u;
+constexpr int kLanesMax = (1 << 24) - 1; // lanes of a network at most (so edges, too, fit 24 bits)
 constexpr int kBigNT = 1024;             // threads per workgroup for tiles above kTileCapLds
 constexpr int kBigCapLds = 1408;         // vehicles per big tile piece staged in LDS (110 KiB)
 constexpr unsigned long long kBarrierTimeout = 20000000ull;   // 0.2 s of the 100 MHz clock
-constexpr int kScanLdsMax = 8192;        // edge blocks whose offsets k_scatter scans in LDS (32 KiB)
+constexpr int kScanLdsMax = 8192;        // commit blocks whose offsets k_scatter scans in LDS (32 KiB)
 constexpr int kCounterCopies = 1024;     // each counter is spread over 1,024 slots (few colliding atomics)
 
 // ---- vehicle meta word ---------------------------------------------------
@@ -192,11 +193,11 @@ struct Dev {
     const int* lanes;
     const int* lane_base;
     const EdgeC* ec;            // the four above, packed per edge
+    const uint32_t* lane_edge;  // [lane] its edge | its index on the edge << 24
     // vehicles (static)
     int n_veh;
     const int64_t* roff;
-    const int* redges;
-    const uint8_t* rmask;       // per route entry: lane mask of the move to the next route edge (0xFF last)
+    const uint32_t* rnext;      // per route entry: the next route edge and the lane mask of the move there (route_word)
     const uint8_t* cls;
     const float* alpha;
     const int* due;             // due[t] = vehicles with departure step <= t, t <= max_dep
@@ -249,7 +250,7 @@ struct Dev {
     int* enter_stamp;
     int* lane_off;              // next layout: lane start relative to its commit block
     int* lane_newcnt;
-    // per edge
+    // per commit block, and per edge
     int* blk_sum;
     int* blk_off;
     int n_blk;
@@ -291,10 +292,12 @@ struct LaneTabs {
     int* lane_newcnt;
     unsigned long long* win_node;
     int lane0, node0;
+    int* req_list;              // lanes with a request this step, in any order (null: not listed)
+    int* n_req;
 };
 __device__ inline LaneTabs lane_tabs(const Dev& d) {
     return LaneTabs{d.rear, d.post, d.req_stamp, d.win, d.exit_stamp, d.enter_stamp, d.lane_off, d.lane_newcnt,
-                    d.win_node, 0, 0};
+                    d.win_node, 0, 0, nullptr, nullptr};
 }
 
 // k_tile_step's tile counters: after the movement stamps, 128-byte aligned
@@ -324,12 +327,13 @@ struct TileBuf {
     // that later phases find them in LDS
     float* L;           // edge length
     float* lim;         // edge speed limit; after Phase 2 the vehicle's new speed
-    uint32_t* lbe;      // first global lane of the edge | its lanes << 24
+    uint32_t* lbe;      // first global lane of the edge | its lanes << 28
     uint32_t* lbf;      // the same for the next edge (0 if none)
 };
 
-// lane words: first global lane (below 2^24) and lane count in one word
-constexpr int kLaneBaseBits = 24;
+// lane words: first global lane and lane count (at most 8) in one word.  The
+// lanes are numbered with gaps (kLaneBlock), so a base may pass 2^24.
+constexpr int kLaneBaseBits = 28;
 __device__ inline int lw_base(uint32_t w) { return (int)(w & ((1u << kLaneBaseBits) - 1u)); }
 __device__ inline int lw_lanes(uint32_t w) { return (int)(w >> kLaneBaseBits); }
 __device__ inline int lastm_of(const int* lml, int i) { return (int)(short)(lml[i] & 0xFFFF); }
@@ -1127,6 +1131,7 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
                     }
                     d.outbox[gl] = ob;
                     tb.req_stamp[gl - tb.lane0] = t;
+                    if (tb.req_list) tb.req_list[atomicAdd(tb.n_req, 1)] = gl;
                 }
             }
         }
@@ -1448,19 +1453,22 @@ __device__ inline void admit_request(const Dev& d, const LaneTabs& tb, const Slo
 
 // Admission of a due departure-queue head (departure step hd.x, id hd.y):
 // it claims the queue's lane if the lane's rear leaves it s0 at x = 0.
+// Returns whether it did.
 template <bool kDefer>
-__device__ inline void admit_head(const Dev& d, const LaneTabs& tb, int q, int2 hd, int t) {
+__device__ inline bool admit_head(const Dev& d, const LaneTabs& tb, int q, int2 hd, int t) {
     const int gl = d.qlane[q];
     if (kDefer) {
         const int2 bl = d.big_lane[gl];
         if (bl.x == t) {
             defer_item(d, bl.y, d.n_lanes_total + q);
-            return;
+            return false;
         }
     }
     const LanePost p = tb.post[gl - tb.lane0];
-    if (p.stamp != t || p.rear_xm >= d.qs0[q])
+    const bool room = p.stamp != t || p.rear_xm >= d.qs0[q];
+    if (room)
         claim(tb, gl, (1ull << 63) | ((unsigned long long)(uint32_t)hd.x << 32) | (uint32_t)hd.y, t);
+    return room;
 }
 
 // One item per lane of [l0, l1) (its front may have asked to leave the edge
@@ -1572,191 +1580,193 @@ __global__ void __launch_bounds__(kBigNT) k_big_admit(Dev d) {
     }
 }
 
-// One thread per edge, over its lanes (most edges have one or two).  For a
-// lane the thread
-//   * settles its front's end-of-edge request: arrival, admitted transfer
-//     (an entry record on the next edge), or held at the stop line;
-//   * inserts the departure whose key won the lane;
-//   * counts its vehicles for the next layout.
-// The edge's travel-time sum adds the exits in ascending vehicle id (at most
-// one per lane; kept in LDS and sorted there when an edge has several).
-// Lanes without a request cost three 4-byte stamps and their post-move count.
-// Returns the edge's vehicles in the next layout, its lane counts in mync.
-// myid, mytt: room for one exit per lane.
-__device__ inline int commit_edge(const Dev& d, const LaneTabs& tb, const Slots& S, int e, const EdgeC& ce, int t,
-                                  CounterAcc& acc, uint32_t* myid, double* mytt, uint16_t* mync, int* smoved) {
-    int c = 0, nex = 0;
-    const int nl = ce.lanes, base = ce.lane_base;
-    {
-        int node_win = -1;                         // case 1: lane index of this node's winning crossing
-        if (d.imode == 1) {
-            const unsigned long long wn = tb.win_node[d.efrom[e] - tb.node0];
-            if (wn != ~0ull) node_win = d.outbox[(int)(wn & ((1ull << 26) - 1))].target;
-        }
-        // each lane's three stamps are loaded one lane ahead
-        const int b0 = base - tb.lane0;
-        LanePost pn = tb.post[b0];
-        int rn = tb.req_stamp[b0], en = tb.enter_stamp[b0];
-        for (int l = 0; l < nl; ++l) {
-            const int gl = base + l;
-            const LanePost p = pn;
-            const bool req = rn == t;
-            bool claimed = en == t;
-            if (l + 1 < nl) {
-                pn = tb.post[b0 + l + 1];
-                rn = tb.req_stamp[b0 + l + 1];
-                en = tb.enter_stamp[b0 + l + 1];
-            }
-            const int pcnt = p.stamp == t ? p.cnt : 0;
-            bool exits = false;
-            if (req) {
-                const Outbox ob = d.outbox[gl];
-                // every load of this request first, then the decisions and stores
-                const uint32_t m = S.meta[ob.slot];
-                const float xs = S.x[ob.slot], vs = S.v[ob.slot];
-                const int hs = d.held_since[ob.vid];
-                const double tin = d.tau_in[ob.vid];
-                int kk = 0;
-                int64_t r0 = 0;
-                if (ob.target >= 0) {              // the route, for an entry record
-                    kk = d.cursor[ob.vid] + 1;
-                    r0 = d.roff[ob.vid];
-                }
-                bool won;
-                if (d.imode == 1) {
-                    won = ob.target >= 0 && ob.elig && tb.win_node[ob.elig - 1 - tb.node0] == ob.key;
-                    if (won) d.rr[ob.elig - 1] = (int)((ob.tl_cls >> 16) & 255u);   // the pair just served
-                } else {
-                    won = ob.target >= 0 && ob.elig && tb.win[ob.target - tb.lane0] == ob.key;
-                }
-                const bool arrived = ob.target < 0;
-                if (d.trace)
-                    d.trace[(size_t)(t % d.trace_period) * d.trace_stride + ob.slot].kb |=
-                        (arrived ? TB_ARRIVE : (won ? TB_EXIT : TB_HELD)) << 8;
-                exits = arrived || won;
-                if (arrived) {                     // arrival at the route end
-                    d.status[ob.vid] = kArrived;
-                    d.fin_x[ob.vid] = xs;
-                    d.fin_v[ob.vid] = vs;
-                    d.fin_meta[ob.vid] = m;
-                } else if (!won) {                 // held at the stop line
-                    S.x[ob.slot] = ce.L;
-                    S.v[ob.slot] = 0.0f;
-                    S.meta[ob.slot] = m | (1u << 5);
-                    if (hs < 0) d.held_since[ob.vid] = t;
-                }
-                // counted outside the branches: an increment of a different
-                // counter in each branch would be merged into one store through
-                // a computed index, which moves the counters to scratch memory
-                acc.c[cArrived] += arrived ? 1u : 0u;
-                acc.c[cTransfers] += won ? 1u : 0u;
-                acc.c[cWaivedExits] += (won && !lane_allowed(m, ob.nxt, l)) ? 1u : 0u;
-                acc.c[cHolds] += exits ? 0u : 1u;
-                if (exits) *smoved = 1;                 // gridlock detector
-                if (exits) {
-                    tb.exit_stamp[b0 + l] = t;
-                    const double tau = ((double)t + (double)ob.phi) * (double)d.dt;
-                    myid[nex] = ob.vid;
-                    mytt[nex] = tau - tin;
-                    ++nex;
-                    if (arrived) d.t_arr[ob.vid] = tau;
-                    else d.tau_in[ob.vid] = tau;
-                }
-                if (won) {                         // entry record, stored at the target lane
-                    const int64_t pos = r0 + kk + 1;   // route index of the edge after ob.nxt
-                    EntryRec r;
-                    r.x = ob.xp;
-                    r.v = ob.v;
-                    r.vid = ob.vid;
-                    r.edge = ob.nxt;
-                    r.gl = ob.target;
-                    r.meta = m_make((int)(ob.tl_cls & 255u), false, false, 0, (int)((ob.tl_cls >> 8) & 255u),
-                                    d.rmask[r0 + kk]);
-                    r.nxt = pos < d.roff[ob.vid + 1] ? d.redges[pos] : -1;
-                    r.pad = 0;
-                    d.cursor[ob.vid] = kk;
-                    d.held_since[ob.vid] = -1;
-                    d.ent[ob.target] = r;
-                }
-            }
-            // the departure whose key won this lane; in case 1 only departures
-            // claim lanes, and this node's crossing into the lane comes first
-            const bool transfer_in = node_win == gl;
-            if (claimed && !transfer_in) {
-                const unsigned long long w = tb.win[b0 + l];
-                if (w >> 63) {
-                    const int vid = (int)(uint32_t)w;
-                    const int4 vq = d.vq[vid];     // vid is the head of queue vq.x
-                    const int64_t q0 = d.roff[vid];
-                    d.qhead[vq.x] = vq.y + 1;
-                    d.qhd[vq.x] = vq.z >= 0 ? make_int2(vq.w, vq.z) : make_int2(INT_MAX, -1);
-                    EntryRec r;
-                    r.x = 0.0f;
-                    r.v = 0.0f;
-                    r.vid = (uint32_t)vid;
-                    r.edge = e;                    // the queue's lane is on the first route edge
-                    r.gl = gl;
-                    r.meta = m_make(l, false, false, 0, d.cls[vid], d.rmask[q0]);
-                    r.nxt = (q0 + 1 < d.roff[vid + 1]) ? d.redges[q0 + 1] : -1;
-                    r.pad = 0;
-                    d.status[vid] = kActive;
-                    d.cursor[vid] = 0;
-                    d.held_since[vid] = -1;
-                    d.tau_in[vid] = (double)(t + 1) * (double)d.dt;
-                    d.ent[gl] = r;
-                    acc.c[cDeparted]++;
-                    *smoved = 1;
-                }
-            }
-            if (transfer_in && !claimed) tb.enter_stamp[b0 + l] = t;   // the scatter takes the crossing's record
-            claimed = claimed || transfer_in;
-            // next layout: this lane's count (its offset follows the block scan)
-            const int nc = pcnt - (exits ? 1 : 0) + (claimed ? 1 : 0);
-            mync[l] = (uint16_t)nc;
-            tb.lane_newcnt[b0 + l] = nc;
-            c += nc;
-        }
-        if (nex > 0) {
-            // travel times of the edge's exits, added in ascending vehicle id
-            for (int i = 1; i < nex; ++i)
-                for (int j = i; j > 0 && myid[j - 1] > myid[j]; --j) {
-                    const uint32_t ti = myid[j];
-                    myid[j] = myid[j - 1];
-                    myid[j - 1] = ti;
-                    const double tt = mytt[j];
-                    mytt[j] = mytt[j - 1];
-                    mytt[j - 1] = tt;
-                }
-            double sum = d.tt_sum[e];
-            for (int i = 0; i < nex; ++i) sum += mytt[i];
-            d.tt_sum[e] = sum;
-            d.tt_cnt[e] += (unsigned long long)nex;
-        }
+// ---- commit ------------------------------------------------------------------
+// One thread per lane.  Its chain is the lane's stamps, the request, the
+// vehicle's arrays with the target lane's winning key, and the route word of an
+// entry: four dependent rounds of loads, each issued together, and that chain is
+// what bounds it.  (One thread per edge, taking its lanes one after another, went
+// through it once per lane that any thread of the wavefront had a request on:
+// 10.9 us a step on the 100x100 city and 28.2 on the metropolitan lattice,
+// against 5.7 and 19.4.)
+
+// A route entry's word: the next route edge | lane mask of the move there <<
+// 24; all ones on a route's last edge (no next edge, every lane).
+constexpr uint32_t kRouteEnd = 0xFFFFFFu;
+__host__ __device__ inline uint32_t route_word(int next, uint32_t mask) {
+    return next < 0 ? ~0u : (uint32_t)next | (mask << 24);
+}
+__device__ inline int word_next(uint32_t w) { return (w & kRouteEnd) == kRouteEnd ? -1 : (int)(w & kRouteEnd); }
+
+// The exits of a workgroup's lanes, for the travel times of their edges.
+struct Exits {
+    uint32_t* vid;     // [lane] the vehicle that left, ~0 if none
+    double* tt;        // [lane] its traversal time
+    uint32_t* n;       // [lane 0 of an edge] exits from the edge
+};
+
+// Settles the end-of-edge request of lane gl's front (on edge e, lane l of
+// it): arrival, admitted transfer (an entry record on the next edge), or held
+// at the stop line.  Returns whether the front leaves the edge.  li: the lane
+// in ex.
+__device__ inline bool commit_request(const Dev& d, const LaneTabs& tb, const Slots& S, int gl, int e, int l, int li,
+                                      int t, CounterAcc& acc, const Exits& ex, int* smoved) {
+    const Outbox ob = d.outbox[gl];
+    const float L = d.L[e];
+    // every load of this request first, then the decisions and stores
+    const uint32_t m = S.meta[ob.slot];
+    const float xs = S.x[ob.slot], vs = S.v[ob.slot];
+    const int hs = d.held_since[ob.vid];
+    const double tin = d.tau_in[ob.vid];
+    const int kk = d.cursor[ob.vid] + 1;
+    const int64_t r0 = d.roff[ob.vid];
+    const bool arrived = ob.target < 0;
+    bool won;
+    if (d.imode == 1) {
+        won = !arrived && ob.elig && tb.win_node[ob.elig - 1 - tb.node0] == ob.key;
+        if (won) d.rr[ob.elig - 1] = (int)((ob.tl_cls >> 16) & 255u);   // the pair just served
+    } else {
+        won = !arrived && ob.elig && tb.win[ob.target - tb.lane0] == ob.key;
     }
-    return c;
+    if (d.trace)
+        d.trace[(size_t)(t % d.trace_period) * d.trace_stride + ob.slot].kb |=
+            (arrived ? TB_ARRIVE : (won ? TB_EXIT : TB_HELD)) << 8;
+    const bool exits = arrived || won;
+    if (won) {                             // entry record, stored at the target lane
+        const uint32_t w = d.rnext[r0 + kk];
+        EntryRec r;
+        r.x = ob.xp;
+        r.v = ob.v;
+        r.vid = ob.vid;
+        r.edge = ob.nxt;
+        r.gl = ob.target;
+        r.meta = m_make((int)(ob.tl_cls & 255u), false, false, 0, (int)((ob.tl_cls >> 8) & 255u), w >> 24);
+        r.nxt = word_next(w);
+        r.pad = 0;
+        d.cursor[ob.vid] = kk;
+        d.held_since[ob.vid] = -1;
+        d.ent[ob.target] = r;
+    }
+    if (arrived) {                         // arrival at the route end
+        d.status[ob.vid] = kArrived;
+        d.fin_x[ob.vid] = xs;
+        d.fin_v[ob.vid] = vs;
+        d.fin_meta[ob.vid] = m;
+    } else if (!won) {                     // held at the stop line
+        S.x[ob.slot] = L;
+        S.v[ob.slot] = 0.0f;
+        S.meta[ob.slot] = m | (1u << 5);
+        if (hs < 0) d.held_since[ob.vid] = t;
+    }
+    // counted outside the branches: an increment of a different counter in each
+    // branch would be merged into one store through a computed index, which
+    // moves the counters to scratch memory
+    acc.c[cArrived] += arrived ? 1u : 0u;
+    acc.c[cTransfers] += won ? 1u : 0u;
+    acc.c[cWaivedExits] += (won && !lane_allowed(m, ob.nxt, l)) ? 1u : 0u;
+    acc.c[cHolds] += exits ? 0u : 1u;
+    if (exits) {
+        *smoved = 1;                       // gridlock detector
+        tb.exit_stamp[gl - tb.lane0] = t;
+        const double tau = ((double)t + (double)ob.phi) * (double)d.dt;
+        ex.vid[li] = ob.vid;
+        ex.tt[li] = tau - tin;
+        atomicAdd(&ex.n[li - l], 1u);
+        if (arrived) d.t_arr[ob.vid] = tau;
+        else d.tau_in[ob.vid] = tau;
+    }
+    return exits;
 }
 
-// The edges of one block: one thread per edge, then the offsets of the edges
-// in the workgroup and of their lanes.
-__device__ inline void commit_block(const Dev& d, int blk, int t, int par, CounterAcc& acc, Scan4* wsh4,
-                                    uint32_t* xid, double* xtt, uint16_t* xnc, int* smoved) {
-    const int e = blk * kEdgeBlock + (int)threadIdx.x;
-    const LaneTabs tb = lane_tabs(d);
-    uint16_t* const mync = xnc + threadIdx.x * kCommitLanes;
-    EdgeC ce{0.0f, 0.0f, 0, 0};
-    int c = 0;
-    if (e < d.n_edges) {
-        ce = d.ec[e];
-        c = commit_edge(d, tb, d.s[par], e, ce, t, acc, xid + threadIdx.x * kCommitLanes,
-                        xtt + threadIdx.x * kCommitLanes, mync, smoved);
+// The departure whose key won lane gl (edge e, lane l of it), if it was one.
+__device__ inline void commit_departure(const Dev& d, const LaneTabs& tb, int gl, int e, int l, int t, CounterAcc& acc,
+                                        int* smoved) {
+    const unsigned long long w = tb.win[gl - tb.lane0];
+    if (!(w >> 63)) return;
+    const int vid = (int)(uint32_t)w;
+    const int4 vq = d.vq[vid];             // vid is the head of queue vq.x
+    const int64_t q0 = d.roff[vid];
+    const int c = d.cls[vid];
+    const uint32_t rw = d.rnext[q0];
+    d.qhead[vq.x] = vq.y + 1;
+    d.qhd[vq.x] = vq.z >= 0 ? make_int2(vq.w, vq.z) : make_int2(INT_MAX, -1);
+    EntryRec r;
+    r.x = 0.0f;
+    r.v = 0.0f;
+    r.vid = (uint32_t)vid;
+    r.edge = e;                            // the queue's lane is on the first route edge
+    r.gl = gl;
+    r.meta = m_make(l, false, false, 0, c, rw >> 24);
+    r.nxt = word_next(rw);
+    r.pad = 0;
+    d.status[vid] = kActive;
+    d.cursor[vid] = 0;
+    d.held_since[vid] = -1;
+    d.tau_in[vid] = (double)(t + 1) * (double)d.dt;
+    d.ent[gl] = r;
+    acc.c[cDeparted]++;
+    *smoved = 1;
+}
+
+// Case 1: whether the crossing that the tail node of edge e admits enters its
+// lane gl.
+__device__ inline bool crossing_into(const Dev& d, const LaneTabs& tb, int e, int gl) {
+    if (d.imode != 1) return false;
+    const unsigned long long wn = tb.win_node[d.efrom[e] - tb.node0];
+    return wn != ~0ull && d.outbox[(int)(wn & ((1ull << 26) - 1))].target == gl;
+}
+
+// Lane gl in this step: its request, the vehicle that entered it, and its
+// count in the next layout, which is returned.
+__device__ inline int commit_lane(const Dev& d, const LaneTabs& tb, const Slots& S, int gl, int e, int l, int li, int t,
+                                  CounterAcc& acc, const Exits& ex, int* smoved) {
+    const int g0 = gl - tb.lane0;
+    const LanePost p = tb.post[g0];
+    const bool req = tb.req_stamp[g0] == t;
+    bool claimed = tb.enter_stamp[g0] == t;
+    // the departure whose key won this lane; in case 1 only departures claim
+    // lanes, and this node's crossing into the lane comes first
+    const bool transfer_in = crossing_into(d, tb, e, gl);
+    bool exits = false;
+    if (req) exits = commit_request(d, tb, S, gl, e, l, li, t, acc, ex, smoved);
+    if (claimed && !transfer_in) commit_departure(d, tb, gl, e, l, t, acc, smoved);
+    if (transfer_in && !claimed) tb.enter_stamp[g0] = t;   // the scatter takes the crossing's record
+    claimed = claimed || transfer_in;
+    const int nc = (p.stamp == t ? p.cnt : 0) - (exits ? 1 : 0) + (claimed ? 1 : 0);
+    tb.lane_newcnt[g0] = nc;
+    return nc;
+}
+
+// The travel time of lane li's exit (on edge e, lane l of it), once every lane
+// of the edge is settled (a barrier before): an edge's only exit adds its own,
+// the lowest lane of several exits adds them in ascending vehicle id.
+__device__ inline void commit_travel_time(const Dev& d, int e, int l, int li, const Exits& ex) {
+    const int first = li - l;
+    const uint32_t n = ex.n[first];
+    if (n > 1u) {
+        for (int q = 0; q < l; ++q)
+            if (ex.vid[first + q] != ~0u) return;
+        const int lanes = d.lanes[e];
+        double sum = d.tt_sum[e];
+        uint32_t from = 0u;                // ids below it are added
+        for (uint32_t k = 0; k < n; ++k) {
+            int next = -1;
+            uint32_t id = ~0u;
+            for (int q = l; q < lanes; ++q) {
+                const uint32_t v = ex.vid[first + q];
+                if (v >= from && v < id) {
+                    id = v;
+                    next = q;
+                }
+            }
+            if (next < 0) break;
+            sum += ex.tt[first + next];
+            from = id + 1u;
+        }
+        d.tt_sum[e] = sum;
+    } else {
+        d.tt_sum[e] += ex.tt[li];
     }
-    const Scan4 run = wg_exclusive_scan4<kCommitNT>(Scan4{c, -1, -1, -1}, wsh4);
-    int o = run.s;
-    for (int l = 0; l < ce.lanes; ++l) {
-        d.lane_off[ce.lane_base + l] = o;
-        o += mync[l];
-    }
-    if (threadIdx.x == kCommitNT - 1) d.blk_sum[blk] = run.s + c;
+    d.tt_cnt[e] += (unsigned long long)n;
 }
 
 __device__ inline void flush_commit_counters(const Dev& d, const CounterAcc& acc, unsigned* shc) {
@@ -1764,25 +1774,39 @@ __device__ inline void flush_commit_counters(const Dev& d, const CounterAcc& acc
     if (threadIdx.x == 0 && shc[cDeparted]) atomicAdd(&d.ctl->n_departed, (int)shc[cDeparted]);
 }
 
-__global__ void __launch_bounds__(kCommitNT) k_commit(Dev d) {
+// A workgroup's lanes are those of whole edges (the lanes are numbered so that
+// no edge lies across a multiple of kLaneBlock); then the offsets of the lanes
+// in the workgroup.
+__global__ void __launch_bounds__(kLaneBlock) k_commit(Dev d) {
     __shared__ unsigned shc[cNumCounters];
-    __shared__ Scan4 wsh4[kCommitNT / 64];
-    __shared__ uint32_t xid[kCommitNT * kCommitLanes];     // exits of each thread's edge
-    __shared__ double xtt[kCommitNT * kCommitLanes];
-    __shared__ uint16_t xnc[kCommitNT * kCommitLanes];   // new counts of each thread's lanes
+    __shared__ Scan4 wsh4[kLaneBlock / 64];
+    __shared__ uint32_t xid[kLaneBlock], xn[kLaneBlock];
+    __shared__ double xtt[kLaneBlock];
     __shared__ int smoved;                                // gridlock detector: an exit or a departure here
-    if (threadIdx.x < cNumCounters) shc[threadIdx.x] = 0;
-    if (threadIdx.x == 0) smoved = 0;
-    __syncthreads();
+    const int tid = threadIdx.x, gl = blockIdx.x * kLaneBlock + tid;
+    const uint32_t le = d.lane_edge[gl];
+    if (tid < cNumCounters) shc[tid] = 0;
+    if (tid == 0) smoved = 0;
+    xid[tid] = ~0u;
+    xn[tid] = 0u;
     const int t = d.ctl->t_b, par = t & 1;
+    __syncthreads();
+    const LaneTabs tb = lane_tabs(d);
+    const Exits ex{xid, xtt, xn};
+    const int e = (int)(le & kLaneEdgeMask), l = (int)(le >> kLaneEdgeBits);
     CounterAcc acc;
     acc.zero();
-    commit_block(d, blockIdx.x, t, par, acc, wsh4, xid, xtt, xnc, &smoved);
+    int c = 0;
+    if (le != ~0u) c = commit_lane(d, tb, d.s[par], gl, e, l, tid, t, acc, ex, &smoved);
+    const Scan4 run = wg_exclusive_scan4<kLaneBlock>(Scan4{c, -1, -1, -1}, wsh4);   // a barrier in it
+    d.lane_off[gl] = run.s;
+    if (tid == kLaneBlock - 1) d.blk_sum[blockIdx.x] = run.s + c;
+    if (xid[tid] != ~0u) commit_travel_time(d, e, l, tid, ex);
     flush_commit_counters(d, acc, shc);
     publish_moved(d, &smoved, t);
 }
 
-// ---- offsets of the edge blocks and the end of the step --------------------
+// ---- offsets of the commit blocks and the end of the step --------------------
 // Exclusive scan of the commit workgroups' vehicle counts into off[0, nb);
 // returns the total (the active vehicles of the next step).  The sums were
 // written by k_commit, a previous kernel, so no fence is needed: no workgroup
@@ -1840,7 +1864,7 @@ __device__ inline void finish_step(const Dev& d, int t, int par, int total) {
     d.ctl->t_a = t + 1;   // the tile kernels and admission of this step are done
 }
 
-// Networks with more edge blocks than kScanLdsMax: one workgroup scans the
+// Networks with more commit blocks than kScanLdsMax: one workgroup scans the
 // block offsets into global memory before k_scatter.
 __global__ void __launch_bounds__(kBigNT) k_blkscan(Dev d) {
     __shared__ Scan4 wsh4[kBigNT / 64];
@@ -1880,7 +1904,7 @@ __device__ inline void put_record(const Dev& d, const LaneTabs& tb, const Slots&
 // record that entered it if it was claimed this step.  Each round of loads of
 // the two is issued together: the record with its lane and the lane's claim
 // stamp; then the tables of the record's lane and the entry of a claimed lane.
-// off(edge): where the offsets of that edge's lanes count from.
+// off(lane): where that lane's offset counts from.
 template <class Off>
 __device__ inline void scatter_item(const Dev& d, const LaneTabs& tb, const Slots& A, const Slots& B, int k, int i,
                                     int nnew, int t, const float* slen, Off off) {
@@ -1922,21 +1946,21 @@ __device__ inline void scatter_item(const Dev& d, const LaneTabs& tb, const Slot
             atomicOr(&d.ctl->err, kErrScatter);
         } else if (!(ex && r == 0)) {         // unless the lane's front left the edge
             const int nr = r - ex;
-            put_record(d, tb, B, off(edge) + loff + nr, nnew, x, v, vid, edge, meta, nxt, (nr == ncnt - 1) && !entered,
+            put_record(d, tb, B, off(gl) + loff + nr, nnew, x, v, vid, edge, meta, nxt, (nr == ncnt - 1) && !entered,
                        gl, t, slen);
         }
     }
     if (claimed) {                            // the entry is the lane's new rear
-        put_record(d, tb, B, off(en.edge) + enoff + encnt - 1, nnew, en.x, en.v, en.vid, en.edge, en.meta, en.nxt, true,
+        put_record(d, tb, B, off(i) + enoff + encnt - 1, nnew, en.x, en.v, en.vid, en.edge, en.meta, en.nxt, true,
                    i, t, slen);
         tb.win[i0] = ~0ull;                   // lane free for the next step's claims
     }
 }
 
 // slot of a vehicle in the next layout:
-//   block offset + edge offset in block + lane offset in edge + rank in lane
+//   block offset + lane offset in block + rank in lane
 // kLds: the workgroup scans the block offsets itself into LDS (at most
-// kScanLdsMax edge blocks), and workgroup 0 finishes the step; otherwise
+// kScanLdsMax commit blocks), and workgroup 0 finishes the step; otherwise
 // k_blkscan has done both.
 template <bool kLds>
 __device__ inline void scatter_items(const Dev& d, int* soff, Scan4* wsh4, int* totp, float* slen) {
@@ -1964,14 +1988,14 @@ __device__ inline void scatter_items(const Dev& d, int* soff, Scan4* wsh4, int* 
     const int nit = max(nold, nl);
     for (int k = blockIdx.x * kNT + threadIdx.x; k < nit; k += gridDim.x * kNT) {
         scatter_item(d, tb, A, B, k < nold ? k : -1, k < nl ? k : -1, nnew, t, slen,
-                     [&](int edge) { return boff[edge / kEdgeBlock]; });
+                     [&](int lane) { return boff[lane / kLaneBlock]; });
     }
 }
 
 template <bool kLds>
 __global__ void __launch_bounds__(kNT) k_scatter(Dev d) {
     // kLds: the block offsets, d.n_blk ints of dynamic LDS sized at launch
-    // (so a network with few edge blocks leaves room for more workgroups)
+    // (so a network with few commit blocks leaves room for more workgroups)
     extern __shared__ int soff[];
     __shared__ Scan4 wsh4[kWaves];
     __shared__ int tot;
