@@ -1274,7 +1274,10 @@ sim_status sim_backward(sim_handle* h, const double* dL_dmean_tt, double* dL_dpa
             if (!std::isfinite(dL_dmean_tt[e])) throw Fail{SIM_EINVAL, fmt("dL_dmean_tt[%d] is not finite", e)};
             if (cnt[e]) w[e] = dL_dmean_tt[e] / (double)cnt[e];
         }
-        const int gbw = std::max(1, std::min(256, (N + kNT - 1) / kNT));
+        // a small network: one launch per segment for the traced re-run and one for its reverse sweep
+        const bool small = h->small && h->sm.n_scen == 1 && h->small_veh <= kSmallActive;
+        // parameter sums: one set per workgroup, or per thread of the one workgroup
+        const int gbw = small ? kSmallBwNT : std::max(1, std::min(256, (N + kNT - 1) / kNT));
         double* dw = (double*)get(8 * (size_t)E);
         HIP_OK(hipMemcpy(dw, w.data(), 8 * (size_t)E, hipMemcpyHostToDevice));
         double* lam[5];
@@ -1297,20 +1300,23 @@ sim_status sim_backward(sim_handle* h, const double* dL_dmean_tt, double* dL_dpa
         traced.trace_stride = N;
         traced.nact_hist = nact;
         // per-record parts and the look-ahead lists of one reverse step
-        const size_t NLs = (size_t)std::max(h->n_lanes, 1);
+        const size_t NLs = small ? 1 : (size_t)std::max(h->n_lanes, 1);
+        const size_t NA = small ? 1 : (size_t)N;
         BwPart* part = (BwPart*)get(sizeof(BwPart) * (size_t)N);
         int* lk_cnt = (int*)get(4 * NLs);
         int* lk_rec = (int*)get(4 * NLs * kLookListCap);
-        double* lkx = (double*)get(8 * (size_t)N);
-        double* lkv = (double*)get(8 * (size_t)N);
-        int* lk_stamp = (int*)get(4 * (size_t)N);
+        double* lkx = (double*)get(8 * NA);
+        double* lkv = (double*)get(8 * NA);
+        int* lk_stamp = (int*)get(4 * NA);
         HIP_OK(hipMemsetAsync(lk_cnt, 0, 4 * NLs, h->stream));
-        HIP_OK(hipMemsetAsync(lk_stamp, 0xFF, 4 * (size_t)N, h->stream));
+        HIP_OK(hipMemsetAsync(lk_stamp, 0xFF, 4 * NA, h->stream));
+        const auto k_bw = NC <= 1 ? k_backward<1> : NC <= 4 ? k_backward<4> : k_backward<16>;
+        const auto k_bw_small = NC <= 1 ? k_small_backward<1> : NC <= 4 ? k_small_backward<4> : k_small_backward<16>;
         // one reverse step: (lx, lv) -> (nx, nv) for step index i of a segment
         auto reverse_step = [&](hipStream_t s, int i, double* ix, double* iv, double* ox, double* ov) {
             const TraceRec* tr = trace + (size_t)i * N;
-            hipLaunchKernelGGL(k_backward, dim3(gbw), dim3(kNT), 0, s, saved, tr, nact + i, i, NC, ix, iv, part,
-                               lk_cnt, lk_rec, lt, dw, gpart, ox, ov, N);
+            hipLaunchKernelGGL(k_bw, dim3(gbw), dim3(kNT), 0, s, saved, tr, nact + i, NC, ix, iv, part, lk_cnt, lk_rec,
+                               lt, dw, gpart, ox, ov, N);
             hipLaunchKernelGGL(k_bw_looks, dim3(gbw), dim3(kNT), 0, s, tr, nact + i, i, part, lk_cnt, lk_rec, lkx,
                                lkv, lk_stamp);
             hipLaunchKernelGGL(k_bw_gather, dim3(gbw), dim3(kNT), 0, s, tr, nact + i, i, part, lkx, lkv, lk_stamp,
@@ -1349,10 +1355,8 @@ sim_status sim_backward(sim_handle* h, const double* dL_dmean_tt, double* dL_dpa
             HIP_OK(e);
             HIP_OK(hipGraphInstantiate(&ge[which], gg[which], nullptr, nullptr, 0));
         };
-        // the traced re-run of a small network: one launch per segment
-        const bool small = h->small && h->sm.n_scen == 1 && h->small_veh <= kSmallActive;
         try {
-            for (int wch = small ? 2 : 0; wch < 4; ++wch) capture(wch);
+            for (int wch = 0; wch < 4 && !small; ++wch) capture(wch);
             bool a_is_in = true;                       // lx/lv are lam[0]/lam[1]
             for (int sg = nseg - 1; sg >= 0; --sg) {
                 const int t0 = sg * R, t1 = std::min(T, t0 + R);
@@ -1367,6 +1371,11 @@ sim_status sim_backward(sim_handle* h, const double* dL_dmean_tt, double* dL_dpa
                     const bool batch = t1 - t >= kGraphSteps;
                     HIP_OK(hipGraphLaunch(ge[batch ? 1 : 0], h->stream));
                     t += batch ? kGraphSteps : 1;
+                }
+                if (small) {
+                    hipLaunchKernelGGL(k_bw_small, dim3(1), dim3(kSmallBwNT), 0, h->stream, saved, trace, (size_t)N,
+                                       nact, t1 - t0, NC, lam[0], lam[1], lt, dw, part, gpart);
+                    continue;
                 }
                 double *ix = a_is_in ? lam[0] : lam[2], *iv = a_is_in ? lam[1] : lam[3];
                 double *ox = a_is_in ? lam[2] : lam[0], *ov = a_is_in ? lam[3] : lam[1];
@@ -1409,7 +1418,7 @@ sim_status sim_backward(sim_handle* h, const double* dL_dmean_tt, double* dL_dpa
         HIP_OK(hipStreamSynchronize(h->stream));
         for (int k = 0; k < np; ++k) {
             double acc = 0.0;
-            for (int b = 0; b < gbw; ++b) acc += gp[(size_t)b * np + k];
+            for (int b = 0; b < gbw; ++b) acc += small ? gp[(size_t)k * gbw + b] : gp[(size_t)b * np + k];
             dL_dparams[k] = acc;
         }
     });

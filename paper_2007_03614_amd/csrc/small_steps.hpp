@@ -318,4 +318,92 @@ __global__ void __launch_bounds__(kSmallNT) k_small_gather(Dev d, Small sm, int 
     small_end_step(d, t);
 }
 
+// ---- the reverse sweep of a small network --------------------------------------
+// The steps [0, steps) of a traced segment, last first, in one launch of one
+// workgroup (k_backward, k_bw_looks and k_bw_gather as phases between workgroup
+// barriers: three launches a step take 32 us on the 10x10 grid, whose 370
+// records are one a thread).  The adjoints are updated in place: a vehicle's are
+// read by its own record and written after that, and one that was not yet on the
+// road is never read again.  The lists of look-ahead records are in LDS, the
+// parts in device memory, gpart: [5 * n_classes][kSmallBwNT], each thread's own.
+constexpr int kSmallBwNT = 512;
+
+template <int NC>
+__global__ void __launch_bounds__(kSmallBwNT) k_small_backward(Dev d, const TraceRec* trace, size_t stride,
+                                                              const int* nact, int steps, int n_classes, double* lx,
+                                                              double* lv, double* lt, const double* w, BwPart* part,
+                                                              double* gpart) {
+    __shared__ int lk_cnt[kSmallLanes];
+    __shared__ int lk_rec[kSmallLanes * kLookListCap];
+    __shared__ double lk_x[kSmallLanes], lk_v[kSmallLanes];
+    const int tid = threadIdx.x, nl = min(d.n_lanes_total, kSmallLanes), np = 5 * n_classes;
+    ParamGrad<NC> acc{};
+#pragma unroll
+    for (int k = 0; k < 5 * NC; ++k)
+        if (k < np) acc.g[k] = gpart[k * kSmallBwNT + tid];
+    for (int g = tid; g < nl; g += kSmallBwNT) lk_cnt[g] = 0;
+    __syncthreads();
+    for (int i = steps - 1; i >= 0; --i) {
+        const TraceRec* rec = trace + (size_t)i * stride;
+        const int n = nact[i];
+        for (int r = tid; r < n; r += kSmallBwNT) {
+            const TraceRec R = rec[r];
+            const BwRecord o = backward_record(d, R, lx, lv, lt, w);
+            part[r] = o.part;
+            acc.add(o);
+            if (follows(R) && (r == 0 || (int)rec[r - 1].vid != R.partner)) atomicOr(&d.ctl->err, kErrTrace);
+            if (looks_ahead(R)) {
+                const int k = atomicAdd(&lk_cnt[R.look_gl], 1);
+                if (k < kLookListCap) lk_rec[R.look_gl * kLookListCap + k] = r;
+                else atomicOr(&d.ctl->err, kErrTrace);
+            }
+        }
+        __syncthreads();
+        // own part and the follower's; meanwhile the lanes' look-ahead sums, in record order
+        for (int r = tid; r < n; r += kSmallBwNT) {
+            const int v = (int)rec[r].vid;
+            const BwPart P = part[r];
+            double ax = P.sx, av = P.sv;
+            if (r + 1 < n) {
+                const TraceRec F = rec[r + 1];
+                if (F.partner == v && follows(F)) {
+                    const BwPart Q = part[r + 1];
+                    ax += Q.px;
+                    av += Q.pv;
+                }
+            }
+            lx[v] = ax;
+            lv[v] = av;
+        }
+        for (int g = tid; g < nl; g += kSmallBwNT) {
+            const int m = min(lk_cnt[g], kLookListCap);
+            double sx = 0.0, sv = 0.0;
+            for (int k = 0, from = 0; k < m; ++k) {
+                int next = INT_MAX;
+                for (int q = 0; q < m; ++q) {
+                    const int r = lk_rec[g * kLookListCap + q];
+                    if (r >= from) next = min(next, r);
+                }
+                sx += part[next].px;
+                sv += part[next].pv;
+                from = next + 1;
+            }
+            lk_x[g] = sx;
+            lk_v[g] = sv;
+        }
+        __syncthreads();
+        for (int g = tid; g < nl; g += kSmallBwNT)
+            if (lk_cnt[g] > 0) {
+                const int v = rec[lk_rec[g * kLookListCap]].partner;   // the lane's rear, the partner of all of them
+                lx[v] += lk_x[g];
+                lv[v] += lk_v[g];
+                lk_cnt[g] = 0;
+            }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int k = 0; k < 5 * NC; ++k)
+        if (k < np) gpart[k * kSmallBwNT + tid] = acc.g[k];
+}
+
 }  // namespace manta

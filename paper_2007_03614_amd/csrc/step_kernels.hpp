@@ -2014,8 +2014,6 @@ __global__ void __launch_bounds__(kNT) k_scatter(Dev d) {
 // travel time) / (traversals of the edge).  Parameter gradients of the
 // workgroup's records are reduced in a fixed tree and added to its own slot
 // gpart[blockIdx][5 * classes] (one workgroup per slot, kernels in order).
-constexpr int kParamMax = 5 * 16;
-
 __device__ inline double idm_partials(double v, double v0, double vl, double s, const ClassParams& p, int kind,
                                       uint32_t bits, double d[8]) {
     for (int k = 0; k < 8; ++k) d[k] = 0.0;   // d acc / d (v, vl, s, v0, T, a, b, s0)
@@ -2075,15 +2073,108 @@ struct BwPart {
     double px, pv;    // its partner
 };
 
-__global__ void __launch_bounds__(kNT) k_backward(Dev d, const TraceRec* rec, const int* n_ptr, int t, int n_classes,
+// One record's part of the reverse step: for its own vehicle and its partner,
+// and the gradient of its class's parameters (g, zero where there is none).
+struct BwRecord {
+    BwPart part;
+    double g[5];
+    int cls;
+};
+
+__device__ inline BwRecord backward_record(const Dev& d, const TraceRec& R, const double* lx, const double* lv,
+                                           double* lt, const double* w) {
+    BwRecord o{};
+    const double dt = (double)d.dt;
+    const uint32_t bits = R.kb >> 8;
+    const int kind = (int)(R.kb & 255u);
+    const int i = (int)R.vid, e = R.edge;
+    const double L = (double)d.L[e];
+    const double x = R.x, v = R.v, xn = R.xn;
+    double mx = lx[i], mv = lv[i];
+    const int c = d.cls[i];
+    o.cls = c;
+    if (bits & (TB_HELD | TB_W | TB_ARRIVE)) {
+        mx = 0.0;
+        mv = 0.0;
+    }
+    if (bits & (TB_EXIT | TB_ARRIVE)) {       // crossing time (t + phi) dt, phi = (L - x) / (xn - x)
+        const double gt = w[e] + lt[i];
+        if (xn != x) {
+            const double dd = xn - x;
+            mx += gt * dt * (-(L - x) / (dd * dd));
+            o.part.sx = gt * dt * ((L - xn) / (dd * dd));
+        }
+        lt[i] = -w[e];
+    }
+    if (!(bits & (TB_HELD | TB_W))) {
+        const ClassParams cp = d.cp[c];
+        const double lim = (double)driver_limit(d.lim[e], d.v0_spread, d.seed, e, d.edge_period, d.rid[i]);
+        const double v0 = (double)cp.v0f * lim;
+        double pd[8];
+        const double acc = idm_partials(v, v0, (double)R.vl, (double)R.s, cp, kind, bits, pd);
+        double macc = 0.0, ax = 0.0, av = 0.0;
+        if (bits & TB_C) {                     // clamped to the leader's rear
+            o.part.px = mx;
+            mx = 0.0;
+        }
+        if (bits & TB_B) {                     // exact stop
+            ax += mx;
+            av += mx * (-v / acc);
+            macc += mx * (v * v / (2.0 * acc * acc));
+        } else {
+            ax += mx;
+            av += mx * dt + mv;
+            macc += mx * 0.5 * dt * dt + mv * dt;
+        }
+        av += macc * pd[0];
+        if (kind == kVeh || kind == kLook) {
+            ax -= macc * pd[2];
+            o.part.px += macc * pd[2];
+            o.part.pv += macc * pd[1];
+        } else if (kind == kStop) {
+            ax -= macc * pd[2];
+        }
+        o.part.sx += ax;
+        o.part.sv += av;
+        o.g[0] = macc * pd[3] * lim;
+        o.g[1] = macc * pd[4];
+        o.g[2] = macc * pd[5];
+        o.g[3] = macc * pd[6];
+        o.g[4] = macc * pd[7];
+    }
+    return o;
+}
+
+// whether record R's leader is the vehicle of the record before it, which then takes R's partner part
+__device__ inline bool follows(const TraceRec& R) {
+    const uint32_t bits = R.kb >> 8;
+    return ((int)(R.kb & 255u) == kVeh || (bits & TB_C)) && !(bits & (TB_HELD | TB_W));
+}
+__device__ inline bool looks_ahead(const TraceRec& R) {
+    return (int)(R.kb & 255u) == kLook && !((R.kb >> 8) & (TB_HELD | TB_W));
+}
+
+// Parameter gradients of one thread, NC classes at most.  Every access has a
+// constant index, so that they stay in registers: an array indexed by a
+// record's class would live in scratch memory.
+template <int NC>
+struct ParamGrad {
+    double g[5 * NC];
+    __device__ void add(const BwRecord& r) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int k = 0; k < 5; ++k) g[5 * c + k] += r.cls == c ? r.g[k] : 0.0;
+    }
+};
+
+template <int NC>
+__global__ void __launch_bounds__(kNT) k_backward(Dev d, const TraceRec* rec, const int* n_ptr, int n_classes,
                                                  const double* lx, const double* lv, BwPart* part, int* lk_cnt,
                                                  int* lk_rec, double* lt, const double* w, double* gpart,
                                                  double* ox, double* ov, int n_all) {
-    __shared__ double red[kNT];
-    double g[kParamMax];
-    const int np = 5 * n_classes;
-    for (int k = 0; k < np; ++k) g[k] = 0.0;
-    const double dt = (double)d.dt;
+    __shared__ double red[kNT / 64][5 * NC];
+    ParamGrad<NC> acc{};
     const int n = *n_ptr;
     // the step's output adjoints start at zero (k_bw_gather writes those of
     // the vehicles active at the step's start)
@@ -2093,81 +2184,31 @@ __global__ void __launch_bounds__(kNT) k_backward(Dev d, const TraceRec* rec, co
     }
     for (int r = blockIdx.x * kNT + threadIdx.x; r < n; r += gridDim.x * kNT) {
         const TraceRec R = rec[r];
-        const uint32_t bits = R.kb >> 8;
-        const int kind = (int)(R.kb & 255u);
-        const int i = (int)R.vid, e = R.edge, j = R.partner;
-        const double L = (double)d.L[e];
-        const double x = R.x, v = R.v, xn = R.xn;
-        double mx = lx[i], mv = lv[i];
-        BwPart P{0.0, 0.0, 0.0, 0.0};
-        if (bits & (TB_HELD | TB_W | TB_ARRIVE)) {
-            mx = 0.0;
-            mv = 0.0;
-        }
-        if (bits & (TB_EXIT | TB_ARRIVE)) {       // crossing time (t + phi) dt, phi = (L - x) / (xn - x)
-            const double gt = w[e] + lt[i];
-            if (xn != x) {
-                const double dd = xn - x;
-                mx += gt * dt * (-(L - x) / (dd * dd));
-                P.sx = gt * dt * ((L - xn) / (dd * dd));
-            }
-            lt[i] = -w[e];
-        }
-        if (!(bits & (TB_HELD | TB_W))) {
-            const int c = d.cls[i];
-            const ClassParams cp = d.cp[c];
-            const double lim = (double)driver_limit(d.lim[e], d.v0_spread, d.seed, e, d.edge_period, d.rid[i]);
-            const double v0 = (double)cp.v0f * lim;
-            double pd[8];
-            const double acc = idm_partials(v, v0, (double)R.vl, (double)R.s, cp, kind, bits, pd);
-            double macc = 0.0, ax = 0.0, av = 0.0;
-            if (bits & TB_C) {                     // clamped to the leader's rear
-                P.px = mx;
-                mx = 0.0;
-            }
-            if (bits & TB_B) {                     // exact stop
-                ax += mx;
-                av += mx * (-v / acc);
-                macc += mx * (v * v / (2.0 * acc * acc));
-            } else {
-                ax += mx;
-                av += mx * dt + mv;
-                macc += mx * 0.5 * dt * dt + mv * dt;
-            }
-            av += macc * pd[0];
-            if (kind == kVeh || kind == kLook) {
-                ax -= macc * pd[2];
-                P.px += macc * pd[2];
-                P.pv += macc * pd[1];
-            } else if (kind == kStop) {
-                ax -= macc * pd[2];
-            }
-            P.sx += ax;
-            P.sv += av;
-            g[5 * c + 0] += macc * pd[3] * lim;
-            g[5 * c + 1] += macc * pd[4];
-            g[5 * c + 2] += macc * pd[5];
-            g[5 * c + 3] += macc * pd[6];
-            g[5 * c + 4] += macc * pd[7];
-        }
-        part[r] = P;
-        if ((kind == kVeh || (bits & TB_C)) && !(bits & (TB_HELD | TB_W)) && (r == 0 || (int)rec[r - 1].vid != j))
+        const BwRecord o = backward_record(d, R, lx, lv, lt, w);
+        part[r] = o.part;
+        acc.add(o);
+        if (follows(R) && (r == 0 || (int)rec[r - 1].vid != R.partner))
             atomicOr(&d.ctl->err, kErrTrace);     // the leader is not the record just before
-        if (kind == kLook && !(bits & (TB_HELD | TB_W))) {
+        if (looks_ahead(R)) {
             const int k = atomicAdd(&lk_cnt[R.look_gl], 1);
             if (k < kLookListCap) lk_rec[(size_t)R.look_gl * kLookListCap + k] = r;
             else atomicOr(&d.ctl->err, kErrTrace);
         }
     }
-    for (int k = 0; k < np; ++k) {                 // fixed-order tree per parameter
-        red[threadIdx.x] = g[k];
-        __syncthreads();
-        for (int h = kNT / 2; h > 0; h >>= 1) {
-            if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) gpart[(size_t)blockIdx.x * np + k] += red[0];
-        __syncthreads();
+    // a fixed tree per parameter: over the lanes of a wavefront, then over the wavefronts
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < 5 * NC; ++k) {
+        double s = acc.g[k];
+        for (int h = 32; h > 0; h >>= 1) s += __shfl_xor(s, h);
+        if (lane == 0) red[wave][k] = s;
+    }
+    __syncthreads();
+    const int np = 5 * n_classes;
+    if ((int)threadIdx.x < np) {
+        double s = red[0][threadIdx.x];
+        for (int q = 1; q < kNT / 64; ++q) s += red[q][threadIdx.x];
+        gpart[(size_t)blockIdx.x * np + threadIdx.x] += s;
     }
 }
 
@@ -2180,7 +2221,7 @@ __global__ void __launch_bounds__(kNT) k_bw_looks(const TraceRec* rec, const int
     const int n = *n_ptr;
     for (int r = blockIdx.x * kNT + threadIdx.x; r < n; r += gridDim.x * kNT) {
         const TraceRec R = rec[r];
-        if ((int)(R.kb & 255u) != kLook || ((R.kb >> 8) & (TB_HELD | TB_W))) continue;
+        if (!looks_ahead(R)) continue;
         const int g = R.look_gl;
         const int m = min(lk_cnt[g], kLookListCap);
         int lst[kLookListCap];
@@ -2221,8 +2262,7 @@ __global__ void __launch_bounds__(kNT) k_bw_gather(const TraceRec* rec, const in
         double ax = P.sx, av = P.sv;
         if (r + 1 < n) {
             const TraceRec F = rec[r + 1];
-            const uint32_t fb = F.kb >> 8;
-            if (F.partner == i && ((int)(F.kb & 255u) == kVeh || (fb & TB_C)) && !(fb & (TB_HELD | TB_W))) {
+            if (F.partner == i && follows(F)) {
                 const BwPart Q = part[r + 1];
                 ax += Q.px;
                 av += Q.pv;
