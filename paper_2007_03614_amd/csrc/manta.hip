@@ -16,6 +16,7 @@
 #include "../../include/manta.h"
 #include "routing.hpp"
 #include "small_steps.hpp"
+#include "state_io.hpp"
 #include "step_kernels.hpp"
 
 static_assert(manta::cNumCounters == SIM_N_COUNTERS, "device counters and sim_state.counters differ");
@@ -105,6 +106,11 @@ struct sim_handle {
     std::vector<int> small_due;       // [scenario][step]: vehicles due by then
     std::vector<int> small_n;         // [scenario]: vehicles
     int* arrived = nullptr;           // pinned, written by the device: [scenario] arrivals at the end of a launch
+    // state I/O: the arrays by vehicle id on the device, and a pinned block (allocated at first use) that small
+    // states pass through whole and larger ones with their head
+    IoWork iow{};
+    char* io_dev = nullptr;
+    char* io_pin = nullptr;
     // host copies of the static inputs needed for state I/O
     std::vector<int64_t> roff;
     std::vector<int32_t> redges, dep, lanes, lane_base, conn_off, conn_to, ins_lane;
@@ -136,6 +142,8 @@ struct sim_handle {
         graph_k = nullptr;
         if (arrived) (void)hipHostFree(arrived);
         arrived = nullptr;
+        if (io_pin) (void)hipHostFree(io_pin);
+        io_pin = nullptr;
         for (void* p : bufs) al.put(p);
         bufs.clear();
         for (void* p : snaps) al.put(p);
@@ -430,7 +438,7 @@ void plan_small(sim_handle* h, const std::vector<SmallRange>& range, long long m
     sm.range = h->upload(range.data(), range.size());
     sm.due = ns > 1 ? h->upload(h->small_due.data(), h->small_due.size()) : d.due;
     sm.due_stride = ns > 1 ? stride : 0;
-    sm.q0 = h->upload(h->qoff.data(), h->qoff.size());
+    sm.q0 = h->iow.q0;
     if (ns > 1) {
         const size_t NV = (size_t)std::max(h->n_veh, 1);
         sm.extra = Slots{h->dev<float>(NV), h->dev<float>(NV), h->dev<uint32_t>(NV), h->dev<int32_t>(NV),
@@ -852,6 +860,23 @@ sim_status create_impl(const sim_network* net, const sim_routes* r, const sim_id
             std::vector<double> neg1(NV, -1.0);
             HIP_OK(hipMemcpy(d.tau_in, neg1.data(), sizeof(double) * NV, hipMemcpyHostToDevice));
             HIP_OK(hipMemcpy(d.t_arr, neg1.data(), sizeof(double) * NV, hipMemcpyHostToDevice));
+            {   // state I/O
+                std::vector<uint32_t> entry(NV, 0);
+                for (int i = 0; i < N; ++i)
+                    entry[i] = (uint32_t)h->redges[h->roff[i]] | ((uint32_t)h->ins_lane[i] << kLaneEdgeBits);
+                IoWork& w = h->iow;
+                w.entry = h->upload(entry.data(), entry.size());
+                w.dep = h->upload(h->dep.data(), N);
+                w.q0 = h->upload(h->qoff.data(), h->qoff.size());
+                w.list = h->dev<int>(NV);
+                w.cnt = h->dev<int>(NL);
+                w.off = h->dev<int>(NL);
+                w.blk = h->dev<int>(h->n_blk);
+                w.qmin = h->dev<int>(std::max(NQ, 1));
+                w.qmax = h->dev<int>(std::max(NQ, 1));
+                HIP_OK(hipMemset(w.cnt, 0, sizeof(int) * (size_t)NL));
+                h->io_dev = h->dev<char>(state_io_at(nullptr, N, nullptr));
+            }
             {   // scenarios: edges, lanes, queues, nodes and vehicles in one piece each
                 const int np = d.edge_period, ns = std::max(1, E / np);
                 std::vector<SmallRange> range(ns + 1);
@@ -974,90 +999,136 @@ sim_status sim_n_active(sim_handle* h, int32_t* out) {
     });
 }
 
+}  // extern "C"
+
+namespace {
+// States up to kIoPinned bytes pass through pinned memory in one copy: a
+// pageable copy of a small field costs about 10 us each, whatever its size;
+// above, a copy per field between the device and the caller's pageable arrays
+// is as fast.  A read of at most kIoDirect vehicles is written there by the
+// kernel itself.
+constexpr size_t kIoPinned = (size_t)1 << 20;
+constexpr int kIoDirect = 2048;
+
+StateIo io_pinned(sim_handle* h) {
+    if (!h->io_pin) HIP_OK(hipHostMalloc((void**)&h->io_pin, kIoPinned, hipHostMallocDefault));
+    StateIo s;
+    // only the head where the arrays do not fit
+    state_io_at(h->io_pin, state_io_at(nullptr, h->n_veh, nullptr) <= kIoPinned ? h->n_veh : 0, &s);
+    return s;
+}
+
+// f(array in a, array in b, bytes) for every field of a state; caller: its array in sim_state
+template <class F>
+void for_each_field(const StateIo& a, const sim_state* s, int n, F&& f) {
+    const size_t N = (size_t)n;
+    f((void*)a.status, (void*)s->status, N);
+    f((void*)a.edge, (void*)s->edge, 4 * N);
+    f((void*)a.lane, (void*)s->lane, 4 * N);
+    f((void*)a.cursor, (void*)s->cursor, 4 * N);
+    f((void*)a.x, (void*)s->x, 4 * N);
+    f((void*)a.v, (void*)s->v, 4 * N);
+    f((void*)a.held_since, (void*)s->held_since, 4 * N);
+    f((void*)a.mand, (void*)s->mand, N);
+    f((void*)a.ww, (void*)s->ww, 4 * N);
+    f((void*)a.tau_in, (void*)s->tau_in, 8 * N);
+    f((void*)a.t_arr, (void*)s->t_arr, 8 * N);
+}
+
+// Why a written state is refused: its first inconsistent vehicle, then the
+// first overlap, then the first queue out of order (the device has found one).
+void explain_bad_state(const sim_handle* h, const sim_state* in) {
+    struct Rec {
+        int edge, lane;
+        float x;
+        int id;
+    };
+    std::vector<Rec> act;
+    for (int i = 0; i < h->n_veh; ++i) {
+        const uint8_t s = in->status[i];
+        if (s > 2) throw Fail{SIM_EINVAL, fmt("vehicle %d: bad status", i)};
+        const int64_t rl = h->roff[i + 1] - h->roff[i];
+        if (in->cursor[i] < 0 || in->cursor[i] >= rl) throw Fail{SIM_EINVAL, fmt("vehicle %d: bad cursor", i)};
+        if (s == kActive) {
+            const int e = h->redges[h->roff[i] + in->cursor[i]];
+            if (in->edge[i] != e) throw Fail{SIM_EINVAL, fmt("vehicle %d: edge is not the route edge", i)};
+            if (in->lane[i] < 0 || in->lane[i] >= h->lanes[e]) throw Fail{SIM_EINVAL, fmt("vehicle %d: lane", i)};
+            if (!(in->x[i] >= 0.f && in->x[i] <= h->L[e]) || !(in->v[i] >= 0.f) || !std::isfinite(in->v[i]))
+                throw Fail{SIM_EINVAL, fmt("vehicle %d: x or v out of range", i)};
+            if (in->ww[i] < 0 || in->ww[i] > kPatience) throw Fail{SIM_EINVAL, fmt("vehicle %d: ww", i)};
+            act.push_back(Rec{e, in->lane[i], in->x[i], i});
+        }
+    }
+    std::sort(act.begin(), act.end(), [](const Rec& a, const Rec& b) {
+        if (a.edge != b.edge) return a.edge < b.edge;
+        if (a.lane != b.lane) return a.lane < b.lane;
+        if (a.x != b.x) return a.x > b.x;
+        return a.id > b.id;
+    });
+    for (size_t k = 1; k < act.size(); ++k)
+        if (act[k].edge == act[k - 1].edge && act[k].lane == act[k - 1].lane &&
+            act[k - 1].x - h->len_c[h->cls[act[k - 1].id]] < act[k].x)
+            throw Fail{SIM_EINVAL, fmt("vehicles %d and %d overlap", act[k - 1].id, act[k].id)};
+    for (size_t q = 0; q + 1 < h->qoff.size(); ++q) {
+        int k = h->qoff[q];
+        while (k < h->qoff[q + 1] && in->status[h->qveh[k]] != kWaiting) ++k;
+        for (int k2 = k; k2 < h->qoff[q + 1]; ++k2)
+            if (in->status[h->qveh[k2]] != kWaiting)
+                throw Fail{SIM_EINVAL, fmt("vehicle %d departed before an earlier vehicle of its entry lane",
+                                           h->qveh[k2])};
+    }
+    throw Fail{SIM_EINVAL, "inconsistent state"};
+}
+}  // namespace
+
+extern "C" {
+
 sim_status sim_read_state(sim_handle* h, sim_state* o) {
     if (!h || !o) return SIM_EINVAL;
     return guarded(h, [&] {
-        const Dev& d = h->d;
         const int N = h->n_veh;
+        const size_t bytes = state_io_at(nullptr, N, nullptr);
+        const StateIo pin = io_pinned(h);
+        StateIo dev;
+        state_io_at(h->io_dev, N, &dev);
+        const bool whole = bytes <= kIoPinned, direct = N <= kIoDirect && whole;
+        const int g = std::max((int)cNumCounters, std::min(2048, (N + kNT - 1) / kNT));
+        if (direct) {
+            void* p = nullptr;
+            HIP_OK(hipHostGetDevicePointer(&p, h->io_pin, 0));
+            state_io_at((char*)p, N, &dev);
+            pin.head->bad = 0;
+        } else {
+            HIP_OK(hipMemsetAsync(&dev.head->bad, 0, sizeof(int), h->stream));
+        }
+        hipLaunchKernelGGL(k_io_read, dim3(g), dim3(kNT), 0, h->stream, h->d, h->iow, dev);
+        HIP_OK(hipGetLastError());
+        if (!direct)
+            HIP_OK(hipMemcpyAsync(pin.head, dev.head, whole ? bytes : sizeof(IoHead), hipMemcpyDeviceToHost, h->stream));
         HIP_OK(hipStreamSynchronize(h->stream));
-        Ctl c;
-        HIP_OK(hipMemcpy(&c, d.ctl, sizeof(Ctl), hipMemcpyDeviceToHost));
-        if (c.err) throw Fail{SIM_EDEVICE, fmt("device layout check failed (code %d)", c.err)};
-        const int par = c.t_a & 1, na = c.n_act[par];
-        std::vector<float> sx(na), sv(na), fx(N), fv(N);
-        std::vector<uint32_t> svid(na), smeta(na), fmeta(N);
-        std::vector<int32_t> sedge(na), cur(N), hs(N);
-        std::vector<uint8_t> st(N);
-        std::vector<double> tin(N), tar(N);
-        const Slots S = d.s[par];
-        if (na) {
-            HIP_OK(hipMemcpy(sx.data(), S.x, 4 * (size_t)na, hipMemcpyDeviceToHost));
-            HIP_OK(hipMemcpy(sv.data(), S.v, 4 * (size_t)na, hipMemcpyDeviceToHost));
-            HIP_OK(hipMemcpy(svid.data(), S.vid, 4 * (size_t)na, hipMemcpyDeviceToHost));
-            HIP_OK(hipMemcpy(smeta.data(), S.meta, 4 * (size_t)na, hipMemcpyDeviceToHost));
-            HIP_OK(hipMemcpy(sedge.data(), S.edge, 4 * (size_t)na, hipMemcpyDeviceToHost));
-        }
-        if (N) {
-            HIP_OK(hipMemcpy(st.data(), d.status, (size_t)N, hipMemcpyDeviceToHost));
-            HIP_OK(hipMemcpy(cur.data(), d.cursor, 4 * (size_t)N, hipMemcpyDeviceToHost));
-            HIP_OK(hipMemcpy(hs.data(), d.held_since, 4 * (size_t)N, hipMemcpyDeviceToHost));
-            HIP_OK(hipMemcpy(tin.data(), d.tau_in, 8 * (size_t)N, hipMemcpyDeviceToHost));
-            HIP_OK(hipMemcpy(tar.data(), d.t_arr, 8 * (size_t)N, hipMemcpyDeviceToHost));
-            HIP_OK(hipMemcpy(fx.data(), d.fin_x, 4 * (size_t)N, hipMemcpyDeviceToHost));
-            HIP_OK(hipMemcpy(fv.data(), d.fin_v, 4 * (size_t)N, hipMemcpyDeviceToHost));
-            HIP_OK(hipMemcpy(fmeta.data(), d.fin_meta, 4 * (size_t)N, hipMemcpyDeviceToHost));
-        }
-        std::vector<int> slot_of(N, -1);
-        for (int s = 0; s < na; ++s) {
-            if (svid[s] >= (uint32_t)N) throw Fail{SIM_EDEVICE, "corrupt layout: vehicle id out of range"};
-            slot_of[svid[s]] = s;
-        }
-        for (int i = 0; i < N; ++i) {
-            float x = 0.f, v = 0.f;
-            int edge, lane, ww = 0;
-            uint8_t mand = 0;
-            if (st[i] == kActive) {
-                const int s = slot_of[i];
-                if (s < 0) throw Fail{SIM_EDEVICE, fmt("corrupt layout: active vehicle %d has no slot", i)};
-                x = sx[s];
-                v = sv[s];
-                edge = sedge[s];
-                lane = m_lane(smeta[s]);
-                mand = m_mand(smeta[s]);
-                ww = m_ww(smeta[s]);
-            } else if (st[i] == kArrived) {
-                x = fx[i];
-                v = fv[i];
-                edge = h->redges[h->roff[i] + cur[i]];
-                lane = m_lane(fmeta[i]);
-                mand = m_mand(fmeta[i]);
-                ww = m_ww(fmeta[i]);
-            } else {
-                edge = h->redges[h->roff[i]];
-                lane = h->ins_lane[i];
-            }
-            if (o->status) o->status[i] = st[i];
-            if (o->edge) o->edge[i] = edge;
-            if (o->lane) o->lane[i] = lane;
-            if (o->cursor) o->cursor[i] = cur[i];
-            if (o->x) o->x[i] = x;
-            if (o->v) o->v[i] = v;
-            if (o->held_since) o->held_since[i] = hs[i];
-            if (o->mand) o->mand[i] = mand;
-            if (o->ww) o->ww[i] = ww;
-            if (o->tau_in) o->tau_in[i] = tin[i];
-            if (o->t_arr) o->t_arr[i] = tar[i];
-        }
-        if (o->counters) {
-            std::vector<unsigned long long> cc((size_t)cNumCounters * kCounterCopies);
-            HIP_OK(hipMemcpy(cc.data(), d.counters, 8 * cc.size(), hipMemcpyDeviceToHost));
-            for (int k = 0; k < cNumCounters; ++k) {
-                unsigned long long v = 0;
-                for (int q = 0; q < kCounterCopies; ++q) v += cc[k * kCounterCopies + q];
-                o->counters[k] = (int64_t)v;
+        if (pin.head->err) throw Fail{SIM_EDEVICE, fmt("device layout check failed (code %d)", pin.head->err)};
+        if (pin.head->bad) throw Fail{SIM_EDEVICE, "corrupt layout: a slot without an active vehicle"};
+        std::vector<uint8_t> st;
+        const uint8_t* status = pin.status;
+        if (!whole) {
+            status = o->status;
+            if (!status) {
+                st.resize(N);
+                HIP_OK(hipMemcpyAsync(st.data(), dev.status, (size_t)N, hipMemcpyDeviceToHost, h->stream));
+                status = st.data();
             }
         }
-        o->t = c.t_a;
+        for_each_field(whole ? pin : dev, o, N, [&](void* from, void* to, size_t n) {
+            if (!to || !n) return;
+            if (whole) memcpy(to, from, n);
+            else HIP_OK(hipMemcpyAsync(to, from, n, hipMemcpyDeviceToHost, h->stream));
+        });
+        HIP_OK(hipStreamSynchronize(h->stream));
+        if (std::count(status, status + N, (uint8_t)kActive) != pin.head->n_act)
+            throw Fail{SIM_EDEVICE, "corrupt layout: an active vehicle has no slot"};
+        if (o->counters)
+            for (int k = 0; k < cNumCounters; ++k) o->counters[k] = (int64_t)pin.head->counters[k];
+        o->t = pin.head->t;
     });
 }
 
@@ -1070,134 +1141,42 @@ sim_status sim_write_state(sim_handle* h, const sim_state* in) {
             throw Fail{SIM_EINVAL, "every state field is required"};
         if (in->t < 0) throw Fail{SIM_EINVAL, "t < 0"};
         const Dev& d = h->d;
-        struct Rec {
-            int edge, lane;
-            float x;
-            int id;
-        };
-        std::vector<Rec> act;
-        for (int i = 0; i < N; ++i) {
-            const uint8_t s = in->status[i];
-            if (s > 2) throw Fail{SIM_EINVAL, fmt("vehicle %d: bad status", i)};
-            const int64_t rl = h->roff[i + 1] - h->roff[i];
-            if (in->cursor[i] < 0 || in->cursor[i] >= rl) throw Fail{SIM_EINVAL, fmt("vehicle %d: bad cursor", i)};
-            if (s == kActive) {
-                const int e = h->redges[h->roff[i] + in->cursor[i]];
-                if (in->edge[i] != e) throw Fail{SIM_EINVAL, fmt("vehicle %d: edge is not the route edge", i)};
-                if (in->lane[i] < 0 || in->lane[i] >= h->lanes[e]) throw Fail{SIM_EINVAL, fmt("vehicle %d: lane", i)};
-                if (!(in->x[i] >= 0.f && in->x[i] <= h->L[e]) || !(in->v[i] >= 0.f) || !std::isfinite(in->v[i]))
-                    throw Fail{SIM_EINVAL, fmt("vehicle %d: x or v out of range", i)};
-                if (in->ww[i] < 0 || in->ww[i] > kPatience) throw Fail{SIM_EINVAL, fmt("vehicle %d: ww", i)};
-                act.push_back(Rec{e, in->lane[i], in->x[i], i});
-            }
-        }
-        std::sort(act.begin(), act.end(), [](const Rec& a, const Rec& b) {
-            if (a.edge != b.edge) return a.edge < b.edge;
-            if (a.lane != b.lane) return a.lane < b.lane;
-            if (a.x != b.x) return a.x > b.x;
-            return a.id > b.id;
+        const hipStream_t s = h->stream;
+        const size_t bytes = state_io_at(nullptr, N, nullptr);
+        const bool whole = bytes <= kIoPinned;
+        const StateIo pin = io_pinned(h);
+        StateIo dev;
+        state_io_at(h->io_dev, N, &dev);
+        HIP_OK(hipStreamSynchronize(s));
+        *pin.head = IoHead{};
+        pin.head->t = in->t;
+        pin.head->set_counters = in->counters != nullptr;
+        if (in->counters)
+            for (int k = 0; k < cNumCounters; ++k) pin.head->counters[k] = in->counters[k];
+        for_each_field(whole ? pin : dev, in, N, [&](void* to, void* from, size_t n) {
+            if (!n) return;
+            if (whole) memcpy(to, from, n);
+            else HIP_OK(hipMemcpyAsync(to, from, n, hipMemcpyHostToDevice, s));
         });
-        for (size_t k = 1; k < act.size(); ++k)
-            if (act[k].edge == act[k - 1].edge && act[k].lane == act[k - 1].lane &&
-                act[k - 1].x - h->len_c[h->cls[act[k - 1].id]] < act[k].x)
-                throw Fail{SIM_EINVAL, fmt("vehicles %d and %d overlap", act[k - 1].id, act[k].id)};
-        const int na = (int)act.size(), t = in->t, par = t & 1;
-        std::vector<float> sx(na), sv(na);
-        std::vector<uint32_t> svid(na), smeta(na);
-        std::vector<int32_t> sedge(na), snxt(na);
-        std::vector<LaneRear> rear(h->n_lanes);
-        for (auto& r : rear) r = LaneRear{0.f, 0.f, -1, 0u};
-        for (int k = 0; k < na; ++k) {
-            const int i = act[k].id, e = act[k].edge;
-            const int64_t pos = h->roff[i] + in->cursor[i] + 1;
-            const int nx = pos < h->roff[i + 1] ? h->redges[pos] : -1;
-            sx[k] = in->x[i];
-            sv[k] = in->v[i];
-            svid[k] = (uint32_t)i;
-            sedge[k] = e;
-            snxt[k] = nx;
-            smeta[k] = m_make(in->lane[i], in->mand[i] != 0, in->held_since[i] >= 0, in->ww[i], h->cls[i],
-                              h->mask_of(e, nx));
-            const bool last = (k + 1 == na) || act[k + 1].edge != e || act[k + 1].lane != act[k].lane;
-            if (last) rear[h->lane_base[e] + act[k].lane] = LaneRear{in->x[i] - h->len_c[h->cls[i]], in->v[i], t, (uint32_t)i};
-        }
-        // departure queues: the vehicles that have left a queue must be a prefix of it
-        std::vector<int> qhead(h->qoff.begin(), h->qoff.end());
-        int departed = 0;
-        for (size_t q = 0; q + 1 < h->qoff.size(); ++q) {
-            int k = h->qoff[q];
-            while (k < h->qoff[q + 1] && in->status[h->qveh[k]] != kWaiting) ++k;
-            for (int k2 = k; k2 < h->qoff[q + 1]; ++k2)
-                if (in->status[h->qveh[k2]] != kWaiting)
-                    throw Fail{SIM_EINVAL, fmt("vehicle %d departed before an earlier vehicle of its entry lane",
-                                               h->qveh[k2])};
-            qhead[q] = k;
-            departed += k - h->qoff[q];
-        }
-        std::vector<uint8_t> st(in->status, in->status + N);
-        std::vector<float> fx(N, 0.f), fv(N, 0.f);
-        std::vector<uint32_t> fmeta(N, 0);
-        for (int i = 0; i < N; ++i)
-            if (st[i] == kArrived) {
-                fx[i] = in->x[i];
-                fv[i] = in->v[i];
-                fmeta[i] = m_make(in->lane[i], in->mand[i] != 0, false, in->ww[i], h->cls[i], 0);
-            }
-        HIP_OK(hipStreamSynchronize(h->stream));
-        const Slots S = d.s[par];
-        if (na) {
-            HIP_OK(hipMemcpy(S.x, sx.data(), 4 * (size_t)na, hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(S.v, sv.data(), 4 * (size_t)na, hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(S.vid, svid.data(), 4 * (size_t)na, hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(S.meta, smeta.data(), 4 * (size_t)na, hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(S.edge, sedge.data(), 4 * (size_t)na, hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(S.nxt, snxt.data(), 4 * (size_t)na, hipMemcpyHostToDevice));
-        }
-        if (N) {
-            HIP_OK(hipMemcpy(d.status, st.data(), (size_t)N, hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(d.cursor, in->cursor, 4 * (size_t)N, hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(d.held_since, in->held_since, 4 * (size_t)N, hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(d.tau_in, in->tau_in, 8 * (size_t)N, hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(d.t_arr, in->t_arr, 8 * (size_t)N, hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(d.fin_x, fx.data(), 4 * (size_t)N, hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(d.fin_v, fv.data(), 4 * (size_t)N, hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(d.fin_meta, fmeta.data(), 4 * (size_t)N, hipMemcpyHostToDevice));
-        }
-        HIP_OK(hipMemcpy(d.qhead, qhead.data(), 4 * qhead.size(), hipMemcpyHostToDevice));
-        if (h->nq > 0) {
-            std::vector<int2> qhd(h->nq);
-            for (int q = 0; q < h->nq; ++q)
-                qhd[q] = qhead[q] < h->qoff[q + 1] ? make_int2(h->dep[h->qveh[qhead[q]]], h->qveh[qhead[q]])
-                                                   : make_int2(INT_MAX, -1);
-            HIP_OK(hipMemcpy(d.qhd, qhd.data(), sizeof(int2) * qhd.size(), hipMemcpyHostToDevice));
-        }
-        HIP_OK(hipMemcpy(d.rear, rear.data(), sizeof(LaneRear) * h->n_lanes, hipMemcpyHostToDevice));
-        HIP_OK(hipMemset(d.post, 0xFF, sizeof(LanePost) * h->n_lanes));
-        HIP_OK(hipMemset(d.outbox, 0xFF, sizeof(Outbox) * h->n_lanes));
-        HIP_OK(hipMemset(d.req_stamp, 0xFF, sizeof(int) * h->n_lanes));
-        HIP_OK(hipMemset(d.win, 0xFF, sizeof(unsigned long long) * h->n_lanes));
-        HIP_OK(hipMemset(d.exit_stamp, 0xFF, sizeof(int) * h->n_lanes));
-        HIP_OK(hipMemset(d.enter_stamp, 0xFF, sizeof(int) * h->n_lanes));
-        HIP_OK(hipMemset(d.big_lane, 0xFF, sizeof(int2) * h->n_lanes));   // no big-tile marks of other runs
-        HIP_OK(hipMemset(d.moved_at, 0xFF, sizeof(int) * kMovedSlots));     // nor movement stamps
-        HIP_OK(hipMemset(tile_counters(d), 0, sizeof(int) * kTileCtrInts));   // nor tile counts
-        if (d.imode == 1) {                        // the round-robin restarts
-            HIP_OK(hipMemset(d.rr, 0xFF, sizeof(int) * (size_t)d.n_nodes));
-            HIP_OK(hipMemset(d.win_node, 0xFF, sizeof(unsigned long long) * (size_t)d.n_nodes));
-        }
-        Ctl c{};
-        c.t_a = t;
-        c.t_b = t;
-        c.n_act[par] = na;
-        c.n_departed = departed;
-        HIP_OK(hipMemcpy(d.ctl, &c, sizeof(Ctl), hipMemcpyHostToDevice));
-        if (in->counters) {
-            std::vector<unsigned long long> cc((size_t)cNumCounters * kCounterCopies, 0ull);
-            for (int k = 0; k < cNumCounters; ++k) cc[(size_t)k * kCounterCopies] = (unsigned long long)in->counters[k];
-            HIP_OK(hipMemcpy(d.counters, cc.data(), 8 * cc.size(), hipMemcpyHostToDevice));
-        }
-        HIP_OK(hipDeviceSynchronize());
-        h->t = t;
+        HIP_OK(hipMemcpyAsync(dev.head, pin.head, whole ? bytes : sizeof(IoHead), hipMemcpyHostToDevice, s));
+        auto grid = [](long long n) { return dim3((unsigned)std::max(1LL, std::min(4096LL, (n + kNT - 1) / kNT))); };
+        // the new layout is built in the buffer that the current step does not use
+        const Slots B = d.s[(h->t & 1) ^ 1], S = d.s[in->t & 1];
+        const dim3 b(kNT), gv = grid(std::max(N, d.nq));
+        hipLaunchKernelGGL(k_io_clear, grid(d.nq), b, 0, s, h->iow, d.nq);
+        hipLaunchKernelGGL(k_io_check, gv, b, 0, s, d, h->iow, dev);
+        hipLaunchKernelGGL(k_io_lanes, dim3(h->n_blk), dim3(kLaneBlock), 0, s, h->iow);
+        hipLaunchKernelGGL(k_io_blocks, dim3(1), dim3(kBigNT), 0, s, d, h->iow, dev.head);
+        hipLaunchKernelGGL(k_io_place, gv, b, 0, s, d, h->iow, dev);
+        hipLaunchKernelGGL(k_io_rank, gv, b, 0, s, d, h->iow, dev, B);
+        hipLaunchKernelGGL(k_io_verify, gv, b, 0, s, d, h->iow, dev, B);
+        hipLaunchKernelGGL(k_io_apply, grid(std::max({(long long)N, (long long)h->n_lanes, (long long)d.n_nodes})), b, 0,
+                           s, d, h->iow, dev, B, S);
+        HIP_OK(hipGetLastError());
+        HIP_OK(hipMemcpyAsync(pin.head, dev.head, sizeof(IoHead), hipMemcpyDeviceToHost, s));
+        HIP_OK(hipStreamSynchronize(s));
+        if (pin.head->bad) explain_bad_state(h, in);
+        h->t = in->t;
         if (h->arrived) {
             std::vector<int> arr(h->sm.n_scen, 0);
             for (int k = 0, i = 0; k < h->sm.n_scen; ++k)
@@ -1206,7 +1185,7 @@ sim_status sim_write_state(sim_handle* h, const sim_state* in) {
         }
         for (void* p : h->snaps) h->al.put(p);
         h->snaps.clear();
-        h->rec_broken = (t != 0);
+        h->rec_broken = (in->t != 0);
     });
 }
 
