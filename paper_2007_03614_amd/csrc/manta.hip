@@ -270,11 +270,12 @@ void launch_step(sim_handle* h, hipStream_t s, hipEvent_t* ev = nullptr) {
     const Dev& d = h->d;
     const dim3 b(kNT);
     const bool lds_scan = h->n_blk <= kScanLdsMax;
+    const auto commit = (1 << d.lane_shift) == kManyBlock ? k_commit_many : k_commit;
     if (!ev) {
         hipLaunchKernelGGL(d.v0_spread != 0.0f ? k_tile_step_v0spread : k_tile_step, dim3(h->g_tile), dim3(kTileNT),
                            0, s, d);
         hipLaunchKernelGGL(k_big_admit, dim3(h->g_big), dim3(kBigNT), 0, s, d);
-        hipLaunchKernelGGL(k_commit, dim3(h->n_blk), dim3(kLaneBlock), 0, s, d);
+        hipLaunchKernelGGL(commit, dim3(h->n_blk), dim3(kCommitNT), 0, s, d);
         if (lds_scan) {
             hipLaunchKernelGGL(k_scatter<true>, dim3(h->g_scatter), b, h->scatter_lds, s, d);
         } else {
@@ -287,10 +288,10 @@ void launch_step(sim_handle* h, hipStream_t s, hipEvent_t* ev = nullptr) {
                           0, s, ev[0], ev[1], 0, d);
     hipExtLaunchKernelGGL(k_big_admit, dim3(h->g_big), dim3(kBigNT), 0, s, ev[2], ev[3], 0, d);
     if (lds_scan) {
-        hipExtLaunchKernelGGL(k_commit, dim3(h->n_blk), dim3(kLaneBlock), 0, s, ev[4], ev[5], 0, d);
+        hipExtLaunchKernelGGL(commit, dim3(h->n_blk), dim3(kCommitNT), 0, s, ev[4], ev[5], 0, d);
         hipExtLaunchKernelGGL(k_scatter<true>, dim3(h->g_scatter), b, h->scatter_lds, s, ev[6], ev[7], 0, d);
     } else {   // the block scan is counted with commit
-        hipExtLaunchKernelGGL(k_commit, dim3(h->n_blk), dim3(kLaneBlock), 0, s, ev[4], nullptr, 0, d);
+        hipExtLaunchKernelGGL(commit, dim3(h->n_blk), dim3(kCommitNT), 0, s, ev[4], nullptr, 0, d);
         hipExtLaunchKernelGGL(k_blkscan, dim3(1), dim3(kBigNT), 0, s, nullptr, ev[5], 0, d);
         hipExtLaunchKernelGGL(k_scatter<false>, dim3(h->g_scatter), b, 0, s, ev[6], ev[7], 0, d);
     }
@@ -570,22 +571,23 @@ sim_status create_impl(const sim_network* net, const sim_routes* r, const sim_id
             Dev& d = h->d;
             // ---- network
             // Lanes are numbered edge after edge, with gaps so that no edge lies
-            // across a multiple of kLaneBlock (a workgroup of k_commit has whole
-            // edges); the gaps never hold a vehicle.
-            h->lanes.assign(E, 0);
+            // across two commit blocks (a workgroup of the commit kernel has
+            // whole edges); the gaps never hold a vehicle.
+            h->lanes.assign(net->n_lanes, net->n_lanes + E);
             h->lane_base.assign(E + 1, 0);
             long long real = 0, next = 0;
+            for (const int n : h->lanes) real += n;
+            if (real > kLanesMax) throw Fail{SIM_EUNSUPPORTED, fmt("%lld lanes: at most %d", real, kLanesMax)};
+            const int block = real > kManyLanes ? kManyBlock : kCommitNT;
+            d.lane_shift = __builtin_ctz(block);
             for (int e = 0; e < E; ++e) {
-                const int n = net->n_lanes[e];
-                h->lanes[e] = n;
-                real += n;
-                if (real > kLanesMax) throw Fail{SIM_EUNSUPPORTED, fmt("%lld lanes or more: at most %d", real, kLanesMax)};
-                if (next / kLaneBlock != (next + n - 1) / kLaneBlock) next = (next + kLaneBlock - 1) / kLaneBlock * kLaneBlock;
+                const int n = h->lanes[e];
+                if (next / block != (next + n - 1) / block) next = (next + block - 1) / block * block;
                 h->lane_base[e] = (int)next;
                 next += n;
             }
             h->lane_base[E] = (int)next;
-            const int NL = (int)((next + kLaneBlock - 1) / kLaneBlock * kLaneBlock);
+            const int NL = (int)((next + block - 1) / block * block);
             h->n_lanes = NL;
             h->lanes_real = (int)real;
             const int NC = net->conn_off[E];
@@ -781,7 +783,7 @@ sim_status create_impl(const sim_network* net, const sim_routes* r, const sim_id
                 h->g_big_min = (int)std::max(1LL, std::min<long long>(h->g_big_max, (items + kBigNT - 1) / kBigNT));
                 h->g_big = h->g_big_min;
             }
-            h->n_blk = NL / kLaneBlock;
+            h->n_blk = NL >> d.lane_shift;
             d.n_blk = h->n_blk;
             h->scatter_lds = h->n_blk <= kScanLdsMax ? sizeof(int) * (size_t)h->n_blk : 0;
             h->g_scatter_max = std::max(1, std::min(4096, (N + kNT - 1) / kNT));
@@ -1165,7 +1167,9 @@ sim_status sim_write_state(sim_handle* h, const sim_state* in) {
         const dim3 b(kNT), gv = grid(std::max(N, d.nq));
         hipLaunchKernelGGL(k_io_clear, grid(d.nq), b, 0, s, h->iow, d.nq);
         hipLaunchKernelGGL(k_io_check, gv, b, 0, s, d, h->iow, dev);
-        hipLaunchKernelGGL(k_io_lanes, dim3(h->n_blk), dim3(kLaneBlock), 0, s, h->iow);
+        const int block = 1 << d.lane_shift;
+        hipLaunchKernelGGL(block == kManyBlock ? k_io_lanes<kManyBlock> : k_io_lanes<kCommitNT>, dim3(h->n_blk), dim3(block), 0,
+                           s, h->iow);
         hipLaunchKernelGGL(k_io_blocks, dim3(1), dim3(kBigNT), 0, s, d, h->iow, dev.head);
         hipLaunchKernelGGL(k_io_place, gv, b, 0, s, d, h->iow, dev);
         hipLaunchKernelGGL(k_io_rank, gv, b, 0, s, d, h->iow, dev, B);

@@ -197,7 +197,7 @@ __global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps)
             const int gl = tb.req_list[i], li = gl - r0.lane;
             if (ex.vid[li] != ~0u) {
                 const uint32_t le = d.lane_edge[gl];
-                commit_travel_time(d, (int)(le & kLaneEdgeMask), (int)(le >> kLaneEdgeBits), li, ex);
+                commit_travel_time<false>(d, (int)(le & kLaneEdgeMask), (int)(le >> kLaneEdgeBits), li, ex);
             }
         }
         // the lanes of the next layout
@@ -217,7 +217,10 @@ __global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps)
             nnew = stot;
         }
         for (int i = tid; i < max(n, nl); i += NT)
-            scatter_item(d, tb, S, B, i < n ? i : -1, i < nl ? r0.lane + i : -1, nnew, t, slen, [](int) { return 0; });
+            scatter_item(
+                d, tb, S, B, i < n ? i : -1,
+                [&] { return i < nl && tb.enter_stamp[i] == t ? r0.lane + i : -1; }, nnew, t, slen,
+                [](int) { return 0; });
         if (d.imode == 1)
             for (int i = tid; i < sm.nodes; i += NT) tb.win_node[i] = ~0ull;
         if (tid == 0) {
@@ -336,7 +339,8 @@ __global__ void __launch_bounds__(kSmallBwNT) k_small_backward(Dev d, const Trac
     __shared__ int lk_cnt[kSmallLanes];
     __shared__ int lk_rec[kSmallLanes * kLookListCap];
     __shared__ double lk_x[kSmallLanes], lk_v[kSmallLanes];
-    const int tid = threadIdx.x, nl = min(d.n_lanes_total, kSmallLanes), np = 5 * n_classes;
+    const EdgeC last = d.ec[d.n_edges - 1];
+    const int tid = threadIdx.x, nl = min(last.lane_base + last.lanes, kSmallLanes), np = 5 * n_classes;
     ParamGrad<NC> acc{};
 #pragma unroll
     for (int k = 0; k < 5 * NC; ++k)

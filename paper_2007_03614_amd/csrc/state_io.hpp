@@ -65,7 +65,7 @@ struct IoWork {
     int* list;                // [vehicle] active vehicles by lane, unordered within
     int* cnt;                 // [lane] vehicles still to be placed; zero between calls
     int* off;                 // [lane] first slot, relative to the lane's block
-    int* blk;                 // [block of kLaneBlock lanes] vehicles, then first slot
+    int* blk;                 // [commit block] vehicles, then first slot
     int* qmin;                // [queue] first index that still waits, last that has left
     int* qmax;
 };
@@ -171,13 +171,14 @@ __global__ void __launch_bounds__(kNT) k_io_check(Dev d, IoWork w, StateIo in) {
     if (bad) in.head->bad = 1;
 }
 
-__global__ void __launch_bounds__(kLaneBlock) k_io_lanes(IoWork w) {
-    __shared__ Scan4 wsh4[kLaneBlock / 64];
-    const int gl = blockIdx.x * kLaneBlock + threadIdx.x;
+template <int NT>
+__global__ void __launch_bounds__(NT) k_io_lanes(IoWork w) {
+    __shared__ Scan4 wsh4[NT / 64];
+    const int gl = blockIdx.x * NT + threadIdx.x;
     const int c = w.cnt[gl];
-    const Scan4 r = wg_exclusive_scan4<kLaneBlock>(Scan4{c, -1, -1, -1}, wsh4);
+    const Scan4 r = wg_exclusive_scan4<NT>(Scan4{c, -1, -1, -1}, wsh4);
     w.off[gl] = r.s;
-    if (threadIdx.x == kLaneBlock - 1) w.blk[blockIdx.x] = r.s + c;
+    if (threadIdx.x == NT - 1) w.blk[blockIdx.x] = r.s + c;
 }
 
 __global__ void __launch_bounds__(kBigNT) k_io_blocks(Dev d, IoWork w, IoHead* head) {
@@ -189,7 +190,7 @@ __global__ void __launch_bounds__(kBigNT) k_io_blocks(Dev d, IoWork w, IoHead* h
 }
 
 __device__ inline int io_start(const Dev& d, const IoWork& w, int gl, int n_act) {
-    return gl < d.n_lanes_total ? w.blk[gl / kLaneBlock] + w.off[gl] : n_act;
+    return gl < d.n_lanes_total ? w.blk[gl >> d.lane_shift] + w.off[gl] : n_act;
 }
 
 // The active vehicles of every lane, in any order (a state with a bad vehicle
@@ -206,7 +207,7 @@ __global__ void __launch_bounds__(kNT) k_io_place(Dev d, IoWork w, StateIo in) {
             ww < 0 || ww > kPatience)
             continue;
         const int gl = c.lane_base + l;
-        w.list[w.blk[gl / kLaneBlock] + w.off[gl] + atomicSub(&w.cnt[gl], 1) - 1] = i;
+        w.list[w.blk[gl >> d.lane_shift] + w.off[gl] + atomicSub(&w.cnt[gl], 1) - 1] = i;
     }
 }
 

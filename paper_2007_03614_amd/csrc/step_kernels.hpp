@@ -42,7 +42,9 @@ constexpr int kTileCtrStride = 32;       // ints between two counters: one 128-b
 constexpr int kTileCtrInts = 2 * kTileGroups * kTileCtrStride;   // [step parity][group] counters
 constexpr int kTileWindowAuto = 192;     // largest window the per-step choice takes
 constexpr int kTileDrawTasks = 384;      // listed Philox blocks per tile round (more are computed in place)
-constexpr int kLaneBlock = 256;          // lanes per commit workgroup (one thread per lane)
+constexpr int kCommitNT = 256;           // threads per commit workgroup: one lane each, or four on
+constexpr int kManyLanes = 190000;       // networks of more lanes than this (k_commit_many)
+constexpr int kManyBlock = 4 * kCommitNT;
 constexpr int kLaneEdgeBits = 24;        // lane_edge: the lane's edge | its index on the edge << 24; ~0 past an edge's lanes
 constexpr uint32_t kLaneEdgeMask = (1u << kLaneEdgeBits) - 1u;
 constexpr int kLanesMax = (1 << 24) - 1; // lanes of a network at most (so edges, too, fit 24 bits)
@@ -254,6 +256,7 @@ struct Dev {
     int* blk_sum;
     int* blk_off;
     int n_blk;
+    int lane_shift;             // a commit block is 1 << lane_shift lanes
     double* tt_sum;
     unsigned long long* tt_cnt;
     EntryRec* ent;              // per lane: the record entering it this step (where enter_stamp == t)
@@ -332,7 +335,7 @@ struct TileBuf {
 };
 
 // lane words: first global lane and lane count (at most 8) in one word.  The
-// lanes are numbered with gaps (kLaneBlock), so a base may pass 2^24.
+// lanes are numbered with gaps (commit blocks), so a base may pass 2^24.
 constexpr int kLaneBaseBits = 28;
 __device__ inline int lw_base(uint32_t w) { return (int)(w & ((1u << kLaneBaseBits) - 1u)); }
 __device__ inline int lw_lanes(uint32_t w) { return (int)(w >> kLaneBaseBits); }
@@ -1475,15 +1478,17 @@ __device__ inline bool admit_head(const Dev& d, const LaneTabs& tb, int q, int2 
 // this step) and one per departure queue of [q00, q1), over workgroups wg of nwg.  A request is
 // eligible if it does not overlap the target lane's rear after the move; a
 // due queue head if the lane's rear leaves it s0 at x = 0.  Each thread takes
-// its items four at a time and loads their stamps (queue heads) together, so
-// that the loads overlap.
-// The four stamps are read into one bit mask of due items, so that no
+// its items eight at a time and loads their stamps (queue heads) together, so
+// that the loads overlap: the 1.09M lanes of the metropolitan lattice are one
+// round (7.3 us; in two rounds of four 8.4).  Items a whole stride apart: of
+// eight neighbouring lanes several may be due, one after another.
+// The eight stamps are read into one bit mask of due items, so that no
 // per-thread array is indexed by a runtime value (which would put it in
 // scratch memory).
 template <int NT, bool kDefer>
 __device__ inline void admit_items(const Dev& d, const LaneTabs& tb, const Slots& S, int t, int wg, int nwg, int l0,
                                    int l1, int q00, int q1) {
-    constexpr int kU = 4;
+    constexpr int kU = 8;
     const int stride = nwg * NT;
     for (int i0 = l0 + wg * NT + (int)threadIdx.x; i0 < l1; i0 += kU * stride) {
         unsigned due = 0;
@@ -1587,7 +1592,9 @@ __global__ void __launch_bounds__(kBigNT) k_big_admit(Dev d) {
 // what bounds it.  (One thread per edge, taking its lanes one after another, went
 // through it once per lane that any thread of the wavefront had a request on:
 // 10.9 us a step on the 100x100 city and 28.2 on the metropolitan lattice,
-// against 5.7 and 19.4.)
+// against 5.7 and 19.4.)  A lattice of 1.09M lanes is two rounds of the
+// wavefronts that fit the GPU, and one wavefront in two has a request: there a
+// thread takes four lanes (k_commit_many, 14.3 us).
 
 // A route entry's word: the next route edge | lane mask of the move there <<
 // 24; all ones on a route's last edge (no next edge, every lane).
@@ -1738,7 +1745,10 @@ __device__ inline int commit_lane(const Dev& d, const LaneTabs& tb, const Slots&
 
 // The travel time of lane li's exit (on edge e, lane l of it), once every lane
 // of the edge is settled (a barrier before): an edge's only exit adds its own,
-// the lowest lane of several exits adds them in ascending vehicle id.
+// the lowest lane of several exits adds them in ascending vehicle id.  kAtomic:
+// the only exit's is added in the L2, and nothing waits for the sum; not where
+// later steps of the same launch read it.
+template <bool kAtomic>
 __device__ inline void commit_travel_time(const Dev& d, int e, int l, int li, const Exits& ex) {
     const int first = li - l;
     const uint32_t n = ex.n[first];
@@ -1763,10 +1773,14 @@ __device__ inline void commit_travel_time(const Dev& d, int e, int l, int li, co
             from = id + 1u;
         }
         d.tt_sum[e] = sum;
+        d.tt_cnt[e] += (unsigned long long)n;
+    } else if (kAtomic) {
+        unsafeAtomicAdd(&d.tt_sum[e], ex.tt[li]);
+        atomicAdd(&d.tt_cnt[e], 1ull);
     } else {
         d.tt_sum[e] += ex.tt[li];
+        d.tt_cnt[e] += 1ull;
     }
-    d.tt_cnt[e] += (unsigned long long)n;
 }
 
 __device__ inline void flush_commit_counters(const Dev& d, const CounterAcc& acc, unsigned* shc) {
@@ -1775,15 +1789,15 @@ __device__ inline void flush_commit_counters(const Dev& d, const CounterAcc& acc
 }
 
 // A workgroup's lanes are those of whole edges (the lanes are numbered so that
-// no edge lies across a multiple of kLaneBlock); then the offsets of the lanes
-// in the workgroup.
-__global__ void __launch_bounds__(kLaneBlock) k_commit(Dev d) {
+// no edge lies across two commit blocks); then the offsets of the lanes in the
+// workgroup.
+__global__ void __launch_bounds__(kCommitNT) k_commit(Dev d) {
     __shared__ unsigned shc[cNumCounters];
-    __shared__ Scan4 wsh4[kLaneBlock / 64];
-    __shared__ uint32_t xid[kLaneBlock], xn[kLaneBlock];
-    __shared__ double xtt[kLaneBlock];
+    __shared__ Scan4 wsh4[kCommitNT / 64];
+    __shared__ uint32_t xid[kCommitNT], xn[kCommitNT];
+    __shared__ double xtt[kCommitNT];
     __shared__ int smoved;                                // gridlock detector: an exit or a departure here
-    const int tid = threadIdx.x, gl = blockIdx.x * kLaneBlock + tid;
+    const int tid = threadIdx.x, gl = blockIdx.x * kCommitNT + tid;
     const uint32_t le = d.lane_edge[gl];
     if (tid < cNumCounters) shc[tid] = 0;
     if (tid == 0) smoved = 0;
@@ -1798,10 +1812,103 @@ __global__ void __launch_bounds__(kLaneBlock) k_commit(Dev d) {
     acc.zero();
     int c = 0;
     if (le != ~0u) c = commit_lane(d, tb, d.s[par], gl, e, l, tid, t, acc, ex, &smoved);
-    const Scan4 run = wg_exclusive_scan4<kLaneBlock>(Scan4{c, -1, -1, -1}, wsh4);   // a barrier in it
+    const Scan4 run = wg_exclusive_scan4<kCommitNT>(Scan4{c, -1, -1, -1}, wsh4);   // a barrier in it
     d.lane_off[gl] = run.s;
-    if (tid == kLaneBlock - 1) d.blk_sum[blockIdx.x] = run.s + c;
-    if (xid[tid] != ~0u) commit_travel_time(d, e, l, tid, ex);
+    if (tid == kCommitNT - 1) d.blk_sum[blockIdx.x] = run.s + c;
+    if (xid[tid] != ~0u) commit_travel_time<true>(d, e, l, tid, ex);
+    flush_commit_counters(d, acc, shc);
+    publish_moved(d, &smoved, t);
+}
+
+// Which of four lanes' stamps are step t, as a mask.
+__device__ inline unsigned lanes_at(const int4& s, int t) {
+    return (s.x == t ? 1u : 0u) | (s.y == t ? 2u : 0u) | (s.z == t ? 4u : 0u) | (s.w == t ? 8u : 0u);
+}
+
+// The same for many lanes: the stamps and runs of four lanes a thread, in wide
+// loads; the lanes with a request and those with a claim are listed and settled
+// one a thread, so a workgroup goes through the chain once for 1,024 lanes, and
+// the scatter scans a quarter of the block sums.  The lists cost two barriers:
+// a step takes 72.3 us against 81.5 on the metropolitan lattice (1.09M lanes),
+// 43.2 against 43.5 at 437k, 35.8 against 36.2 at 194k, but 33.4 against 33.3 at
+// 124k and 33.0 against 32.0 on the 100x100 city, so the line lies at 190k.
+__global__ void __launch_bounds__(kCommitNT) k_commit_many(Dev d) {
+    __shared__ unsigned shc[cNumCounters];
+    __shared__ Scan4 wsh4[kCommitNT / 64];
+    __shared__ __align__(16) uint32_t xid[kManyBlock], xn[kManyBlock];
+    __shared__ double xtt[kManyBlock];
+    __shared__ uint16_t req[kManyBlock], clm[kManyBlock];   // listed lanes of the block
+    __shared__ int nreq, nclm;
+    __shared__ int smoved;                                // gridlock detector: an exit or a departure here
+    const int tid = threadIdx.x, l0 = blockIdx.x * kManyBlock, i4 = blockIdx.x * kCommitNT + tid;
+    const LaneTabs tb = lane_tabs(d);
+    const int4 rs = ((const int4*)tb.req_stamp)[i4], es = ((const int4*)tb.enter_stamp)[i4];
+    LanePost p[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) p[q] = tb.post[4 * i4 + q];
+    const int t = d.ctl->t_b, par = t & 1;
+    if (tid < cNumCounters) shc[tid] = 0;
+    if (tid == 0) smoved = nreq = nclm = 0;
+    ((uint4*)xid)[tid] = make_uint4(~0u, ~0u, ~0u, ~0u);
+    ((uint4*)xn)[tid] = make_uint4(0u, 0u, 0u, 0u);
+    unsigned reqs = lanes_at(rs, t), claims = lanes_at(es, t);
+    unsigned in = claims;                                 // lanes that a vehicle enters
+    if (d.imode == 1) {
+        // only departures claim lanes, and the node's crossing into the lane comes first
+        const uint4 le4 = ((const uint4*)d.lane_edge)[i4];
+        const uint32_t le[4] = {le4.x, le4.y, le4.z, le4.w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (le[q] != ~0u && crossing_into(d, tb, (int)(le[q] & kLaneEdgeMask), 4 * i4 + q)) {
+                if (!((claims >> q) & 1u)) tb.enter_stamp[4 * i4 + q] = t;   // the scatter takes the crossing's record
+                claims &= ~(1u << q);
+                in |= 1u << q;
+            }
+    }
+    __syncthreads();
+    if (reqs) {
+        int k = atomicAdd(&nreq, __popc(reqs));
+        for (; reqs; reqs &= reqs - 1) req[k++] = (uint16_t)(4 * tid + __builtin_ctz(reqs));
+    }
+    if (claims) {
+        int k = atomicAdd(&nclm, __popc(claims));
+        for (; claims; claims &= claims - 1) clm[k++] = (uint16_t)(4 * tid + __builtin_ctz(claims));
+    }
+    __syncthreads();
+    const Exits ex{xid, xtt, xn};
+    CounterAcc acc;
+    acc.zero();
+    const int nr = nreq, nc = nclm;
+    for (int i = tid; i < nr; i += kCommitNT) {
+        const int li = req[i];
+        const uint32_t le = d.lane_edge[l0 + li];
+        commit_request(d, tb, d.s[par], l0 + li, (int)(le & kLaneEdgeMask), (int)(le >> kLaneEdgeBits), li, t, acc, ex,
+                       &smoved);
+    }
+    // the claims from the last wavefront on, which has the fewest requests
+    for (int i = kCommitNT - 1 - tid; i < nc; i += kCommitNT) {
+        const int li = clm[i];
+        const uint32_t le = d.lane_edge[l0 + li];
+        commit_departure(d, tb, l0 + li, (int)(le & kLaneEdgeMask), (int)(le >> kLaneEdgeBits), t, acc, &smoved);
+    }
+    __syncthreads();
+    const uint4 out = ((const uint4*)xid)[tid];
+    int4 c;
+    c.x = (p[0].stamp == t ? p[0].cnt : 0) - (out.x != ~0u) + (int)(in & 1u);
+    c.y = (p[1].stamp == t ? p[1].cnt : 0) - (out.y != ~0u) + (int)((in >> 1) & 1u);
+    c.z = (p[2].stamp == t ? p[2].cnt : 0) - (out.z != ~0u) + (int)((in >> 2) & 1u);
+    c.w = (p[3].stamp == t ? p[3].cnt : 0) - (out.w != ~0u) + (int)((in >> 3) & 1u);
+    ((int4*)tb.lane_newcnt)[i4] = c;
+    const int sum = c.x + c.y + c.z + c.w;
+    const int o = wg_exclusive_scan4<kCommitNT>(Scan4{sum, -1, -1, -1}, wsh4).s;
+    ((int4*)d.lane_off)[i4] = make_int4(o, o + c.x, o + c.x + c.y, o + c.x + c.y + c.z);
+    if (tid == kCommitNT - 1) d.blk_sum[blockIdx.x] = o + sum;
+    for (int i = tid; i < nr; i += kCommitNT) {
+        const int li = req[i];
+        if (xid[li] == ~0u) continue;
+        const uint32_t le = d.lane_edge[l0 + li];
+        commit_travel_time<true>(d, (int)(le & kLaneEdgeMask), (int)(le >> kLaneEdgeBits), li, ex);
+    }
     flush_commit_counters(d, acc, shc);
     publish_moved(d, &smoved, t);
 }
@@ -1900,14 +2007,14 @@ __device__ inline void put_record(const Dev& d, const LaneTabs& tb, const Slots&
     }
 }
 
-// The record in slot k (none: -1), and lane i (none: -1), which takes the
-// record that entered it if it was claimed this step.  Each round of loads of
-// the two is issued together: the record with its lane and the lane's claim
-// stamp; then the tables of the record's lane and the entry of a claimed lane.
+// The record in slot k (none: -1), and the record that entered lane claim()
+// (none: -1).  Each round of loads of the two is issued together: the record
+// with its lane and the stamps that claim() reads; then the tables of the
+// record's lane and the entry of a claimed lane.
 // off(lane): where that lane's offset counts from.
-template <class Off>
-__device__ inline void scatter_item(const Dev& d, const LaneTabs& tb, const Slots& A, const Slots& B, int k, int i,
-                                    int nnew, int t, const float* slen, Off off) {
+template <class Claim, class Off>
+__device__ inline void scatter_item(const Dev& d, const LaneTabs& tb, const Slots& A, const Slots& B, int k,
+                                    Claim claim, int nnew, int t, const float* slen, Off off) {
     const bool hv = k >= 0;
     float x = 0.0f, v = 0.0f;
     uint32_t vid = 0, meta = 0;
@@ -1921,8 +2028,9 @@ __device__ inline void scatter_item(const Dev& d, const LaneTabs& tb, const Slot
         nxt = A.nxt[k];
         gl = A.gl[k];
     }
+    const int i = claim();
+    const bool claimed = i >= 0;
     const int g0 = gl - tb.lane0, i0 = i - tb.lane0;
-    const bool claimed = i >= 0 && tb.enter_stamp[i0] == t;
     LanePost lp{};
     int ex = 0, ncnt = 0, loff = 0;
     bool entered = false;
@@ -1984,11 +2092,23 @@ __device__ inline void scatter_items(const Dev& d, int* soff, Scan4* wsh4, int* 
     }
     const Slots A = d.s[par], B = d.s[par ^ 1];
     const LaneTabs tb = lane_tabs(d);
-    // item k is the record in slot k (k < nold) and lane k (k < nl)
-    const int nit = max(nold, nl);
+    // item k is the record in slot k (k < nold) and the lanes 4k to 4k + 3 (whose claim stamps are one load)
+    const auto off = [&](int lane) { return boff[lane >> d.lane_shift]; };
+    const int nit = max(nold, nl / 4);
     for (int k = blockIdx.x * kNT + threadIdx.x; k < nit; k += gridDim.x * kNT) {
-        scatter_item(d, tb, A, B, k < nold ? k : -1, k < nl ? k : -1, nnew, t, slen,
-                     [&](int lane) { return boff[lane / kLaneBlock]; });
+        unsigned claims = 0;
+        const auto next = [&] {
+            if (claims == 0u) return -1;
+            const int i = 4 * k + __builtin_ctz(claims);
+            claims &= claims - 1;
+            return i;
+        };
+        const auto first = [&] {
+            if (4 * k < nl) claims = lanes_at(((const int4*)tb.enter_stamp)[k], t);
+            return next();
+        };
+        scatter_item(d, tb, A, B, k < nold ? k : -1, first, nnew, t, slen, off);
+        while (claims) scatter_item(d, tb, A, B, -1, next, nnew, t, slen, off);
     }
 }
 

@@ -45,3 +45,38 @@ def test_lane_counts(M, oracle_mod, lanes, mode):
     os_, oc = orc.edge_stats()
     assert np.array_equal(gc, oc) and np.array_equal(gs, os_)
     assert dict(zip(M.COUNTERS, g.state()["counters"].tolist())) == orc.counters()
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("lanes", [3, "mixed"])
+def test_many_lanes(M, oracle_mod, lanes, mode):
+    """Above 190,000 lanes a thread of the commit takes four lanes."""
+    from test_gpu_parity import compare_states
+    rows = 140
+    net = W.grid_network(rows, rows, lanes=3)
+    rng = np.random.default_rng(5)
+    if lanes == "mixed":
+        two_way = {}
+        for e, (a, b) in enumerate(zip(net.edge_from.tolist(), net.edge_to.tolist())):
+            net.lanes[e] = two_way.setdefault((min(a, b), max(a, b)), rng.integers(1, 9))
+        W.turn_lane_masks(net)
+    assert net.lanes.sum() > 190_000
+    w = W.config1(n_vehicles=6000)
+    w.net = net
+    o = rng.integers(0, net.n_nodes, 6000)
+    d = (o + rng.integers(1, 4, 6000) + rows * rng.integers(0, 3, 6000)) % net.n_nodes
+    near = rng.integers(0, 60, 3000)                 # half of the trips in one corner, which fills up
+    o[:3000], d[:3000] = near, near + 2 * rows + rng.integers(1, 9, 3000)
+    w.route_off, w.route_edges, ok = W.shortest_routes(net, o, d)
+    assert ok.all()
+    w.params.intersection_mode = mode
+    w.depart_step = (w.depart_step // 8).astype(np.int32)
+    g, orc = M.Sim(w), oracle_mod.OracleSim(w)
+    for steps in (30, 120, 150):
+        g.step(steps)
+        orc.step(steps)
+        assert compare_states(g.state(), orc.state(), f"step {orc.t}")
+    gs, gc = g.edge_stats()
+    os_, oc = orc.edge_stats()
+    assert gc.sum() > 1000 and np.array_equal(gc, oc) and np.array_equal(gs, os_)
+    assert dict(zip(M.COUNTERS, g.state()["counters"].tolist())) == orc.counters()
