@@ -83,11 +83,11 @@ __global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps)
     __shared__ unsigned shc[cNumCounters];
     __shared__ ClassParams scp[16];
     __shared__ float slen[16];
-    __shared__ uint32_t dtask[2 * NT];
+    __shared__ uint16_t dlist[2 * NT];
     __shared__ int dcount[2];
     __shared__ int smoved, sdep, stot, sreq, shead;
     const int tid = threadIdx.x, k = blockIdx.x;
-    const DrawQ dq{dtask, dcount, 2 * NT};
+    const DrawQ dq{dlist, dcount, 2 * NT};
     const SmallRange r0 = sm.range[k], r1 = sm.range[k + 1];
     const int nl = r1.lane - r0.lane;
     // the tile, where the exits of a step and its claiming queues are kept once its tiles are done; then the lanes' tables

@@ -41,7 +41,8 @@ constexpr int kTileCtrRounds = 8;        // the counters hand out tiles above th
 constexpr int kTileCtrStride = 32;       // ints between two counters: one 128-byte line each
 constexpr int kTileCtrInts = 2 * kTileGroups * kTileCtrStride;   // [step parity][group] counters
 constexpr int kTileWindowAuto = 192;     // largest window the per-step choice takes
-constexpr int kTileDrawTasks = 384;      // listed Philox blocks per tile round (more are computed in place)
+constexpr int kTileAhead = 32;           // slots past a window whose records are loaded with it
+constexpr int kTileDraws = 384;          // listed draws per tile round
 constexpr int kCommitNT = 256;           // threads per commit workgroup: one lane each, or four on
 constexpr int kManyLanes = 190000;       // networks of more lanes than this (k_commit_many)
 constexpr int kManyBlock = 4 * kCommitNT;
@@ -552,23 +553,70 @@ __device__ inline int first_edge_start(const int32_t* edge, int lo, int hi, int*
     return hi;
 }
 
-// Both ends of a tile in one pass over the slots [w0, w0 + NT): a0 = the
-// first edge start in [w0, w1) (w1 if none), a1 = the first edge start at or
-// after w1 (n if none).  Windows are at most NT / 2 slots, so the pass also
-// covers NT / 2 slots past w1; a longer edge continues with first_edge_start.
 struct TileSpan {   // a tile's slots [a0, a1) and the end of its window
     int a0, a1, w1;
 };
 
+// A vehicle's record at the start of the step, with the constants of its edge
+// and next edge (of edge 0 if there is none, f < 0).
+struct StepRecord {
+    uint32_t m, vid;
+    int e, f;
+    float x, v;
+    EdgeC ce, cf;
+};
+
+// e: its edge, loaded before
+__device__ inline StepRecord load_record(const Dev& d, const Slots& S, int s, int e) {
+    StepRecord r;
+    r.e = e;
+    r.f = S.nxt[s];
+    r.m = S.meta[s];
+    r.x = S.x[s];
+    r.v = S.v[s];
+    r.vid = S.vid[s];
+    r.ce = d.ec[r.e];
+    r.cf = d.ec[max(r.f, 0)];
+    return r;
+}
+
+// The record that a thread loads while the ends of its tile are looked for:
+// that of slot `slot` (-1: none); the slots below `end` are all loaded.
+struct AheadRecord {
+    StepRecord r;
+    int slot, end;
+};
+
+// Both ends of a tile in one pass over the slots [w0, w0 + NT): a0 = the
+// first edge start in [w0, w1) (w1 if none), a1 = the first edge start at or
+// after w1 (n if none).  Windows are at most 256 slots, so with NT = 256 the
+// pass also covers the slots past w1 of all but the longest windows; a longer
+// edge continues with first_edge_start.
+// The tile's records are loaded by the same pass, up to kTileAhead slots past
+// w1, before the ends are known: those loads and the ones of the edges'
+// constants behind them are two of the step's five dependent rounds, here in
+// the shadow of the search (15.4 -> 14.9 us on the 100x100 city, whose
+// workgroups have one tile each).  Slots outside the tile are dropped (another
+// workgroup may be rewriting them; each of their words is valid all the same).
+// wsh: 4 * (NT / 64) ints in LDS, used by halves in turn (flip), so that the
+// barrier of the next search separates this one's reads from the writes after it.
 template <int NT>
-__device__ inline void tile_bounds(const int32_t* edge, int w0, int w1, int n, int* wsh2, int& a0, int& a1) {
+__device__ inline TileSpan tile_bounds(const Dev& d, const Slots& S, int w0, int w1, int n, int* wsh, int& flip,
+                                       AheadRecord& ah) {
     constexpr int kW = NT / 64;
+    int* const wsh2 = wsh + flip * 2 * kW;
+    flip ^= 1;
+    const int32_t* edge = S.edge;
     const int s = w0 + (int)threadIdx.x;
-    const bool f = s < n && (s == 0 || edge[s] != edge[s - 1]);
-    const bool in0 = f && s < w1, in1 = f && s >= w1;
-    const unsigned long long b0 = __ballot(in0), b1 = __ballot(in1);
+    ah.end = min(min(n, w0 + NT), w1 + kTileAhead);
+    ah.slot = s < ah.end ? s : -1;
+    // (no branch around the loads: the search waits for the first two alone)
+    const int si = min(s, n - 1), e = edge[si], before = edge[max(si - 1, 0)];
+    const int sr = min(s, ah.end - 1);
+    ah.r = load_record(d, S, sr, edge[sr]);
+    const bool f = s < n && (s == 0 || e != before);
+    const unsigned long long b0 = __ballot(f && s < w1), b1 = __ballot(f && s >= w1);
     const int wave = threadIdx.x >> 6;
-    __syncthreads();
     if ((threadIdx.x & 63) == 0) {
         wsh2[wave] = b0 ? (w0 + wave * 64 + (__ffsll((long long)b0) - 1)) : INT32_MAX;
         wsh2[kW + wave] = b1 ? (w0 + wave * 64 + (__ffsll((long long)b1) - 1)) : INT32_MAX;
@@ -579,35 +627,38 @@ __device__ inline void tile_bounds(const int32_t* edge, int w0, int w1, int n, i
         m0 = min(m0, wsh2[w]);
         m1 = min(m1, wsh2[kW + w]);
     }
-    __syncthreads();
-    a0 = m0 == INT32_MAX ? w1 : m0;
-    if (m1 != INT32_MAX) a1 = m1;
-    else a1 = (w0 + NT >= n) ? n : first_edge_start<NT>(edge, w0 + NT, n, wsh2);
+    TileSpan sp;
+    sp.w1 = w1;
+    sp.a0 = m0 == INT32_MAX ? w1 : m0;
+    if (m1 != INT32_MAX) sp.a1 = m1;
+    else sp.a1 = (w0 + NT >= n) ? n : first_edge_start<NT>(edge, w0 + NT, n, wsh2);
+    return sp;
 }
 
 // ---- lane-change draws computed by the whole workgroup -------------------
-// A task is one Philox block (vehicle q of the tile, stream, block index).
-// Its 24-bit words are added into the vehicle's slot with an LDS atomic; the
-// sums are integers, so the order of the additions does not matter and the
-// result equals draw_uniform / draw_normal exactly.
+// An entry is one draw of one vehicle: its Eq. (2) uniform (one Philox block)
+// in round 0, the noise of one side (three blocks) in round 1.  A block's 24-bit
+// words are added into the vehicle's slot with an LDS atomic; the sums are
+// integers, so the order of the additions does not matter and the result equals
+// draw_uniform / draw_normal exactly.
 struct DrawQ {
-    uint32_t* task;   // [cap] q << 4 | stream << 2 | block
-    int* n;           // [2] tasks listed in each round
+    uint16_t* list;   // [cap] q | side << 15
+    int* n;           // [2] entries asked for in each round
     int cap;
 };
 
+template <int kUnroll>
 __device__ inline uint32_t philox_words(uint64_t seed, int t, uint32_t rid, int stream, int blk) {
-    const U64x4 r = philox4x64_10((uint64_t)(int64_t)t, rid, (uint64_t)stream, (uint64_t)blk, seed, 0);
+    const U64x4 r = philox4x64_10<kUnroll>((uint64_t)(int64_t)t, rid, (uint64_t)stream, (uint64_t)blk, seed, 0);
     if (stream == 1) return (uint32_t)(r.w[0] >> 40);
     return (uint32_t)((r.w[0] >> 40) + (r.w[1] >> 40) + (r.w[2] >> 40) + (r.w[3] >> 40));
 }
 
-// list one task; a full list computes it in place
-__device__ inline void draw_task(const DrawQ& dq, int round, uint32_t rid, int q, int stream, int blk, int* slot,
-                                 uint64_t seed, int t) {
+// Lists a draw; false if the list is full (the caller then marks the vehicle).
+__device__ inline bool draw_list(const DrawQ& dq, int round, int q, int side) {
     const int k = atomicAdd(&dq.n[round], 1);
-    if (k < dq.cap) dq.task[k] = ((uint32_t)q << 4) | ((uint32_t)stream << 2) | (uint32_t)blk;
-    else atomicAdd(&slot[q], (int)philox_words(seed, t, rid, stream, blk));
+    if (k < dq.cap) dq.list[k] = (uint16_t)(q | (side << 15));
+    return k < dq.cap;
 }
 
 // The counter id of a vehicle's draws: its id within its scenario (the
@@ -616,16 +667,44 @@ __device__ inline uint32_t draw_id(const Dev& d, uint32_t vid, int e) {
     return vid - (uint32_t)d.scen_voff[e / d.edge_period];
 }
 
+constexpr int kPending = 2, kDrawA = 4, kDrawB = 8;   // Phase 1 decision codes (b.pm >> 16)
+constexpr int kLateA = 16, kLateB = 32;               // a draw that is not in the list
+
+// The listed draws of a round, then, if the list was too short, those of the
+// marked vehicles of the tile (n of them).  One place for the Philox code, and
+// its rounds two at a time in a loop: with copies where a full list was met, all
+// unrolled, the tile kernel was four times its size and spilled 111 scalar
+// registers of keys and pointers (now 29), each read back by a vector
+// instruction, on a kernel whose vector units are 70 % busy on the metropolitan
+// lattice (tile kernel 30.2 -> 28.3 us there, 28.6 -> 27.0 on the dense city).
 template <int NT>
-__device__ inline void draw_run(const Dev& d, const DrawQ& dq, int round, int t, const TileBuf& b, int* u1,
+__device__ inline void draw_run(const Dev& d, const DrawQ& dq, int round, int t, const TileBuf& b, int n, int* u1,
                                 int* na, int* nb) {
-    const int nt = min(dq.n[round], dq.cap);
-    for (int i = threadIdx.x; i < nt; i += NT) {
-        const uint32_t tk = dq.task[i];
-        const int q = (int)(tk >> 4), st = (int)((tk >> 2) & 3u), blk = (int)(tk & 3u);
-        int* slot = st == 1 ? u1 : (st == 2 ? na : nb);
+    const int blocks = round == 0 ? 1 : 3;
+    const int asked = dq.n[round], nl = blocks * min(asked, dq.cap);
+    const int all = nl + (asked > dq.cap ? 2 * blocks * n : 0);
+    for (int i = threadIdx.x; i < all; i += NT) {
+        int q, side, blk;
+        if (i < nl) {
+            const int at = round == 0 ? i : i / 3;
+            blk = i - at * blocks;
+            q = dq.list[at] & 0x7FFF;
+            side = dq.list[at] >> 15;
+        } else {
+            const int j = i - nl, at = round == 0 ? j : j / 3;
+            blk = j - at * blocks;
+            q = at >> 1;
+            side = at & 1;
+            if (round == 0) {
+                if (side || !nb[q]) continue;
+                nb[q] = 0;
+            } else if (!((b.pm[q] >> 16) & (side ? kLateB : kLateA))) {
+                continue;
+            }
+        }
+        int* const slot = round == 0 ? u1 : (side ? nb : na);
         const uint32_t rid = draw_id(d, b.vid[q], (int)(b.el[q] >> 4));
-        atomicAdd(&slot[q], (int)philox_words(d.seed, t, rid, st, blk));
+        atomicAdd(&slot[q], (int)philox_words<2>(d.seed, t, rid, round == 0 ? 1 : 2 + side, blk));
     }
 }
 
@@ -637,7 +716,6 @@ __device__ inline float uniform_of_word(uint32_t w) {
 // twelve uniforms minus 6) and binary32 rounding is monotone, so the noise
 // decides only when G is within 6 m of c.
 constexpr int kGapNo = 0, kGapYes = 1, kGapDraw = 2;
-constexpr int kPending = 2, kDrawA = 4, kDrawB = 8;   // Phase 1 decision codes (b.pm >> 16)
 
 __device__ inline int gap_outcome(float G, float c) {
     if (G < c - 6.0f) return kGapNo;
@@ -646,8 +724,7 @@ __device__ inline int gap_outcome(float G, float c) {
 }
 
 __device__ inline bool gap_with_noise(float G, float c, int word_sum) {
-    const int32_t z = (int32_t)((int64_t)(uint32_t)word_sum - 6ll * 16777216ll);
-    const float g = c + (float)z * 5.9604644775390625e-08f;
+    const float g = c + normal_of_words(word_sum);
     const float need = g > 0.0f ? g : 0.0f;
     return G >= need;
 }
@@ -675,19 +752,19 @@ __device__ inline void finish_pending(const TileBuf& b, int q, int dir, const fl
 
 // ---- Phases 1-2 for one tile ----------------------------------------------
 // kSpread: the per-driver limits may be on (a kernel of its own, so that the
-// common case carries none of their code)
-template <int NT, bool kSpread>
+// common case carries none of their code).  kAhead: the tile's records are
+// loaded already (ahead), as far as they reach.
+template <int NT, bool kSpread, bool kAhead = false>
 __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slots& S, const TileBuf& b, int a0, int n,
                                     int t, CounterAcc& acc, Scan4* wsh4, const ClassParams* scp, const DrawQ& dq,
-                                    int* smoved) {
+                                    int* smoved, const AheadRecord& ahead = AheadRecord{}) {
     const int tid = threadIdx.x;
     const int dir = (t % 2 == 0) ? -1 : 1;
 
     // Phase 1 keeps its scratch in arrays that the scans fill later.  Few
     // vehicles need a Philox draw, and a block costs thousands of cycles, so
     // a wavefront in which one lane draws would make the other 63 wait.
-    // Instead the draws are listed as tasks and computed by the whole
-    // workgroup at once, in two rounds: the uniforms of Eq. (2), listed while
+    // Instead the draws are listed and computed by the whole workgroup at once, in two rounds: the uniforms of Eq. (2), listed while
     // S_t is loaded, then the noise of Eqs. (3)-(4), whose need depends on the
     // mandatory flag.
     int* const u1 = b.pm;                         // Eq. (2) uniform words (read before Phase 1 writes pm)
@@ -699,24 +776,20 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
     float* const cb = (float*)b.inv;
 
     // load S_t (coalesced) and list the Eq. (2) draws
-    for (int q = tid; q < n; q += NT) {
-        const int s = a0 + q;
-        const uint32_t m = S.meta[s];
-        const int e = S.edge[s], f = S.nxt[s];
-        const float x = S.x[s];
+    const auto put = [&](int q, const StepRecord& r) {
+        const uint32_t m = r.m;
+        const int e = r.e, f = r.f;
+        const float x = r.x, L = r.ce.L;
         b.x[q] = x;
-        b.v[q] = S.v[s];
-        b.vid[q] = S.vid[s];
+        b.v[q] = r.v;
+        b.vid[q] = r.vid;
         b.el[q] = ((uint32_t)e << 4) | (uint32_t)m_lane(m);
         b.meta[q] = m;
         b.nxt[q] = f;
-        const EdgeC ce = d.ec[e];
-        const EdgeC cf = f >= 0 ? d.ec[f] : EdgeC{0.0f, 0.0f, 0, 0};
-        const float L = ce.L;
         b.L[q] = L;
-        b.lbe[q] = (uint32_t)ce.lane_base | ((uint32_t)ce.lanes << kLaneBaseBits);
-        b.lbf[q] = (uint32_t)cf.lane_base | ((uint32_t)cf.lanes << kLaneBaseBits);
-        b.lim[q] = ce.lim;
+        b.lbe[q] = (uint32_t)r.ce.lane_base | ((uint32_t)r.ce.lanes << kLaneBaseBits);
+        b.lbf[q] = f < 0 ? 0u : (uint32_t)r.cf.lane_base | ((uint32_t)r.cf.lanes << kLaneBaseBits);
+        b.lim[q] = r.ce.lim;
         u1[q] = 0;
         na[q] = 0;
         nb[q] = 0;
@@ -724,10 +797,17 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
             const float dd = L - x;
             if (dd > kX0) {
                 const float dm = dd - kX0;
-                if (dm * dm < kZCut) draw_task(dq, 0, draw_id(d, b.vid[q], e), q, 1, 0, u1, d.seed, t);
+                if (dm * dm < kZCut && !draw_list(dq, 0, q, 0)) nb[q] = 1;
             }
         }
+    };
+    int q0 = tid;
+    if (kAhead) {
+        const int q = ahead.slot - a0;                          // this thread's record, loaded before
+        if (ahead.slot >= 0 && q >= 0 && q < n) put(q, ahead.r);
+        q0 = max(0, ahead.end - a0) + tid;
     }
+    for (int q = q0; q < n; q += NT) put(q, load_record(d, S, a0 + q, S.edge[a0 + q]));
     __syncthreads();
 
     // ---- runs of S_t (tile order: edge, lane, then x and id descending)
@@ -761,11 +841,14 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
         if (q == 0 || b.el[q - 1] != b.el[q]) atomicOr(&b.run_st[k0], 1u << (16u + (b.el[q] & 15u)));
         b.rk[q] = k | (k0 << 16);
     }
-    draw_run<NT>(d, dq, 0, t, b, u1, na, nb);
-    if (kSpread && d.v0_spread != 0.0f)   // each driver's own limit on its edge (Sec. IV)
-        for (int q = tid; q < n; q += NT) {
-            const int e = (int)(b.el[q] >> 4);
-            b.lim[q] = driver_limit(b.lim[q], d.v0_spread, d.seed, e, d.edge_period, draw_id(d, b.vid[q], e));
+    draw_run<NT>(d, dq, 0, t, b, n, u1, na, nb);
+    // each driver's own limit on its edge (Sec. IV): the words of its draw, a
+    // block a thread (three blocks one after another on the vehicle's own thread
+    // would leave three threads in four idle on the tiles of a short step)
+    if (kSpread && d.v0_spread != 0.0f)
+        for (int i = tid; i < 3 * n; i += NT) {
+            const int q = i / 3, e = (int)(b.el[q] >> 4);
+            atomicAdd(&na[q], (int)philox_words<10>(d.seed, e % d.edge_period, draw_id(d, b.vid[q], e), 4, i - 3 * q));
         }
     __syncthreads();
 
@@ -773,6 +856,10 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
     for (int q = tid; q < n; q += NT) {
         uint32_t m = b.meta[q];
         int moved = 0, pos = 0;
+        if (kSpread && d.v0_spread != 0.0f) {
+            b.lim[q] = driver_limit_of(b.lim[q], d.v0_spread, normal_of_words(na[q]));
+            na[q] = 0;
+        }
         if (!m_held(m)) {
             const uint32_t el = b.el[q];
             const int l = (int)(el & 15u);
@@ -858,11 +945,8 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
                             if (allowed_lp) m &= ~((1u << 4) | (127u << 8));   // mand = 0, ww = 0
                         } else {                                 // decided by the noise
                             moved = kPending | (ra == kGapDraw ? kDrawA : 0) | (rb == kGapDraw ? kDrawB : 0);
-                            const uint32_t rid = draw_id(d, b.vid[q], (int)(el >> 4));
-                            for (int k = 0; k < 3; ++k) {
-                                if (ra == kGapDraw) draw_task(dq, 1, rid, q, 2, k, na, d.seed, t);
-                                if (rb == kGapDraw) draw_task(dq, 1, rid, q, 3, k, nb, d.seed, t);
-                            }
+                            if (ra == kGapDraw && !draw_list(dq, 1, q, 0)) moved |= kLateA;
+                            if (rb == kGapDraw && !draw_list(dq, 1, q, 1)) moved |= kLateB;
                         }
                     }
                 }
@@ -874,7 +958,7 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
         b.meta[q] = m;
     }
     __syncthreads();
-    draw_run<NT>(d, dq, 1, t, b, u1, na, nb);
+    draw_run<NT>(d, dq, 1, t, b, n, u1, na, nb);
     __syncthreads();
     if (tid < 2) dq.n[tid] = 0;   // lists of the next tile (several barriers away)
 
@@ -1167,9 +1251,10 @@ __device__ inline void mark_big_lanes(const Dev& d, const int32_t* edge, int a0,
 __device__ inline int tile_window(const Dev& d, int n) {
     int W = d.tile_window;
     if (W == 0) {
-        const long long tgt = gridDim.x;   // the tile workgroups (persistent: all resident)
-        const long long R = max(1LL, ((long long)n + kTileWindowAuto * tgt - 1) / (kTileWindowAuto * tgt));
-        const int w = (int)(((long long)n + R * tgt - 1) / (R * tgt));
+        // (32 bits: a 64-bit division of uniform values is some 200 scalar instructions)
+        const unsigned un = (unsigned)n, tgt = gridDim.x;   // the tile workgroups (persistent: all resident)
+        const unsigned R = max(1u, (un + kTileWindowAuto * tgt - 1u) / (kTileWindowAuto * tgt));
+        const int w = (int)((un + R * tgt - 1u) / (R * tgt));
         W = max(kTileWindowMin, (w + 15) / 16 * 16);
     }
     return W;
@@ -1181,14 +1266,15 @@ template <bool kSpread>
 __device__ inline void tile_step(const Dev& d) {
     __shared__ __align__(16) char lds[kTileCapLds * kTileBytesPerVeh + 64];
     __shared__ Scan4 wsh4[kTileNT / 64];
-    __shared__ int wsh[2 * (kTileNT / 64)];
+    __shared__ int wsh[4 * (kTileNT / 64)];
+    __shared__ int sbig;                        // index of a tile listed as big
     __shared__ unsigned shc[cNumCounters];
     __shared__ ClassParams scp[16];
-    __shared__ uint32_t dtask[kTileDrawTasks];
+    __shared__ uint16_t dlist[kTileDraws];
     __shared__ int dcount[2];
     __shared__ int smoved;                      // gridlock detector: a vehicle of this workgroup moved
     __shared__ int snext;                       // the workgroup's next tile
-    const DrawQ dq{dtask, dcount, kTileDrawTasks};
+    const DrawQ dq{dlist, dcount, kTileDraws};
     if (threadIdx.x < cNumCounters) shc[threadIdx.x] = 0;
     if (threadIdx.x < 2) dcount[threadIdx.x] = 0;
     if (threadIdx.x == 0) smoved = 0;
@@ -1215,14 +1301,14 @@ __device__ inline void tile_step(const Dev& d) {
     // a tile is the set of edges whose first slot lies in one window
     const int W = tile_window(d, n);
     const int ntile = (n + W - 1) / W;
-    const int32_t* edge = d.s[par].edge;
+    const Slots S = d.s[par];
+    AheadRecord ah;
+    int flip = 0;
     // A tile is the set of edges whose first slot lies in one window: its
     // bounds (run_tile), then its phases or its listing as a big tile (do_tile)
     auto run_tile = [&](int k) {
         const int w0 = k * W, w1 = min(n, w0 + W);
-        int a0, a1;
-        tile_bounds<kTileNT>(edge, w0, w1, n, wsh, a0, a1);
-        return TileSpan{a0, a1, w1};
+        return tile_bounds<kTileNT>(d, S, w0, w1, n, wsh, flip, ah);
     };
     auto do_tile = [&](const TileSpan& sp) {
         const int a0 = sp.a0, a1 = sp.a1;
@@ -1233,18 +1319,18 @@ __device__ inline void tile_step(const Dev& d) {
             return;
         }
         if (cnt <= kTileCapLds) {
-            process_tile<kTileNT, kSpread>(d, lane_tabs(d), d.s[par], carve(lds, kTileCapLds), a0, cnt, t, acc, wsh4, scp,
-                                           dq, &smoved);
+            process_tile<kTileNT, kSpread, true>(d, lane_tabs(d), S, carve(lds, kTileCapLds), a0, cnt, t, acc, wsh4, scp,
+                                                 dq, &smoved, ah);
         } else {
             if (threadIdx.x == 0) {
                 const int q = atomicAdd(&d.ctl->n_big[par], 1);
                 d.big_list[2 * q] = a0;
                 d.big_list[2 * q + 1] = a1;
-                wsh[0] = q;
+                sbig = q;
             }
             __syncthreads();
-            mark_big_lanes<kTileNT>(d, edge, a0, a1, t, wsh[0]);
-            __syncthreads();                        // wsh is reused by the next tile
+            mark_big_lanes<kTileNT>(d, S.edge, a0, a1, t, sbig);
+            __syncthreads();                        // sbig is reused by the next tile
         }
     };
     // A workgroup's first tile is its index.  With few rounds per step each
@@ -1255,25 +1341,22 @@ __device__ inline void tile_step(const Dev& d) {
     // workgroup whose tiles ran short takes the next, and each counter sees
     // one workgroup in eight.  The counter is read before the bounds probe,
     // whose loads its round trip overlaps, and the index is shared after the
-    // probe (which begins with a barrier, so every thread has read the
-    // previous one).
-    const int G = (int)gridDim.x;
-    if (ntile > kTileCtrRounds * G) {
-        const int ng = min(kTileGroups, G);
-        const int grp = (int)blockIdx.x % ng;
-        int* const ctr = tile_counters(d) + (par * kTileGroups + grp) * kTileCtrStride;
-        int k = blockIdx.x;
-        while (k < ntile) {
-            int nk = 0;
-            if (threadIdx.x == 0) nk = G + grp + ng * atomicAdd(ctr, 1);
-            const TileSpan sp = run_tile(k);
-            if (threadIdx.x == 0) snext = nk;
-            do_tile(sp);
+    // probe (which has a barrier in it, so every thread has read the previous
+    // one).  One loop for both, so the tile's phases are in the kernel once.
+    const int G = (int)gridDim.x, ng = min(kTileGroups, G), grp = (int)blockIdx.x % ng;
+    const bool handed = ntile > kTileCtrRounds * G;
+    int* const ctr = tile_counters(d) + (par * kTileGroups + grp) * kTileCtrStride;
+    for (int k = blockIdx.x; k < ntile;) {
+        int nk = k + G;
+        if (handed && threadIdx.x == 0) nk = G + grp + ng * atomicAdd(ctr, 1);
+        const TileSpan sp = run_tile(k);
+        if (handed && threadIdx.x == 0) snext = nk;
+        do_tile(sp);
+        k = nk;
+        if (handed) {
             __syncthreads();                        // snext written
             k = __builtin_amdgcn_readfirstlane(snext);
         }
-    } else {
-        for (int k = blockIdx.x; k < ntile; k += G) do_tile(run_tile(k));
     }
     flush_counters_lds(d, acc, shc);
     publish_moved(d, &smoved, t);
@@ -1341,10 +1424,10 @@ __device__ __forceinline__ void big_tiles(const Dev& d, int t, int par, int nbig
     __shared__ int wsh[kBigNT / 64];
     __shared__ unsigned shc[cNumCounters];
     __shared__ ClassParams scp[16];
-    __shared__ uint32_t dtask[2 * kBigNT];
+    __shared__ uint16_t dlist[2 * kBigNT];
     __shared__ int dcount[2];
     __shared__ int smoved;                      // gridlock detector: a vehicle of this workgroup moved
-    const DrawQ dq{dtask, dcount, 2 * kBigNT};
+    const DrawQ dq{dlist, dcount, 2 * kBigNT};
     if (threadIdx.x < cNumCounters) shc[threadIdx.x] = 0;
     if (threadIdx.x < 2) dcount[threadIdx.x] = 0;
     if (threadIdx.x == 0) smoved = 0;
