@@ -277,7 +277,7 @@ void launch_step(sim_handle* h, hipStream_t s, hipEvent_t* ev = nullptr) {
         hipLaunchKernelGGL(k_big_admit, dim3(h->g_big), dim3(kBigNT), 0, s, d);
         hipLaunchKernelGGL(commit, dim3(h->n_blk), dim3(kCommitNT), 0, s, d);
         if (lds_scan) {
-            hipLaunchKernelGGL(k_scatter<true>, dim3(h->g_scatter), b, h->scatter_lds, s, d);
+            hipLaunchKernelGGL(k_scatter<true>, dim3(h->g_scatter + 1), b, h->scatter_lds, s, d);
         } else {
             hipLaunchKernelGGL(k_blkscan, dim3(1), dim3(kBigNT), 0, s, d);
             hipLaunchKernelGGL(k_scatter<false>, dim3(h->g_scatter), b, 0, s, d);
@@ -289,7 +289,7 @@ void launch_step(sim_handle* h, hipStream_t s, hipEvent_t* ev = nullptr) {
     hipExtLaunchKernelGGL(k_big_admit, dim3(h->g_big), dim3(kBigNT), 0, s, ev[2], ev[3], 0, d);
     if (lds_scan) {
         hipExtLaunchKernelGGL(commit, dim3(h->n_blk), dim3(kCommitNT), 0, s, ev[4], ev[5], 0, d);
-        hipExtLaunchKernelGGL(k_scatter<true>, dim3(h->g_scatter), b, h->scatter_lds, s, ev[6], ev[7], 0, d);
+        hipExtLaunchKernelGGL(k_scatter<true>, dim3(h->g_scatter + 1), b, h->scatter_lds, s, ev[6], ev[7], 0, d);
     } else {   // the block scan is counted with commit
         hipExtLaunchKernelGGL(commit, dim3(h->n_blk), dim3(kCommitNT), 0, s, ev[4], nullptr, 0, d);
         hipExtLaunchKernelGGL(k_blkscan, dim3(1), dim3(kBigNT), 0, s, nullptr, ev[5], 0, d);

@@ -216,11 +216,12 @@ __global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps)
             __syncthreads();
             nnew = stot;
         }
-        for (int i = tid; i < max(n, nl); i += NT)
-            scatter_item(
-                d, tb, S, B, i < n ? i : -1,
-                [&] { return i < nl && tb.enter_stamp[i] == t ? r0.lane + i : -1; }, nnew, t, slen,
-                [](int) { return 0; });
+        for (int i = tid; i < max(n, nl); i += NT) {
+            ScatterItem r;
+            scatter_load_record(S, i < n ? i : -1, r);
+            scatter_load_tables(d, tb, i < nl && tb.enter_stamp[i] == t ? r0.lane + i : -1, r);
+            scatter_store(d, tb, B, r, nnew, t, slen, [](int) { return 0; });
+        }
         if (d.imode == 1)
             for (int i = tid; i < sm.nodes; i += NT) tb.win_node[i] = ~0ull;
         if (tid == 0) {

@@ -2008,30 +2008,48 @@ __global__ void __launch_bounds__(kCommitNT) k_commit_many(Dev d) {
 // thread's contiguous chunk straight from memory would wait for one load
 // after another.
 template <int NT>
+__device__ inline void stage_block_sums(const int* blk_sum, int m, int* stage) {
+    // eight of a thread in flight before the first use, none in a branch (a
+    // loop over what is left of eight would wait for each load)
+    for (int i0 = (int)threadIdx.x; i0 < m; i0 += 8 * NT) {
+        int v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = blk_sum[min(i0 + u * NT, m - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (i0 + u * NT < m) stage[i0 + u * NT] = v[u];
+    }
+}
+
+// The staged sums (a barrier before) in place: offsets from `from`; returns the
+// end, in *tot too.  A barrier follows the last write.
+template <int NT>
+__device__ inline int scan_staged_sums(int m, int* stage, int from, Scan4* wsh4, int* tot) {
+    const int chunk = (m + NT - 1) / NT;
+    const int lo = min(m, (int)threadIdx.x * chunk), hi = min(m, lo + chunk);
+    int loc = 0;
+    for (int i = lo; i < hi; ++i) loc += stage[i];
+    int o = from + wg_exclusive_scan4<NT>(Scan4{loc, -1, -1, -1}, wsh4).s;
+    for (int i = lo; i < hi; ++i) {
+        const int v = stage[i];
+        stage[i] = o;
+        o += v;
+    }
+    if (hi == m && lo < hi) *tot = o;
+    __syncthreads();
+    return *tot;
+}
+
+template <int NT>
 __device__ inline int scan_block_sums_staged(const int* blk_sum, int nb, int* off, int* stage, int cap,
                                              Scan4* wsh4, int* tot) {
     int carry = 0;
     for (int r0 = 0; r0 < nb; r0 += cap) {
         const int m = min(cap, nb - r0);
-        // coalesced loads, every one of a thread in flight before the first use
-#pragma unroll 8
-        for (int i = (int)threadIdx.x; i < m; i += NT) stage[i] = blk_sum[r0 + i];
+        stage_block_sums<NT>(blk_sum + r0, m, stage);
         __syncthreads();
-        const int chunk = (m + NT - 1) / NT;
-        const int lo = min(m, (int)threadIdx.x * chunk), hi = min(m, lo + chunk);
-        int loc = 0;
-        for (int i = lo; i < hi; ++i) loc += stage[i];
-        const Scan4 r = wg_exclusive_scan4<NT>(Scan4{loc, -1, -1, -1}, wsh4);
-        int o = carry + r.s;
-        for (int i = lo; i < hi; ++i) {
-            const int v = stage[i];
-            stage[i] = o;
-            o += v;
-        }
-        if (hi == m && lo < hi) *tot = o;
-        __syncthreads();
+        carry = scan_staged_sums<NT>(m, stage, carry, wsh4, tot);
         for (int i = (int)threadIdx.x; i < m; i += NT) off[r0 + i] = stage[i];
-        carry = *tot;
         __syncthreads();                            // stage and *tot are reused by the next round
     }
     return carry;
@@ -2090,61 +2108,68 @@ __device__ inline void put_record(const Dev& d, const LaneTabs& tb, const Slots&
     }
 }
 
-// The record in slot k (none: -1), and the record that entered lane claim()
-// (none: -1).  Each round of loads of the two is issued together: the record
-// with its lane and the stamps that claim() reads; then the tables of the
-// record's lane and the entry of a claimed lane.
+// The record in slot k and the record that entered lane i (k, i: none -1), with
+// the tables that give their places in the next layout.  Loaded in two rounds:
+// the record with its lane (and whatever stamps tell the caller its i); then the
+// tables of the record's lane and the entry of a claimed lane.
+struct ScatterItem {
+    int k, i;
+    float x, v;
+    uint32_t vid, meta;
+    int edge, nxt, gl;
+    LanePost lp;
+    int exit_stamp, enter_stamp, ncnt, loff;
+    EntryRec en;
+    int encnt, enoff;
+};
+
+// (Without a branch, so that nothing waits for them before they are used: with
+// none, slot 0 and the tables of the first lane.)
+__device__ inline void scatter_load_record(const Slots& A, int k, ScatterItem& r) {
+    const int s = max(k, 0);
+    r.k = k;
+    r.gl = A.gl[s];
+    r.meta = A.meta[s];
+    r.edge = A.edge[s];
+    r.x = A.x[s];
+    r.v = A.v[s];
+    r.vid = A.vid[s];
+    r.nxt = A.nxt[s];
+}
+
+__device__ inline void scatter_load_tables(const Dev& d, const LaneTabs& tb, int i, ScatterItem& r) {
+    const int g0 = r.k >= 0 ? r.gl - tb.lane0 : 0;
+    r.i = i;
+    r.lp = tb.post[g0];
+    r.exit_stamp = tb.exit_stamp[g0];
+    r.ncnt = tb.lane_newcnt[g0];
+    r.enter_stamp = tb.enter_stamp[g0];
+    r.loff = tb.lane_off[g0];
+    if (i >= 0) {
+        r.en = d.ent[i];
+        r.encnt = tb.lane_newcnt[i - tb.lane0];
+        r.enoff = tb.lane_off[i - tb.lane0];
+    }
+}
+
 // off(lane): where that lane's offset counts from.
-template <class Claim, class Off>
-__device__ inline void scatter_item(const Dev& d, const LaneTabs& tb, const Slots& A, const Slots& B, int k,
-                                    Claim claim, int nnew, int t, const float* slen, Off off) {
-    const bool hv = k >= 0;
-    float x = 0.0f, v = 0.0f;
-    uint32_t vid = 0, meta = 0;
-    int edge = 0, nxt = 0, gl = 0;
-    if (hv) {
-        meta = A.meta[k];
-        edge = A.edge[k];
-        x = A.x[k];
-        v = A.v[k];
-        vid = A.vid[k];
-        nxt = A.nxt[k];
-        gl = A.gl[k];
-    }
-    const int i = claim();
-    const bool claimed = i >= 0;
-    const int g0 = gl - tb.lane0, i0 = i - tb.lane0;
-    LanePost lp{};
-    int ex = 0, ncnt = 0, loff = 0;
-    bool entered = false;
-    if (hv) {
-        lp = tb.post[g0];
-        ex = tb.exit_stamp[g0] == t ? 1 : 0;
-        ncnt = tb.lane_newcnt[g0];
-        entered = tb.enter_stamp[g0] == t;
-        loff = tb.lane_off[g0];
-    }
-    EntryRec en{};
-    int encnt = 0, enoff = 0;
-    if (claimed) {
-        en = d.ent[i];
-        encnt = tb.lane_newcnt[i0];
-        enoff = tb.lane_off[i0];
-    }
-    if (hv) {
-        const int r = k - lp.start;
-        if (lp.stamp != t) {
+template <class Off>
+__device__ inline void scatter_store(const Dev& d, const LaneTabs& tb, const Slots& B, const ScatterItem& r, int nnew,
+                                     int t, const float* slen, Off off) {
+    if (r.k >= 0) {
+        const int rank = r.k - r.lp.start, ex = r.exit_stamp == t ? 1 : 0;
+        if (r.lp.stamp != t) {
             atomicOr(&d.ctl->err, kErrScatter);
-        } else if (!(ex && r == 0)) {         // unless the lane's front left the edge
-            const int nr = r - ex;
-            put_record(d, tb, B, off(gl) + loff + nr, nnew, x, v, vid, edge, meta, nxt, (nr == ncnt - 1) && !entered,
-                       gl, t, slen);
+        } else if (!(ex && rank == 0)) {      // unless the lane's front left the edge
+            const int nr = rank - ex;
+            put_record(d, tb, B, off(r.gl) + r.loff + nr, nnew, r.x, r.v, r.vid, r.edge, r.meta, r.nxt,
+                       (nr == r.ncnt - 1) && r.enter_stamp != t, r.gl, t, slen);
         }
     }
-    if (claimed) {                            // the entry is the lane's new rear
-        put_record(d, tb, B, off(i) + enoff + encnt - 1, nnew, en.x, en.v, en.vid, en.edge, en.meta, en.nxt, true,
-                   i, t, slen);
-        tb.win[i0] = ~0ull;                   // lane free for the next step's claims
+    if (r.i >= 0) {                           // the entry is the lane's new rear
+        put_record(d, tb, B, off(r.i) + r.enoff + r.encnt - 1, nnew, r.en.x, r.en.v, r.en.vid, r.en.edge, r.en.meta,
+                   r.en.nxt, true, r.i, t, slen);
+        tb.win[r.i - tb.lane0] = ~0ull;       // lane free for the next step's claims
     }
 }
 
@@ -2155,43 +2180,68 @@ __device__ inline void scatter_item(const Dev& d, const LaneTabs& tb, const Slot
 // k_blkscan has done both.
 template <bool kLds>
 __device__ inline void scatter_items(const Dev& d, int* soff, Scan4* wsh4, int* totp, float* slen) {
-    if (threadIdx.x < 16) slen[threadIdx.x] = d.cp[threadIdx.x].len;
+    const float len = d.cp[threadIdx.x & 15].len;   // into slen below, behind the other first loads
     const StepHead sh = step_head(d.ctl);
     const int t = sh.t_b, par = t & 1;
     const int nold = par ? sh.n1 : sh.n0;
     const int nl = d.n_lanes_total;
+    const Slots A = d.s[par], B = d.s[par ^ 1];
+    const LaneTabs tb = lane_tabs(d);
+    // item k is the record in slot k (k < nold) and the lanes 4k to 4k + 3 (whose claim stamps are one load)
+    const int nit = max(nold, nl / 4);
+    unsigned claims = 0;
+    const auto next = [&](int k) {
+        if (claims == 0u) return -1;
+        const int i = 4 * k + __builtin_ctz(claims);
+        claims &= claims - 1;
+        return i;
+    };
+    const auto stamps = [&](int k) { return 4 * k < nl ? ((const int4*)tb.enter_stamp)[k] : make_int4(-1, -1, -1, -1); };
+    int k = blockIdx.x * kNT + threadIdx.x;
+    ScatterItem r;
     const int* boff;
     int nnew;
     if (kLds) {
         // every block sum loaded at once into LDS and scanned there (one round:
-        // at most kScanLdsMax blocks take this path)
-        nnew = scan_block_sums_staged<kNT>(d.blk_sum, d.n_blk, soff, soff, kScanLdsMax, wsh4, totp);
+        // at most kScanLdsMax blocks take this path).  The loads of the first
+        // item, which need no offset, go out with the sums and during the scan
+        // (after it, they are two more of the kernel's four rounds: 5.6 against
+        // 4.8 us a step on the 100x100 city, 18.7 against 16.5 on the
+        // metropolitan lattice, of which 11 are its bytes).
+        scatter_load_record(A, k < nold ? k : -1, r);
+        const int4 st = stamps(k);
+        stage_block_sums<kNT>(d.blk_sum, d.n_blk, soff);
+        claims = lanes_at(st, t);
+        scatter_load_tables(d, tb, next(k), r);
+        if (threadIdx.x < 16) slen[threadIdx.x] = len;
+        __syncthreads();
+        nnew = scan_staged_sums<kNT>(d.n_blk, soff, 0, wsh4, totp);
         boff = soff;
-        if (blockIdx.x == 0 && threadIdx.x < 64) finish_step(d, t, par, nnew);
+        // the last workgroup has no items (it would be done later than the others)
+        if (blockIdx.x == gridDim.x - 1) {
+            if (threadIdx.x < 64) finish_step(d, t, par, nnew);
+            return;
+        }
     } else {
         boff = d.blk_off;
         nnew = d.ctl->n_act[par ^ 1];
-        __syncthreads();                          // slen
+        if (threadIdx.x < 16) slen[threadIdx.x] = len;
+        __syncthreads();
     }
-    const Slots A = d.s[par], B = d.s[par ^ 1];
-    const LaneTabs tb = lane_tabs(d);
-    // item k is the record in slot k (k < nold) and the lanes 4k to 4k + 3 (whose claim stamps are one load)
     const auto off = [&](int lane) { return boff[lane >> d.lane_shift]; };
-    const int nit = max(nold, nl / 4);
-    for (int k = blockIdx.x * kNT + threadIdx.x; k < nit; k += gridDim.x * kNT) {
-        unsigned claims = 0;
-        const auto next = [&] {
-            if (claims == 0u) return -1;
-            const int i = 4 * k + __builtin_ctz(claims);
-            claims &= claims - 1;
-            return i;
-        };
-        const auto first = [&] {
-            if (4 * k < nl) claims = lanes_at(((const int4*)tb.enter_stamp)[k], t);
-            return next();
-        };
-        scatter_item(d, tb, A, B, k < nold ? k : -1, first, nnew, t, slen, off);
-        while (claims) scatter_item(d, tb, A, B, -1, next, nnew, t, slen, off);
+    const int stride = (gridDim.x - (kLds ? 1 : 0)) * kNT;
+    for (bool loaded = kLds; k < nit; k += stride, loaded = false) {
+        if (!loaded) {
+            scatter_load_record(A, k < nold ? k : -1, r);
+            claims = lanes_at(stamps(k), t);
+            scatter_load_tables(d, tb, next(k), r);
+        }
+        scatter_store(d, tb, B, r, nnew, t, slen, off);
+        while (claims) {
+            r.k = -1;
+            scatter_load_tables(d, tb, next(k), r);
+            scatter_store(d, tb, B, r, nnew, t, slen, off);
+        }
     }
 }
 
