@@ -1562,8 +1562,9 @@ __device__ inline bool admit_head(const Dev& d, const LaneTabs& tb, int q, int2 
 // eligible if it does not overlap the target lane's rear after the move; a
 // due queue head if the lane's rear leaves it s0 at x = 0.  Each thread takes
 // its items eight at a time and loads their stamps (queue heads) together, so
-// that the loads overlap: the 1.09M lanes of the metropolitan lattice are one
-// round (7.3 us; in two rounds of four 8.4).  Items a whole stride apart: of
+// that the loads overlap, none of them in a branch (each would be waited for):
+// the 1.09M lanes of the metropolitan lattice are one round (6.4 us; eight loads
+// one after another 7.5, two rounds of four 8.4).  Items a whole stride apart: of
 // eight neighbouring lanes several may be due, one after another.
 // The eight stamps are read into one bit mask of due items, so that no
 // per-thread array is indexed by a runtime value (which would put it in
@@ -1575,11 +1576,11 @@ __device__ inline void admit_items(const Dev& d, const LaneTabs& tb, const Slots
     const int stride = nwg * NT;
     for (int i0 = l0 + wg * NT + (int)threadIdx.x; i0 < l1; i0 += kU * stride) {
         unsigned due = 0;
+        int at[kU];
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int i = i0 + u * stride;
-            if (i < l1 && tb.req_stamp[i - tb.lane0] == t) due |= 1u << u;
-        }
+        for (int u = 0; u < kU; ++u) at[u] = tb.req_stamp[min(i0 + u * stride, l1 - 1) - tb.lane0];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) due |= i0 + u * stride < l1 && at[u] == t ? 1u << u : 0u;
         while (due) {
             const int u = __builtin_ctz(due);
             due &= due - 1;
@@ -1588,11 +1589,11 @@ __device__ inline void admit_items(const Dev& d, const LaneTabs& tb, const Slots
     }
     for (int q0 = q00 + wg * NT + (int)threadIdx.x; q0 < q1; q0 += kU * stride) {
         unsigned due = 0;
+        int at[kU];
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int q = q0 + u * stride;
-            if (q < q1 && d.qhd[q].x <= t) due |= 1u << u;
-        }
+        for (int u = 0; u < kU; ++u) at[u] = d.qhd[min(q0 + u * stride, q1 - 1)].x;
+#pragma unroll
+        for (int u = 0; u < kU; ++u) due |= q0 + u * stride < q1 && at[u] <= t ? 1u << u : 0u;
         while (due) {
             const int q = q0 + __builtin_ctz(due) * stride;
             due &= due - 1;
@@ -1675,7 +1676,7 @@ __global__ void __launch_bounds__(kBigNT) k_big_admit(Dev d) {
 // what bounds it.  (One thread per edge, taking its lanes one after another, went
 // through it once per lane that any thread of the wavefront had a request on:
 // 10.9 us a step on the 100x100 city and 28.2 on the metropolitan lattice,
-// against 5.7 and 19.4.)  A lattice of 1.09M lanes is two rounds of the
+// against 5.1 and 19.0.)  A lattice of 1.09M lanes is two rounds of the
 // wavefronts that fit the GPU, and one wavefront in two has a request: there a
 // thread takes four lanes (k_commit_many, 14.3 us).
 
@@ -1806,13 +1807,14 @@ __device__ inline bool crossing_into(const Dev& d, const LaneTabs& tb, int e, in
 }
 
 // Lane gl in this step: its request, the vehicle that entered it, and its
-// count in the next layout, which is returned.
+// count in the next layout, which is returned.  p, req_stamp, enter_stamp: the
+// lane's, loaded by the caller.
 __device__ inline int commit_lane(const Dev& d, const LaneTabs& tb, const Slots& S, int gl, int e, int l, int li, int t,
-                                  CounterAcc& acc, const Exits& ex, int* smoved) {
+                                  const LanePost& p, int req_stamp, int enter_stamp, CounterAcc& acc, const Exits& ex,
+                                  int* smoved) {
     const int g0 = gl - tb.lane0;
-    const LanePost p = tb.post[g0];
-    const bool req = tb.req_stamp[g0] == t;
-    bool claimed = tb.enter_stamp[g0] == t;
+    const bool req = req_stamp == t;
+    bool claimed = enter_stamp == t;
     // the departure whose key won this lane; in case 1 only departures claim
     // lanes, and this node's crossing into the lane comes first
     const bool transfer_in = crossing_into(d, tb, e, gl);
@@ -1881,20 +1883,23 @@ __global__ void __launch_bounds__(kCommitNT) k_commit(Dev d) {
     __shared__ double xtt[kCommitNT];
     __shared__ int smoved;                                // gridlock detector: an exit or a departure here
     const int tid = threadIdx.x, gl = blockIdx.x * kCommitNT + tid;
+    const LaneTabs tb = lane_tabs(d);
+    // one round of loads, none of which waits for the step number
     const uint32_t le = d.lane_edge[gl];
+    const LanePost p = tb.post[gl];
+    const int rs = tb.req_stamp[gl], es = tb.enter_stamp[gl];
+    const int t = d.ctl->t_b, par = t & 1;
     if (tid < cNumCounters) shc[tid] = 0;
     if (tid == 0) smoved = 0;
     xid[tid] = ~0u;
     xn[tid] = 0u;
-    const int t = d.ctl->t_b, par = t & 1;
     __syncthreads();
-    const LaneTabs tb = lane_tabs(d);
     const Exits ex{xid, xtt, xn};
     const int e = (int)(le & kLaneEdgeMask), l = (int)(le >> kLaneEdgeBits);
     CounterAcc acc;
     acc.zero();
     int c = 0;
-    if (le != ~0u) c = commit_lane(d, tb, d.s[par], gl, e, l, tid, t, acc, ex, &smoved);
+    if (le != ~0u) c = commit_lane(d, tb, d.s[par], gl, e, l, tid, t, p, rs, es, acc, ex, &smoved);
     const Scan4 run = wg_exclusive_scan4<kCommitNT>(Scan4{c, -1, -1, -1}, wsh4);   // a barrier in it
     d.lane_off[gl] = run.s;
     if (tid == kCommitNT - 1) d.blk_sum[blockIdx.x] = run.s + c;
