@@ -490,6 +490,43 @@ __device__ inline Scan4 wg_exclusive_scan4(Scan4 v, Scan4* wsh) {
     return scan4_op(carry, exc);
 }
 
+// Scans of flags, one element a thread: within the wavefront by counting and
+// finding bits of a ballot (a DPP scan of the same takes six dependent rounds a
+// quantity), across the wavefronts by reading every wavefront's total (tile
+// kernel 28.2 -> 26.9 us on the metropolitan lattice, 10.4 -> 9.9 on the town).
+__device__ inline int last_bit(unsigned long long m) { return 63 - __clzll((long long)m); }   // -1: none
+__device__ inline unsigned long long bits_upto(int lane) { return ~0ull >> (63 - lane); }
+__device__ inline int bits_below(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// The totals of the wavefronts before this one (s: sum; a, b: maxima) and, in
+// all, of every wavefront; wsh written by the wavefronts, a barrier before.
+template <int NT>
+__device__ inline Scan4 totals_before(const Scan4* wsh, Scan4& all) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    Scan4 r{0, -1, -1, -1};
+    all = r;
+    if (NT / 64 <= 4) {
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) {
+            const Scan4 x = wsh[w];
+            if (w < wave) r = Scan4{r.s + x.s, max(r.a, x.a), max(r.b, x.b), -1};
+            all = Scan4{all.s + x.s, max(all.a, x.a), max(all.b, x.b), -1};
+        }
+        return r;
+    }
+    // many wavefronts: scanned one a lane, as in wg_exclusive_scan4
+    const Scan4 x = wsh[min((int)(threadIdx.x & 63), NT / 64 - 1)];
+    const Scan4 upto{row_incl_sum(x.s), row_incl_max(x.a), row_incl_max(x.b), -1};
+    all = Scan4{__builtin_amdgcn_readlane(upto.s, NT / 64 - 1), __builtin_amdgcn_readlane(upto.a, NT / 64 - 1),
+                __builtin_amdgcn_readlane(upto.b, NT / 64 - 1), -1};
+    if (wave > 0)
+        r = Scan4{__builtin_amdgcn_readlane(upto.s, wave - 1), __builtin_amdgcn_readlane(upto.a, wave - 1),
+                  __builtin_amdgcn_readlane(upto.b, wave - 1), -1};
+    return r;
+}
+
 // Gridlock detector: a workgroup that saw a vehicle move stamps the step
 // into one of kMovedSlots slots (spread so that thousands of workgroups do
 // not store to one address), from an LDS flag (a register held across the
@@ -811,24 +848,31 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
     __syncthreads();
 
     // ---- runs of S_t (tile order: edge, lane, then x and id descending)
+    const int lane = tid & 63, wave = tid >> 6;
     {
-        const int chunk = (n + NT - 1) / NT;
-        const int lo = min(n, tid * chunk), hi = min(n, lo + chunk);
-        Scan4 loc{0, -1, -1, -1};                 // run starts; the last edge start
-        for (int q = lo; q < hi; ++q) {
-            const uint32_t el = b.el[q], before = q > 0 ? b.el[q - 1] : ~0u;
-            loc.s += el != before ? 1 : 0;
-            if (el >> 4 != before >> 4) loc.a = q;
+        Scan4 from{0, -1, -1, -1};                // runs and the last edge start before the round
+        for (int base = 0; base < n; base += NT) {
+            const int q = base + tid;
+            const uint32_t el = q < n ? b.el[q] : 0u, before = q < n && q > 0 ? b.el[q - 1] : ~0u;
+            const unsigned long long runs = __ballot(q < n && el != before);
+            const unsigned long long edges = __ballot(q < n && el >> 4 != before >> 4);
+            if (lane == 0) wsh4[wave] = Scan4{(int)__popcll(runs), edges ? q + last_bit(edges) : -1, -1, -1};
+            __syncthreads();
+            Scan4 all;
+            const Scan4 r = totals_before<NT>(wsh4, all);
+            if (q < n) {
+                const bool start = (runs >> lane) & 1ull;
+                const int k = from.s + r.s + bits_below(runs) + (start ? 1 : 0) - 1;
+                const unsigned long long upto = edges & bits_upto(lane);
+                const int es = upto ? q - lane + last_bit(upto) : max(from.a, r.a);
+                if (start) b.run_st[k] = (uint32_t)q;
+                b.rk[q] = (uint32_t)k | ((uint32_t)es << 16);
+                if (q == n - 1) b.run_st[k + 1] = (uint32_t)n;
+            }
+            if (base + NT >= n) break;
+            from = Scan4{from.s + all.s, max(from.a, all.a), -1, -1};
+            __syncthreads();                      // wsh4 is reused by the next round
         }
-        const Scan4 r = wg_exclusive_scan4<NT>(loc, wsh4);
-        int k = r.s - 1, es = r.a;
-        for (int q = lo; q < hi; ++q) {
-            const uint32_t el = b.el[q], before = q > 0 ? b.el[q - 1] : ~0u;
-            if (el >> 4 != before >> 4) es = q;
-            if (el != before) b.run_st[++k] = (uint32_t)q;
-            b.rk[q] = (uint32_t)k | ((uint32_t)es << 16);
-        }
-        if (hi == n && lo < hi) b.run_st[k + 1] = (uint32_t)n;
         if (n == 0 && tid == 0) b.run_st[0] = 0u;
     }
     __syncthreads();
@@ -962,27 +1006,34 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
     __syncthreads();
     if (tid < 2) dq.n[tid] = 0;   // lists of the next tile (several barriers away)
 
-    // ---- mover prefix sums and last-mover / last-stayer / run-start maxima
+    // ---- movers before each vehicle, and the last mover and stayer up to it
     {
-        const int chunk = (n + NT - 1) / NT;
-        const int lo = min(n, tid * chunk), hi = min(n, lo + chunk);
-        Scan4 loc{0, -1, -1, -1};
-        for (int q = lo; q < hi; ++q) {
+        Scan4 from{0, -1, -1, -1};
+        for (int base = 0; base < n; base += NT) {
+            const int q = base + tid;
             // the decisions waiting for noise are finished by the thread that scans them
-            finish_pending(b, q, dir, Ga, ca, Gb, cb, na, nb, acc);
-            const int mv = b.pm[q] >> 16;
-            loc.s += mv;
-            if (mv) loc.a = q; else loc.b = q;
+            if (q < n) finish_pending(b, q, dir, Ga, ca, Gb, cb, na, nb, acc);
+            const int mv = q < n ? b.pm[q] >> 16 : 0;
+            const unsigned long long movers = __ballot(q < n && mv), stayers = __ballot(q < n && !mv);
+            if (lane == 0)
+                wsh4[wave] = Scan4{(int)__popcll(movers), movers ? q + last_bit(movers) : -1,
+                                   stayers ? q + last_bit(stayers) : -1, -1};
+            __syncthreads();                      // na, nb (mpref, lml) are read up to here
+            Scan4 all;
+            const Scan4 r = totals_before<NT>(wsh4, all);
+            if (q < n) {
+                const int s = from.s + r.s + bits_below(movers);
+                const unsigned long long m = movers & bits_upto(lane), st = stayers & bits_upto(lane);
+                const int a = m ? q - lane + last_bit(m) : max(from.a, r.a);
+                const int c = st ? q - lane + last_bit(st) : max(from.b, r.b);
+                b.mpref[q] = s;
+                b.lml[q] = (int)(((uint32_t)a & 0xFFFFu) | ((uint32_t)c << 16));
+                if (q == n - 1) b.mpref[n] = s + mv;
+            }
+            if (base + NT >= n) break;
+            from = Scan4{from.s + all.s, max(from.a, all.a), max(from.b, all.b), -1};
+            __syncthreads();                      // wsh4 is reused by the next round
         }
-        Scan4 run = wg_exclusive_scan4<NT>(loc, wsh4);
-        for (int q = lo; q < hi; ++q) {
-            const int mv = b.pm[q] >> 16;
-            b.mpref[q] = run.s;
-            run.s += mv;
-            if (mv) run.a = q; else run.b = q;
-            b.lml[q] = (int)(((uint32_t)run.a & 0xFFFFu) | ((uint32_t)run.b << 16));
-        }
-        if (hi == n && lo < hi) b.mpref[n] = run.s;
         if (n == 0 && tid == 0) b.mpref[0] = 0;
     }
     for (int q = tid; q < n; q += NT) b.inv[q] = -1;
