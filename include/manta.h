@@ -188,8 +188,8 @@ sim_status sim_create_ensemble(const sim_network *net, const sim_routes *master,
  * and the crossing-time interpolation of Sec. IV-A's per-edge outputs).
  * dL_dmean_tt: [n_edges] (edges without a completed traversal are ignored);
  * dL_dparams: [5 * n_classes] out, per class (v0_factor, T, a, b, s0).
- * The handle's state is left as it was.  Adjoint arithmetic is FP64 with
- * atomic accumulation into leaders; parameter sums are reduced in a fixed
+ * The handle's state is left as it was.  Adjoint arithmetic is FP64, every
+ * sum (of a vehicle's adjoint, and of a parameter's gradient) in a fixed
  * order.  Errors: SIM_ESTATE (not recorded), SIM_EINVAL, SIM_ENOMEM. */
 sim_status sim_backward(sim_handle *h, const double *dL_dmean_tt, double *dL_dparams);
 
@@ -231,7 +231,7 @@ sim_status sim_step(sim_handle *h, int32_t n);
  * identical to sim_step. */
 enum {
     SIM_K_TILE_STEP = 0,   /* lane changes, leaders, Eq. (1), integration */
-    SIM_K_BIG_ADMIT,       /* the same for tiles above 384 vehicles, then intersection
+    SIM_K_BIG_ADMIT,       /* the same for tiles above 304 vehicles, then intersection
                               admission: eligibility + priority claim */
     SIM_K_COMMIT,          /* transfers, arrivals, departures, travel times, new counts */
     SIM_K_SCATTER,         /* next sorted layout and look-ahead table */

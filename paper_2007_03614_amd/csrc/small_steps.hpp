@@ -12,7 +12,8 @@
 //
 // Measured per step, four launches against this: a 50-vehicle ring 17.6 and
 // 9.8 us, the 10x10 grid with 365 vehicles on the road 28.2 and 18.7, 32
-// scenarios of it with 4,500 on the road 28.5 and 17.1.
+// scenarios of it with 4,500 on the road 28.5 and 17.1, when it was written; by
+// now the small kernel takes 6.7, 12.6 and 11.8.
 #pragma once
 #include "step_kernels.hpp"
 

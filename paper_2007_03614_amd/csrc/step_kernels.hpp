@@ -8,11 +8,11 @@
 // stamped with the step they are valid for), the rear after the move
 // (admission), and the post-lane-change run of each lane (scatter).
 //
-// One step = 4 launches (5 on networks above 2.1M lanes), all reading the
+// One step = 4 launches (5 on networks above 8.4M lanes), all reading the
 // step number from device memory, so a captured graph of one step can be
 // replayed for every step:
 //   k_tile_step   Phases 1-2 per tile of whole edges, staged in LDS
-//   k_big_admit   the same for tiles above 384 vehicles (1,024 threads), then
+//   k_big_admit   the same for tiles above 304 vehicles (1,024 threads), then
 //                 eligibility + atomicMin of a 64-bit priority key per lane
 //   k_commit      one thread per lane: winners, losers, arrivals, departures,
 //                 travel-time sums, new lane counts and lane offsets within the
