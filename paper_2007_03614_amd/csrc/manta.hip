@@ -264,6 +264,11 @@ void validate(const sim_network* net, const sim_routes* r, const sim_idm_params*
     }
 }
 
+auto scatter_kernel(const Dev& d, bool lds_scan) {
+    if (d.v0_spread != 0.0f) return lds_scan ? k_scatter<true, true> : k_scatter<false, true>;
+    return lds_scan ? k_scatter<true, false> : k_scatter<false, false>;
+}
+
 // The kernels of one step, in order.  ev (optional): 2 events per kernel,
 // recorded by the runtime at the kernel's start and end.
 void launch_step(sim_handle* h, hipStream_t s, hipEvent_t* ev = nullptr) {
@@ -271,16 +276,17 @@ void launch_step(sim_handle* h, hipStream_t s, hipEvent_t* ev = nullptr) {
     const dim3 b(kNT);
     const bool lds_scan = h->n_blk <= kScanLdsMax;
     const auto commit = (1 << d.lane_shift) == kManyBlock ? k_commit_many : k_commit;
+    const auto scatter = scatter_kernel(d, lds_scan);
     if (!ev) {
         hipLaunchKernelGGL(d.v0_spread != 0.0f ? k_tile_step_v0spread : k_tile_step, dim3(h->g_tile), dim3(kTileNT),
                            0, s, d);
         hipLaunchKernelGGL(k_big_admit, dim3(h->g_big), dim3(kBigNT), 0, s, d);
         hipLaunchKernelGGL(commit, dim3(h->n_blk), dim3(kCommitNT), 0, s, d);
         if (lds_scan) {
-            hipLaunchKernelGGL(k_scatter<true>, dim3(h->g_scatter + 1), b, h->scatter_lds, s, d);
+            hipLaunchKernelGGL(scatter, dim3(h->g_scatter + 1), b, h->scatter_lds, s, d);
         } else {
             hipLaunchKernelGGL(k_blkscan, dim3(1), dim3(kBigNT), 0, s, d);
-            hipLaunchKernelGGL(k_scatter<false>, dim3(h->g_scatter), b, 0, s, d);
+            hipLaunchKernelGGL(scatter, dim3(h->g_scatter), b, 0, s, d);
         }
         return;
     }
@@ -289,11 +295,11 @@ void launch_step(sim_handle* h, hipStream_t s, hipEvent_t* ev = nullptr) {
     hipExtLaunchKernelGGL(k_big_admit, dim3(h->g_big), dim3(kBigNT), 0, s, ev[2], ev[3], 0, d);
     if (lds_scan) {
         hipExtLaunchKernelGGL(commit, dim3(h->n_blk), dim3(kCommitNT), 0, s, ev[4], ev[5], 0, d);
-        hipExtLaunchKernelGGL(k_scatter<true>, dim3(h->g_scatter + 1), b, h->scatter_lds, s, ev[6], ev[7], 0, d);
+        hipExtLaunchKernelGGL(scatter, dim3(h->g_scatter + 1), b, h->scatter_lds, s, ev[6], ev[7], 0, d);
     } else {   // the block scan is counted with commit
         hipExtLaunchKernelGGL(commit, dim3(h->n_blk), dim3(kCommitNT), 0, s, ev[4], nullptr, 0, d);
         hipExtLaunchKernelGGL(k_blkscan, dim3(1), dim3(kBigNT), 0, s, nullptr, ev[5], 0, d);
-        hipExtLaunchKernelGGL(k_scatter<false>, dim3(h->g_scatter), b, 0, s, ev[6], ev[7], 0, d);
+        hipExtLaunchKernelGGL(scatter, dim3(h->g_scatter), b, 0, s, ev[6], ev[7], 0, d);
     }
 }
 
@@ -309,6 +315,7 @@ void for_each_state_piece(sim_handle* h, F&& f) {
         f((void*)d.s[b].edge, 4 * N);
         f((void*)d.s[b].meta, 4 * N);
         f((void*)d.s[b].nxt, 4 * N);
+        if (d.v0_spread != 0.0f) f((void*)d.s[b].lim, 4 * N);
     }
     f((void*)d.status, N);
     f((void*)d.cursor, 4 * N);
@@ -443,7 +450,8 @@ void plan_small(sim_handle* h, const std::vector<SmallRange>& range, long long m
     if (ns > 1) {
         const size_t NV = (size_t)std::max(h->n_veh, 1);
         sm.extra = Slots{h->dev<float>(NV), h->dev<float>(NV), h->dev<uint32_t>(NV), h->dev<int32_t>(NV),
-                         h->dev<uint32_t>(NV), h->dev<int32_t>(NV), h->dev<int32_t>(NV)};
+                         h->dev<uint32_t>(NV), h->dev<int32_t>(NV), h->dev<int32_t>(NV),
+                         d.v0_spread != 0.0f ? h->dev<float>(NV) : nullptr};
         sm.n = h->dev<int>(ns + 1);
         sm.moved = h->dev<unsigned long long>((size_t)ns * kSmallWords);
         sm.active = h->dev<unsigned long long>((size_t)ns * kSmallWords);
@@ -796,8 +804,8 @@ sim_status create_impl(const sim_network* net, const sim_routes* r, const sim_id
                 HIP_OK(hipGetDevice(&dev));
                 HIP_OK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
                 const size_t dyn = h->scatter_lds ? h->scatter_lds : sizeof(int) * (size_t)kScanLdsMax;
-                HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_scatter<true>, kNT, dyn));
-                per_cu = std::min(per_cu, lds_fit((const void*)k_scatter<true>, dev, dyn));
+                HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, scatter_kernel(d, true), kNT, dyn));
+                per_cu = std::min(per_cu, lds_fit((const void*)scatter_kernel(d, true), dev, dyn));
                 h->g_scatter_res = std::max(1, std::min(cus * std::max(per_cu, 1), h->g_scatter_max));
                 h->g_scatter = h->g_scatter_res;
             }
@@ -811,6 +819,7 @@ sim_status create_impl(const sim_network* net, const sim_routes* r, const sim_id
                 d.s[b].meta = h->dev<uint32_t>(NV);
                 d.s[b].nxt = h->dev<int32_t>(NV);
                 d.s[b].gl = h->dev<int32_t>(NV);
+                d.s[b].lim = d.v0_spread != 0.0f ? h->dev<float>(NV) : nullptr;
             }
             d.ent = h->dev<EntryRec>(NL);
             d.status = h->dev<uint8_t>(NV);

@@ -52,7 +52,7 @@ __host__ __device__ inline size_t small_table_bytes(int lanes, int nodes) {
 }
 
 __device__ inline Slots slots_at(const Slots& s, int o) {
-    return Slots{s.x + o, s.v + o, s.vid + o, s.edge + o, s.meta + o, s.nxt + o, s.gl + o};
+    return Slots{s.x + o, s.v + o, s.vid + o, s.edge + o, s.meta + o, s.nxt + o, s.gl + o, s.lim ? s.lim + o : nullptr};
 }
 
 // first slot of [0, n) on edge e or a later one
@@ -84,11 +84,11 @@ __global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps)
     __shared__ unsigned shc[cNumCounters];
     __shared__ ClassParams scp[16];
     __shared__ float slen[16];
-    __shared__ uint16_t dlist[2 * NT];
-    __shared__ int dcount[2];
+    __shared__ uint16_t dlist[2 * NT], dfresh[kSpread ? 2 * NT : 1];
+    __shared__ int dcount[3];
     __shared__ int smoved, sdep, stot, sreq, shead;
     const int tid = threadIdx.x, k = blockIdx.x;
-    const DrawQ dq{dlist, dcount, 2 * NT};
+    const DrawQ dq{dlist, dcount, 2 * NT, dfresh};
     const SmallRange r0 = sm.range[k], r1 = sm.range[k + 1];
     const int nl = r1.lane - r0.lane;
     // the tile, where the exits of a step and its claiming queues are kept once its tiles are done; then the lanes' tables
@@ -115,7 +115,7 @@ __global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps)
     int* const heads = (int*)(lds + 16 * (size_t)sm.lanes);
 
     if (tid < cNumCounters) shc[tid] = 0;
-    if (tid < 2) dcount[tid] = 0;
+    if (tid < 3) dcount[tid] = 0;
     if (tid == 0) smoved = sdep = sreq = shead = 0;
     if (tid < 16) {
         scp[tid] = d.cp[tid];
@@ -219,9 +219,9 @@ __global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps)
         }
         for (int i = tid; i < max(n, nl); i += NT) {
             ScatterItem r;
-            scatter_load_record(S, i < n ? i : -1, r);
+            scatter_load_record<kSpread>(S, i < n ? i : -1, r);
             scatter_load_tables(d, tb, i < nl && tb.enter_stamp[i] == t ? r0.lane + i : -1, r);
-            scatter_store(d, tb, B, r, nnew, t, slen, [](int) { return 0; });
+            scatter_store<kSpread>(d, tb, B, r, nnew, t, slen, [](int) { return 0; });
         }
         if (d.imode == 1)
             for (int i = tid; i < sm.nodes; i += NT) tb.win_node[i] = ~0ull;
@@ -292,6 +292,7 @@ __global__ void __launch_bounds__(kSmallNT) k_small_gather(Dev d, Small sm, int 
         B.edge[i] = A.edge[i];
         B.meta[i] = A.meta[i];
         B.nxt[i] = A.nxt[i];
+        if (d.v0_spread != 0.0f) B.lim[i] = A.lim[i];
     }
     if (k != 0) return;
     const int nw = (nsteps + 63) / 64;

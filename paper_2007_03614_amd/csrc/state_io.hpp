@@ -233,6 +233,7 @@ __global__ void __launch_bounds__(kNT) k_io_rank(Dev d, IoWork w, StateIo in, Sl
         B.edge[dst] = e;
         B.meta[dst] = m_make(l, in.mand[i] != 0, in.held_since[i] >= 0, in.ww[i], d.cls[i], rw >> 24);
         B.nxt[dst] = word_next(rw);
+        if (d.v0_spread != 0.0f) B.lim[dst] = kLimUnknown;
     }
 }
 
@@ -293,6 +294,7 @@ __global__ void __launch_bounds__(kNT) k_io_apply(Dev d, IoWork w, StateIo in, S
             S.edge[i] = B.edge[i];
             S.meta[i] = B.meta[i];
             S.nxt[i] = B.nxt[i];
+            if (d.v0_spread != 0.0f) S.lim[i] = B.lim[i];
         }
         if (i < nn) {                          // the round-robin restarts
             d.rr[i] = -1;

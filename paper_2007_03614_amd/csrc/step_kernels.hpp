@@ -122,7 +122,9 @@ struct Slots {
     uint32_t* meta;
     int32_t* nxt;     // next route edge, -1 on the last edge
     int32_t* gl;      // global lane after the lane change, written by the tile kernels for k_scatter
+    float* lim;       // v0_spread > 0: the driver's own limit on its edge, kLimUnknown until its first step there
 };
+constexpr float kLimUnknown = -1.0f;
 
 struct LaneRear {     // rear of a lane at the start of step `stamp`
     float xm;         // x - length of the rear vehicle
@@ -600,12 +602,15 @@ struct StepRecord {
     uint32_t m, vid;
     int e, f;
     float x, v;
+    float lim;        // Slots::lim (own limits only)
     EdgeC ce, cf;
 };
 
-// e: its edge, loaded before
+// e: its edge, loaded before.  kSpread: with the driver's own limit, if there are any
+template <bool kSpread>
 __device__ inline StepRecord load_record(const Dev& d, const Slots& S, int s, int e) {
     StepRecord r;
+    r.lim = kSpread && d.v0_spread != 0.0f ? S.lim[s] : 0.0f;
     r.e = e;
     r.f = S.nxt[s];
     r.m = S.meta[s];
@@ -637,7 +642,7 @@ struct AheadRecord {
 // workgroup may be rewriting them; each of their words is valid all the same).
 // wsh: 4 * (NT / 64) ints in LDS, used by halves in turn (flip), so that the
 // barrier of the next search separates this one's reads from the writes after it.
-template <int NT>
+template <int NT, bool kSpread>
 __device__ inline TileSpan tile_bounds(const Dev& d, const Slots& S, int w0, int w1, int n, int* wsh, int& flip,
                                        AheadRecord& ah) {
     constexpr int kW = NT / 64;
@@ -650,7 +655,7 @@ __device__ inline TileSpan tile_bounds(const Dev& d, const Slots& S, int w0, int
     // (no branch around the loads: the search waits for the first two alone)
     const int si = min(s, n - 1), e = edge[si], before = edge[max(si - 1, 0)];
     const int sr = min(s, ah.end - 1);
-    ah.r = load_record(d, S, sr, edge[sr]);
+    ah.r = load_record<kSpread>(d, S, sr, edge[sr]);
     const bool f = s < n && (s == 0 || e != before);
     const unsigned long long b0 = __ballot(f && s < w1), b1 = __ballot(f && s >= w1);
     const int wave = threadIdx.x >> 6;
@@ -680,8 +685,9 @@ __device__ inline TileSpan tile_bounds(const Dev& d, const Slots& S, int w0, int
 // draw_uniform / draw_normal exactly.
 struct DrawQ {
     uint16_t* list;   // [cap] q | side << 15
-    int* n;           // [2] entries asked for in each round
+    int* n;           // [3] entries asked for in each round, then in fresh
     int cap;
+    uint16_t* fresh;  // [cap] own limits: vehicles in their first step on their edge
 };
 
 template <int kUnroll>
@@ -812,6 +818,8 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
     float* const Gb = (float*)b.pel;
     float* const cb = (float*)b.inv;
 
+    const bool own = kSpread && d.v0_spread != 0.0f;   // each driver has a limit of its own (Sec. IV)
+
     // load S_t (coalesced) and list the Eq. (2) draws
     const auto put = [&](int q, const StepRecord& r) {
         const uint32_t m = r.m;
@@ -829,6 +837,15 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
         b.lim[q] = r.ce.lim;
         u1[q] = 0;
         na[q] = 0;
+        if (kSpread && own) {
+            if (r.lim >= 0.0f) {
+                b.lim[q] = r.lim;
+                na[q] = INT_MIN;                                        // known: no draw
+            } else {
+                const int k = atomicAdd(&dq.n[2], 1);
+                if (k < dq.cap) dq.fresh[k] = (uint16_t)q;
+            }
+        }
         nb[q] = 0;
         if (!m_held(m) && !m_mand(m) && !lane_allowed(m, f, m_lane(m))) {   // Eq. (2) may trigger
             const float dd = L - x;
@@ -844,7 +861,7 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
         if (ahead.slot >= 0 && q >= 0 && q < n) put(q, ahead.r);
         q0 = max(0, ahead.end - a0) + tid;
     }
-    for (int q = q0; q < n; q += NT) put(q, load_record(d, S, a0 + q, S.edge[a0 + q]));
+    for (int q = q0; q < n; q += NT) put(q, load_record<kSpread>(d, S, a0 + q, S.edge[a0 + q]));
     __syncthreads();
 
     // ---- runs of S_t (tile order: edge, lane, then x and id descending)
@@ -886,22 +903,28 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
         b.rk[q] = k | (k0 << 16);
     }
     draw_run<NT>(d, dq, 0, t, b, n, u1, na, nb);
-    // each driver's own limit on its edge (Sec. IV): the words of its draw, a
-    // block a thread (three blocks one after another on the vehicle's own thread
-    // would leave three threads in four idle on the tiles of a short step)
-    if (kSpread && d.v0_spread != 0.0f)
-        for (int i = tid; i < 3 * n; i += NT) {
-            const int q = i / 3, e = (int)(b.el[q] >> 4);
-            atomicAdd(&na[q], (int)philox_words<10>(d.seed, e % d.edge_period, draw_id(d, b.vid[q], e), 4, i - 3 * q));
+    // each driver's own limit on its edge (Sec. IV) is drawn in its first step
+    // there and stays in its record (drawn in every step, three blocks a vehicle,
+    // the tile kernel takes 17.1 us on the 100x100 city, against 15.4, and a step of
+    // the 10x10 grid in one workgroup 19.7, against 17.8): the words of the
+    // draws, a block a thread, of the listed vehicles, or of all that need one
+    // where there are more than the list holds (a state just written)
+    if (kSpread && own) {
+        const int nf = dq.n[2];
+        for (int i = tid; i < 3 * (nf <= dq.cap ? nf : n); i += NT) {
+            const int at = i / 3, q = nf <= dq.cap ? dq.fresh[at] : at, e = (int)(b.el[q] >> 4);
+            if (na[q] < 0) continue;
+            atomicAdd(&na[q], (int)philox_words<2>(d.seed, e % d.edge_period, draw_id(d, b.vid[q], e), 4, i - 3 * at));
         }
+    }
     __syncthreads();
 
     // ---- Phase 1: lane-change decisions (Eqs. (2)-(4)) against S_t
     for (int q = tid; q < n; q += NT) {
         uint32_t m = b.meta[q];
         int moved = 0, pos = 0;
-        if (kSpread && d.v0_spread != 0.0f) {
-            b.lim[q] = driver_limit_of(b.lim[q], d.v0_spread, normal_of_words(na[q]));
+        if (kSpread && own) {
+            if (na[q] >= 0) b.lim[q] = driver_limit_of(b.lim[q], d.v0_spread, normal_of_words(na[q]));
             na[q] = 0;
         }
         if (!m_held(m)) {
@@ -1004,7 +1027,7 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
     __syncthreads();
     draw_run<NT>(d, dq, 1, t, b, n, u1, na, nb);
     __syncthreads();
-    if (tid < 2) dq.n[tid] = 0;   // lists of the next tile (several barriers away)
+    if (tid < 3) dq.n[tid] = 0;   // lists of the next tile (several barriers away)
 
     // ---- movers before each vehicle, and the last mover and stayer up to it
     {
@@ -1194,6 +1217,7 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
         S.edge[dst] = e;
         S.meta[dst] = m;
         S.nxt[dst] = f;
+        if (kSpread && own) S.lim[dst] = b.lim[q];
         S.gl[dst] = lw_base(b.lbe[q]) + lam;
         b.xn[q] = xnew;
         b.fl[q] = fl;
@@ -1321,13 +1345,13 @@ __device__ inline void tile_step(const Dev& d) {
     __shared__ int sbig;                        // index of a tile listed as big
     __shared__ unsigned shc[cNumCounters];
     __shared__ ClassParams scp[16];
-    __shared__ uint16_t dlist[kTileDraws];
-    __shared__ int dcount[2];
+    __shared__ uint16_t dlist[kTileDraws], dfresh[kSpread ? kTileDraws : 1];
+    __shared__ int dcount[3];
     __shared__ int smoved;                      // gridlock detector: a vehicle of this workgroup moved
     __shared__ int snext;                       // the workgroup's next tile
-    const DrawQ dq{dlist, dcount, kTileDraws};
+    const DrawQ dq{dlist, dcount, kTileDraws, dfresh};
     if (threadIdx.x < cNumCounters) shc[threadIdx.x] = 0;
-    if (threadIdx.x < 2) dcount[threadIdx.x] = 0;
+    if (threadIdx.x < 3) dcount[threadIdx.x] = 0;
     if (threadIdx.x == 0) smoved = 0;
     if (threadIdx.x < 16) scp[threadIdx.x] = d.cp[threadIdx.x];
     const StepHead sh = step_head(d.ctl);
@@ -1359,7 +1383,7 @@ __device__ inline void tile_step(const Dev& d) {
     // bounds (run_tile), then its phases or its listing as a big tile (do_tile)
     auto run_tile = [&](int k) {
         const int w0 = k * W, w1 = min(n, w0 + W);
-        return tile_bounds<kTileNT>(d, S, w0, w1, n, wsh, flip, ah);
+        return tile_bounds<kTileNT, kSpread>(d, S, w0, w1, n, wsh, flip, ah);
     };
     auto do_tile = [&](const TileSpan& sp) {
         const int a0 = sp.a0, a1 = sp.a1;
@@ -1475,12 +1499,12 @@ __device__ __forceinline__ void big_tiles(const Dev& d, int t, int par, int nbig
     __shared__ int wsh[kBigNT / 64];
     __shared__ unsigned shc[cNumCounters];
     __shared__ ClassParams scp[16];
-    __shared__ uint16_t dlist[2 * kBigNT];
-    __shared__ int dcount[2];
+    __shared__ uint16_t dlist[2 * kBigNT], dfresh[2 * kBigNT];
+    __shared__ int dcount[3];
     __shared__ int smoved;                      // gridlock detector: a vehicle of this workgroup moved
-    const DrawQ dq{dlist, dcount, 2 * kBigNT};
+    const DrawQ dq{dlist, dcount, 2 * kBigNT, dfresh};
     if (threadIdx.x < cNumCounters) shc[threadIdx.x] = 0;
-    if (threadIdx.x < 2) dcount[threadIdx.x] = 0;
+    if (threadIdx.x < 3) dcount[threadIdx.x] = 0;
     if (threadIdx.x == 0) smoved = 0;
     if (threadIdx.x < 16) scp[threadIdx.x] = d.cp[threadIdx.x];
     __syncthreads();
@@ -2158,8 +2182,9 @@ __global__ void __launch_bounds__(kBigNT) k_blkscan(Dev d) {
 // ---- next layout -----------------------------------------------------------
 // One record of the next layout at slot dst, and the lane's rear for the
 // next step's look-ahead if it is the lane's last vehicle.
+template <bool kSpread>
 __device__ inline void put_record(const Dev& d, const LaneTabs& tb, const Slots& B, int dst, int nnew, float x, float v, uint32_t vid,
-                                  int edge, uint32_t meta, int nxt, bool is_rear, int gl, int t, const float* slen) {
+                                  int edge, uint32_t meta, int nxt, float lim, bool is_rear, int gl, int t, const float* slen) {
     if (dst < 0 || dst >= nnew) {
         atomicOr(&d.ctl->err, kErrScatter);
         return;
@@ -2170,6 +2195,7 @@ __device__ inline void put_record(const Dev& d, const LaneTabs& tb, const Slots&
     B.edge[dst] = edge;
     B.meta[dst] = meta;
     B.nxt[dst] = nxt;
+    if (kSpread) B.lim[dst] = lim;
     if (is_rear) {
         LaneRear lr;
         lr.xm = x - slen[m_cls(meta)];
@@ -2186,7 +2212,7 @@ __device__ inline void put_record(const Dev& d, const LaneTabs& tb, const Slots&
 // tables of the record's lane and the entry of a claimed lane.
 struct ScatterItem {
     int k, i;
-    float x, v;
+    float x, v, lim;
     uint32_t vid, meta;
     int edge, nxt, gl;
     LanePost lp;
@@ -2197,6 +2223,7 @@ struct ScatterItem {
 
 // (Without a branch, so that nothing waits for them before they are used: with
 // none, slot 0 and the tables of the first lane.)
+template <bool kSpread>
 __device__ inline void scatter_load_record(const Slots& A, int k, ScatterItem& r) {
     const int s = max(k, 0);
     r.k = k;
@@ -2207,6 +2234,7 @@ __device__ inline void scatter_load_record(const Slots& A, int k, ScatterItem& r
     r.v = A.v[s];
     r.vid = A.vid[s];
     r.nxt = A.nxt[s];
+    r.lim = kSpread ? A.lim[s] : 0.0f;
 }
 
 __device__ inline void scatter_load_tables(const Dev& d, const LaneTabs& tb, int i, ScatterItem& r) {
@@ -2225,7 +2253,7 @@ __device__ inline void scatter_load_tables(const Dev& d, const LaneTabs& tb, int
 }
 
 // off(lane): where that lane's offset counts from.
-template <class Off>
+template <bool kSpread, class Off>
 __device__ inline void scatter_store(const Dev& d, const LaneTabs& tb, const Slots& B, const ScatterItem& r, int nnew,
                                      int t, const float* slen, Off off) {
     if (r.k >= 0) {
@@ -2234,13 +2262,13 @@ __device__ inline void scatter_store(const Dev& d, const LaneTabs& tb, const Slo
             atomicOr(&d.ctl->err, kErrScatter);
         } else if (!(ex && rank == 0)) {      // unless the lane's front left the edge
             const int nr = rank - ex;
-            put_record(d, tb, B, off(r.gl) + r.loff + nr, nnew, r.x, r.v, r.vid, r.edge, r.meta, r.nxt,
+            put_record<kSpread>(d, tb, B, off(r.gl) + r.loff + nr, nnew, r.x, r.v, r.vid, r.edge, r.meta, r.nxt, r.lim,
                        (nr == r.ncnt - 1) && r.enter_stamp != t, r.gl, t, slen);
         }
     }
     if (r.i >= 0) {                           // the entry is the lane's new rear
-        put_record(d, tb, B, off(r.i) + r.enoff + r.encnt - 1, nnew, r.en.x, r.en.v, r.en.vid, r.en.edge, r.en.meta,
-                   r.en.nxt, true, r.i, t, slen);
+        put_record<kSpread>(d, tb, B, off(r.i) + r.enoff + r.encnt - 1, nnew, r.en.x, r.en.v, r.en.vid, r.en.edge, r.en.meta,
+                   r.en.nxt, kLimUnknown, true, r.i, t, slen);
         tb.win[r.i - tb.lane0] = ~0ull;       // lane free for the next step's claims
     }
 }
@@ -2249,8 +2277,8 @@ __device__ inline void scatter_store(const Dev& d, const LaneTabs& tb, const Slo
 //   block offset + lane offset in block + rank in lane
 // kLds: the workgroup scans the block offsets itself into LDS (at most
 // kScanLdsMax commit blocks), and workgroup 0 finishes the step; otherwise
-// k_blkscan has done both.
-template <bool kLds>
+// k_blkscan has done both.  kSpread: the records have their drivers' own limits.
+template <bool kLds, bool kSpread>
 __device__ inline void scatter_items(const Dev& d, int* soff, Scan4* wsh4, int* totp, float* slen) {
     const float len = d.cp[threadIdx.x & 15].len;   // into slen below, behind the other first loads
     const StepHead sh = step_head(d.ctl);
@@ -2280,7 +2308,7 @@ __device__ inline void scatter_items(const Dev& d, int* soff, Scan4* wsh4, int* 
         // (after it, they are two more of the kernel's four rounds: 5.6 against
         // 4.8 us a step on the 100x100 city, 18.7 against 16.5 on the
         // metropolitan lattice, of which 11 are its bytes).
-        scatter_load_record(A, k < nold ? k : -1, r);
+        scatter_load_record<kSpread>(A, k < nold ? k : -1, r);
         const int4 st = stamps(k);
         stage_block_sums<kNT>(d.blk_sum, d.n_blk, soff);
         claims = lanes_at(st, t);
@@ -2304,20 +2332,20 @@ __device__ inline void scatter_items(const Dev& d, int* soff, Scan4* wsh4, int* 
     const int stride = (gridDim.x - (kLds ? 1 : 0)) * kNT;
     for (bool loaded = kLds; k < nit; k += stride, loaded = false) {
         if (!loaded) {
-            scatter_load_record(A, k < nold ? k : -1, r);
+            scatter_load_record<kSpread>(A, k < nold ? k : -1, r);
             claims = lanes_at(stamps(k), t);
             scatter_load_tables(d, tb, next(k), r);
         }
-        scatter_store(d, tb, B, r, nnew, t, slen, off);
+        scatter_store<kSpread>(d, tb, B, r, nnew, t, slen, off);
         while (claims) {
             r.k = -1;
             scatter_load_tables(d, tb, next(k), r);
-            scatter_store(d, tb, B, r, nnew, t, slen, off);
+            scatter_store<kSpread>(d, tb, B, r, nnew, t, slen, off);
         }
     }
 }
 
-template <bool kLds>
+template <bool kLds, bool kSpread>
 __global__ void __launch_bounds__(kNT) k_scatter(Dev d) {
     // kLds: the block offsets, d.n_blk ints of dynamic LDS sized at launch
     // (so a network with few commit blocks leaves room for more workgroups)
@@ -2325,7 +2353,7 @@ __global__ void __launch_bounds__(kNT) k_scatter(Dev d) {
     __shared__ Scan4 wsh4[kWaves];
     __shared__ int tot;
     __shared__ float slen[16];                    // vehicle length per class
-    scatter_items<kLds>(d, soff, wsh4, &tot, slen);
+    scatter_items<kLds, kSpread>(d, soff, wsh4, &tot, slen);
     if (d.imode == 1)                             // case 1: nodes free for the next step's crossings
         for (int v = blockIdx.x * kNT + threadIdx.x; v < d.n_nodes; v += gridDim.x * kNT) d.win_node[v] = ~0ull;
 }

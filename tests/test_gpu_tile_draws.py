@@ -57,3 +57,25 @@ def test_full_lists(M, oracle_mod, n, spread):
         for s in (whole, runs):
             assert compare_states(s.state(), orc.state(), f"step {orc.t}")
     assert orc.counters()["lane_changes"] > n // 4
+
+
+@pytest.mark.parametrize("n,spread", [(2600, 0.1), (1300, 0.25)])
+def test_own_limits_after_a_written_state(M, oracle_mod, n, spread):
+    """Every driver's limit is unknown after a written state: 2,600 on one edge are more than the 1,024-thread kernel
+    lists (2,048).  Then they are carried from step to step, and drawn for the vehicles that enter the next edge."""
+    from test_gpu_parity import compare_states
+    w, init = _queue(n, spread)
+    g, orc = M.Sim(w), oracle_mod.OracleSim(w)
+    g.write_state(init)
+    orc.write_state(0, init)
+    for steps in (1, 1, 30, 200):
+        g.step(steps)
+        orc.step(steps)
+        assert compare_states(g.state(), orc.state(), f"step {orc.t}")
+    assert orc.counters()["transfers"] > 0
+    mid = g.state()
+    h = M.Sim(w)
+    h.write_state(mid)
+    h.step_timed(25)
+    orc.step(25)
+    assert compare_states(h.state(), orc.state(), f"step {orc.t}")
