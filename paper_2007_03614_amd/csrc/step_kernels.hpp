@@ -2307,7 +2307,7 @@ __device__ inline void scatter_items(const Dev& d, int* soff, Scan4* wsh4, int* 
         // item, which need no offset, go out with the sums and during the scan
         // (after it, they are two more of the kernel's four rounds: 5.6 against
         // 4.8 us a step on the 100x100 city, 18.7 against 16.5 on the
-        // metropolitan lattice, of which 11 are its bytes).
+        // metropolitan lattice, where it moves its bytes at the rate of a copy).
         scatter_load_record<kSpread>(A, k < nold ? k : -1, r);
         const int4 st = stamps(k);
         stage_block_sums<kNT>(d.blk_sum, d.n_blk, soff);
