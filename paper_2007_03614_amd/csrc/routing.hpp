@@ -200,6 +200,7 @@ __global__ void __launch_bounds__(kRouteNT) k_route_tree(int V, const RouteIn* _
         ncur = *pushed;
         if (ncur > 0) continue;
         if (lowest == ~0u) break;
+        __syncthreads();                     // every thread has read the count before it is pushed to again
         bar = max(__float_as_uint(__uint_as_float(lowest >> 1) + step) << 1, lowest + 2u);
         for (int v = tid; v < V; v += NT) {
             const unsigned w = lab[v];
