@@ -134,6 +134,9 @@ __global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps)
     const bool alone = sm.n_scen == 1;
     const int a0 = alone ? 0 : first_slot_of(d.s[par0].edge, n_all, r0.edge);
     int n = (alone ? n_all : first_slot_of(d.s[par0].edge, n_all, r1.edge)) - a0;
+    // A scenario with nothing on the road still loads the first slot of its layout (scatter_load_record, dropped):
+    // behind every vehicle there is none, and it takes the last there is.
+    const int slot_max = max(d.n_veh - 1, 0), v0 = min(r0.veh, slot_max);
     __syncthreads();
     // vehicles that have left the departure queues
     int dep = 0;
@@ -148,11 +151,11 @@ __global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps)
     acc.zero();
     unsigned long long act_sum = 0, denied = 0, grid_steps = 0, mv_bits = 0, ac_bits = 0;
     int run = alone ? d.ctl->stall_run : 0;
-    Slots S = slots_at(d.s[par0], a0);
+    Slots S = slots_at(d.s[par0], min(a0, slot_max));
     for (int j = 0; j < nsteps; ++j) {
         const int t = t0 + j;
         // an ensemble's scenarios write no buffer that another may still read as its first layout
-        const Slots B = alone ? d.s[(t + 1) & 1] : slots_at((nsteps - 1 - j) & 1 ? d.s[par0 ^ 1] : sm.extra, r0.veh);
+        const Slots B = alone ? d.s[(t + 1) & 1] : slots_at((nsteps - 1 - j) & 1 ? d.s[par0 ^ 1] : sm.extra, v0);
         if (d.trace && tid == 0) d.nact_hist[t % d.trace_period] = n;
         tile_pieces<NT, kSpread, false>(d, tb, S, lds, sm.cap, 0, n, t, acc, wsh4, wsh, scp, dq, &smoved);
         for (int i = tid; i < nl; i += NT) {       // (the tile's space is free after its last barrier)
