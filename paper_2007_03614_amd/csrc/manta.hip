@@ -455,6 +455,7 @@ void plan_small(sim_handle* h, const std::vector<SmallRange>& range, long long m
         sm.n = h->dev<int>(ns + 1);
         sm.moved = h->dev<unsigned long long>((size_t)ns * kSmallWords);
         sm.active = h->dev<unsigned long long>((size_t)ns * kSmallWords);
+        sm.late = h->dev<int>((size_t)ns * kSmallSteps);
     }
     sm.cap = cap;
     sm.lanes = lanes;

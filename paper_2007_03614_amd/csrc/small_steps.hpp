@@ -42,6 +42,7 @@ struct Small {
     int* n;                              // ensembles: [n_scen] vehicles after the run, then the step reached
     unsigned long long* moved;           // ensembles: [n_scen][kSmallWords] steps in which a vehicle moved
     unsigned long long* active;          //   and steps that began with one
+    int* late;                           // ensembles: [n_scen][kSmallSteps] vehicles due less those that have departed
     int* arrived;                        // host memory: [n_scen] arrivals so far (null: not wanted)
     int cap, lanes, nodes;               // tile capacity (a multiple of 4), and the tables' entries in LDS
 };
@@ -233,7 +234,8 @@ __global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps)
             dep += sdep;
             sdep = sreq = shead = 0;
             const int due = d.max_dep < 0 ? 0 : sm.due[(size_t)k * sm.due_stride + min(t, d.max_dep)];
-            if (due > dep) denied += (unsigned long long)(due - dep);
+            if (alone) denied += due > dep ? (unsigned long long)(due - dep) : 0ull;
+            else sm.late[(size_t)k * kSmallSteps + j] = due - dep;   // (counted over all scenarios, k_small_gather)
             const bool mv = smoved != 0;
             smoved = 0;
             if (alone) {
@@ -273,13 +275,16 @@ __global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps)
 }
 
 // Ensembles: the scenarios' last layouts, one after another, and the end of
-// the run (control block, gridlock detector over all scenarios).
+// the run (control block, gridlock detector and refused departures over all
+// scenarios: a written state may have more departures than are due in one).
 __global__ void __launch_bounds__(kSmallNT) k_small_gather(Dev d, Small sm, int nsteps) {
     __shared__ int scnt[kSmallScen + 1];
     __shared__ unsigned long long smv[kSmallWords], sac[kSmallWords];
+    __shared__ int slate[kSmallSteps];
     const int tid = threadIdx.x, k = blockIdx.x;
     for (int i = tid; i < sm.n_scen; i += kSmallNT) scnt[i] = sm.n[i];
     if (tid < kSmallWords) smv[tid] = sac[tid] = 0;
+    for (int j = tid; j < nsteps; j += kSmallNT) slate[j] = 0;
     __syncthreads();
     int o = 0, total = 0;
     for (int i = 0; i < sm.n_scen; ++i) {
@@ -304,7 +309,14 @@ __global__ void __launch_bounds__(kSmallNT) k_small_gather(Dev d, Small sm, int 
         atomicOr(&smv[w], sm.moved[(size_t)s * kSmallWords + w]);
         atomicOr(&sac[w], sm.active[(size_t)s * kSmallWords + w]);
     }
+    for (int i = tid; i < sm.n_scen * nsteps; i += kSmallNT) {
+        const int s = i / nsteps, j = i % nsteps;
+        atomicAdd(&slate[j], sm.late[(size_t)s * kSmallSteps + j]);
+    }
     __syncthreads();
+    unsigned long long denied = 0;
+    for (int j = tid; j < nsteps; j += kSmallNT) denied += (unsigned long long)max(slate[j], 0);
+    if (denied) atomicAdd(&d.counters[cInsertDenied * kCounterCopies], denied);
     if (tid != 0) return;
     int run = d.ctl->stall_run;
     unsigned long long grid_steps = 0;
