@@ -10,6 +10,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <numeric>
 #include <string>
 #include <vector>
 
@@ -102,10 +103,12 @@ struct sim_handle {
     Small sm{};
     size_t small_lds = 0;
     int small_veh = 0;                // vehicles of the largest scenario
-    int small_max_dep = -1;
-    std::vector<int> small_due;       // [scenario][step]: vehicles due by then
+    int small_limit = 0;              // vehicles of a scenario on the road at most (kSmallActive)
+    int small_len = 0;
+    std::vector<int> small_road;      // [scenario][small_len]: vehicles on the road if every trip takes its usual time
     std::vector<int> small_n;         // [scenario]: vehicles
-    int* arrived = nullptr;           // pinned, written by the device: [scenario] arrivals at the end of a launch
+    unsigned long long* road = nullptr;   // pinned: [scenario] on the road as last known | that step << 32, written by
+                                          //   the device at the end of a launch and here where a state passes by
     // state I/O: the arrays by vehicle id on the device, and a pinned block (allocated at first use) that small
     // states pass through whole and larger ones with their head
     IoWork iow{};
@@ -140,8 +143,8 @@ struct sim_handle {
         graph = nullptr;
         exec_k = nullptr;
         graph_k = nullptr;
-        if (arrived) (void)hipHostFree(arrived);
-        arrived = nullptr;
+        if (road) (void)hipHostFree(road);
+        road = nullptr;
         if (io_pin) (void)hipHostFree(io_pin);
         io_pin = nullptr;
         for (void* p : bufs) al.put(p);
@@ -397,7 +400,8 @@ void capture_graph(sim_handle* h) {
 // Whether k_small_steps can run the handle, and what it needs.  range: the
 // scenarios' first edge, lane, queue, node and vehicle, with the end of the
 // last.  max_edge: vehicles an edge may hold (one tile must hold it).
-void plan_small(sim_handle* h, const std::vector<SmallRange>& range, long long max_edge) {
+void plan_small(sim_handle* h, const sim_network* net, const sim_idm_params* p, const std::vector<SmallRange>& range,
+                long long max_edge) {
     Dev& d = h->d;
     const int ns = (int)range.size() - 1;
     if (ns < 1 || ns > kSmallScen || ns > h->g_big_max) return;
@@ -430,22 +434,50 @@ void plan_small(sim_handle* h, const std::vector<SmallRange>& range, long long m
     h->small_lds = (size_t)cap * kTileBytesPerVeh + 64 + small_table_bytes(lanes, nodes);
     HIP_OK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max - (int)fa.sharedSizeBytes));
     h->small_veh = nv;
-    h->small_max_dep = d.max_dep;
-    const int stride = std::max(1, d.max_dep + 1);
-    if (ns > 1 && (long long)ns * stride > (16ll << 20)) return;
-    if (ns > 1 || nv > kSmallActive) {
-        h->small_due.assign((size_t)ns * stride, 0);
+    h->small_limit = ns < kSmallMany ? kSmallActive : kSmallActiveMany;
+    const long long stride = std::max(1ll, (long long)d.max_dep + 1);
+    if ((ns > 1 || nv > h->small_limit) && ns * stride > (16ll << 20)) return;
+    std::vector<int> due;
+    if (ns > 1) {
+        due.assign((size_t)(ns * stride), 0);
         for (int k = 0; k < ns; ++k) {
-            int* due = &h->small_due[(size_t)k * stride];
-            for (int i = range[k].veh; i < range[k + 1].veh; ++i) due[h->dep[i]]++;
-            for (int t = 1; t < stride; ++t) due[t] += due[t - 1];
+            int* at = &due[(size_t)(k * stride)];
+            for (int i = range[k].veh; i < range[k + 1].veh; ++i) at[h->dep[i]]++;
+            for (int t = 1; t < stride; ++t) at[t] += at[t - 1];
+        }
+    }
+    if (nv > h->small_limit) {
+        // A trip's usual time is 1.25 times its time at free-flow speed and, with every node flashing red, 8 s a node more
+        // (stopping, standing and starting).  On the 10x10 grid with 350 to 2,500 vehicles on the road the median
+        // trip takes 1.13 to 1.38 times; flashing red 1.66 to 1.80 times, or 9.5 to 11.6 s an edge of 14.4 s more.
+        std::vector<int> leave(h->n_veh);
+        long long last = stride;
+        for (int i = 0; i < h->n_veh; ++i) {
+            double s = 0.0;
+            for (int64_t q = h->roff[i]; q < h->roff[i + 1]; ++q) {
+                const int e = h->redges[q];
+                s += 1.25 * net->length_m[e] / ((double)p->v0_factor[h->cls[i]] * net->speed_limit_mps[e]) +
+                     (d.imode == 1 ? 8.0 : 0.0);
+            }
+            leave[i] = (int)std::min(1e9, h->dep[i] + s / d.dt + 1.0);
+            last = std::max(last, (long long)leave[i] + 1);
+        }
+        h->small_len = (int)std::min(last, (16ll << 20) / ns);
+        h->small_road.assign((size_t)ns * h->small_len, 0);
+        for (int k = 0; k < ns; ++k) {
+            int* at = &h->small_road[(size_t)k * h->small_len];
+            for (int i = range[k].veh; i < range[k + 1].veh; ++i) {
+                at[h->dep[i]]++;
+                if (leave[i] < h->small_len) at[leave[i]]--;
+            }
+            for (int t = 1; t < h->small_len; ++t) at[t] += at[t - 1];
         }
     }
     Small& sm = h->sm;
     sm.n_scen = ns;
     sm.range = h->upload(range.data(), range.size());
-    sm.due = ns > 1 ? h->upload(h->small_due.data(), h->small_due.size()) : d.due;
-    sm.due_stride = ns > 1 ? stride : 0;
+    sm.due = ns > 1 ? h->upload(due.data(), due.size()) : d.due;
+    sm.due_stride = ns > 1 ? (int)stride : 0;
     sm.q0 = h->iow.q0;
     if (ns > 1) {
         const size_t NV = (size_t)std::max(h->n_veh, 1);
@@ -460,42 +492,49 @@ void plan_small(sim_handle* h, const std::vector<SmallRange>& range, long long m
     sm.cap = cap;
     sm.lanes = lanes;
     sm.nodes = nodes;
-    if (nv > kSmallActive) {
+    if (nv > h->small_limit) {
         void* dp = nullptr;
-        HIP_OK(hipHostMalloc((void**)&h->arrived, sizeof(int) * (size_t)ns, hipHostMallocDefault));
-        HIP_OK(hipHostGetDevicePointer(&dp, h->arrived, 0));
-        for (int k = 0; k < ns; ++k) h->arrived[k] = 0;
-        sm.arrived = (int*)dp;
+        HIP_OK(hipHostMalloc((void**)&h->road, sizeof(*h->road) * (size_t)ns, hipHostMallocDefault));
+        HIP_OK(hipHostGetDevicePointer(&dp, h->road, 0));
+        for (int k = 0; k < ns; ++k) h->road[k] = 0;
+        sm.road = (unsigned long long*)dp;
     }
     h->small = true;
 }
 
+// A state by vehicle id passes by (read or written, nothing in flight): what
+// is on the road in each scenario.
+void note_road(sim_handle* h, const uint8_t* status, int t) {
+    if (!h->road) return;
+    for (int k = 0; k < h->sm.n_scen; status += h->small_n[k++])
+        h->road[k] = (unsigned long long)(uint32_t)t << 32 |
+                     (uint32_t)std::count(status, status + h->small_n[k], (uint8_t)kActive);
+}
+
 // How many of the next `want` steps k_small_steps should take.  One workgroup
-// stages a scenario's vehicles tile by tile, so it is the faster way only
-// while a scenario has few on the road.  Known without waiting for the device:
-// at most the vehicles due by then less those that had arrived when the last
-// launch to finish wrote its count.
+// stages a scenario's vehicles, so it is the faster way only while a scenario
+// has few on the road: those last known to be there, and from then on what
+// enters and leaves if every trip takes its usual time.  Nothing waits for the
+// device, and a poor estimate costs time only: both ways give the same results.
 int small_steps_ahead(const sim_handle* h, int want) {
     if (!h->small) return 0;
     const int most = std::min(want, kSmallSteps);
-    if (h->small_veh <= kSmallActive) return most;
-    const int ns = h->sm.n_scen, stride = h->small_max_dep + 1;
-    std::vector<int> here(ns);
-    for (int k = 0; k < ns; ++k) here[k] = ((volatile const int*)h->arrived)[k];
-    auto fits = [&](int s) {
-        for (int k = 0; k < ns; ++k)
-            if (h->small_n[k] > 0 &&
-                h->small_due[(size_t)k * stride + std::min(h->t + s - 1, stride - 1)] - here[k] > kSmallActive)
-                return false;
-        return true;
-    };
-    if (fits(most)) return most;
-    int lo = 0, hi = most;                        // fits(lo), not fits(hi)
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) / 2;
-        (fits(mid) ? lo : hi) = mid;
+    if (h->small_veh <= h->small_limit) return most;
+    const int ns = h->sm.n_scen, len = h->small_len;
+    std::vector<int> more(ns);                    // on the road beyond the usual
+    for (int k = 0; k < ns; ++k) {
+        const unsigned long long w = ((volatile const unsigned long long*)h->road)[k];
+        const long long at = std::min<long long>((long long)(w >> 32), len - 1);
+        more[k] = (int)(uint32_t)w - h->small_road[(size_t)k * len + at];
     }
-    return lo >= 64 ? lo : 0;
+    int ahead = 0;
+    for (int s = std::min(16, most);; s = std::min(s + 16, most)) {
+        const size_t at = (size_t)std::min<long long>((long long)h->t + s, len - 1);
+        for (int k = 0; k < ns; ++k)
+            if (h->small_road[(size_t)k * len + at] + more[k] > h->small_limit) return ahead >= 64 ? ahead : 0;
+        ahead = s;
+        if (s == most) return most;
+    }
 }
 
 void launch_small(sim_handle* h, const Dev& d, int steps) {
@@ -903,7 +942,7 @@ sim_status create_impl(const sim_network* net, const sim_routes* r, const sim_id
                 for (int k = 0; k < ns && whole; ++k)
                     for (int i = range[k].veh; i < range[k + 1].veh; ++i)
                         whole = whole && h->redges[h->roff[i]] >= range[k].edge;
-                if (whole && range[ns].veh == N) plan_small(h, range, max_edge);
+                if (whole && range[ns].veh == N) plan_small(h, net, p, range, max_edge);
             }
             HIP_OK(hipDeviceSynchronize());
             capture_graph(h);
@@ -1138,6 +1177,7 @@ sim_status sim_read_state(sim_handle* h, sim_state* o) {
         HIP_OK(hipStreamSynchronize(h->stream));
         if (std::count(status, status + N, (uint8_t)kActive) != pin.head->n_act)
             throw Fail{SIM_EDEVICE, "corrupt layout: an active vehicle has no slot"};
+        note_road(h, status, pin.head->t);
         if (o->counters)
             for (int k = 0; k < cNumCounters; ++k) o->counters[k] = (int64_t)pin.head->counters[k];
         o->t = pin.head->t;
@@ -1191,12 +1231,7 @@ sim_status sim_write_state(sim_handle* h, const sim_state* in) {
         HIP_OK(hipStreamSynchronize(s));
         if (pin.head->bad) explain_bad_state(h, in);
         h->t = in->t;
-        if (h->arrived) {
-            std::vector<int> arr(h->sm.n_scen, 0);
-            for (int k = 0, i = 0; k < h->sm.n_scen; ++k)
-                for (const int end = i + h->small_n[k]; i < end; ++i) arr[k] += in->status[i] == kArrived;
-            for (int k = 0; k < h->sm.n_scen; ++k) h->arrived[k] = arr[k];
-        }
+        note_road(h, in->status, in->t);
         for (void* p : h->snaps) h->al.put(p);
         h->snaps.clear();
         h->rec_broken = (in->t != 0);
@@ -1267,8 +1302,15 @@ sim_status sim_backward(sim_handle* h, const double* dL_dmean_tt, double* dL_dpa
             if (!std::isfinite(dL_dmean_tt[e])) throw Fail{SIM_EINVAL, fmt("dL_dmean_tt[%d] is not finite", e)};
             if (cnt[e]) w[e] = dL_dmean_tt[e] / (double)cnt[e];
         }
-        // a small network: one launch per segment for the traced re-run and one for its reverse sweep
-        const bool small = h->small && h->sm.n_scen == 1 && h->small_veh <= kSmallActive;
+        // a small network: one launch per segment for the traced re-run and one for its reverse sweep, unless there
+        // were many on the road (on average over the run, which is the same for any checkpoint interval)
+        bool small = h->small && h->sm.n_scen == 1;
+        if (small && h->small_veh > kSmallBwActive) {
+            std::vector<unsigned long long> sum(kCounterCopies);
+            HIP_OK(hipMemcpy(sum.data(), h->d.counters + (size_t)cActiveSum * kCounterCopies, 8 * sum.size(),
+                             hipMemcpyDeviceToHost));
+            small = std::accumulate(sum.begin(), sum.end(), 0ull) <= (unsigned long long)kSmallBwActive * T;
+        }
         // parameter sums: one set per workgroup, or per thread of the one workgroup
         const int gbw = small ? kSmallBwNT : std::max(1, std::min(256, (N + kNT - 1) / kNT));
         double* dw = (double*)get(8 * (size_t)E);

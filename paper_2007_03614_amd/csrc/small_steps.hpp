@@ -26,7 +26,15 @@ constexpr int kSmallNodes = 1024;
 constexpr int kSmallSteps = 1024;        // steps of one launch at most
 constexpr int kSmallWords = kSmallSteps / 64;
 constexpr int kSmallScen = 256;          // scenarios at most: one workgroup per CU
-constexpr int kSmallActive = 3072;       // a scenario's vehicles on the road at most (a bound, see small_steps_ahead)
+// Vehicles on the road up to which one workgroup is the faster way: two a thread, or three where it runs that many
+// scenarios side by side (small_steps_ahead says how many there are expected to be).  us a step, the four launches
+// and the one, 1,000 and 1,100 vehicles: 10x10 grid 22.2 and 20.9, 22.5 and 24.9; 16x16 streets of one lane 18.9 and
+// 15.1, 19.3 and 18.3; 6x6 of three lanes 21.9 and 19.5, 21.7 and 23.6; a ring of 16 km 17.4 and 12.9, 17.2 and
+// 15.9; at 2,900 it takes twice their time.  32 grids of 1,000 and of 1,200: 25.5 and 22.5, 25.4 and 26.9; 64 of 1,400
+// and of 1,600 (two tiles): 29.8 and 27.3, 32.8 and 37.7; 128 of 1,400: 34.1 and 27.9.
+constexpr int kSmallActive = 2 * kSmallNT;
+constexpr int kSmallActiveMany = 3 * kSmallNT;
+constexpr int kSmallMany = 64;
 
 struct SmallRange {                      // what scenario k owns starts here (and ends at the next one's)
     int edge, lane, queue, node, veh;
@@ -43,7 +51,8 @@ struct Small {
     unsigned long long* moved;           // ensembles: [n_scen][kSmallWords] steps in which a vehicle moved
     unsigned long long* active;          //   and steps that began with one
     int* late;                           // ensembles: [n_scen][kSmallSteps] vehicles due less those that have departed
-    int* arrived;                        // host memory: [n_scen] arrivals so far (null: not wanted)
+    unsigned long long* road;            // host memory: [n_scen] vehicles on the road after the launch | step << 32
+                                         //   (null: not wanted)
     int cap, lanes, nodes;               // tile capacity (a multiple of 4), and the tables' entries in LDS
 };
 
@@ -260,7 +269,7 @@ __global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps)
         atomicAdd(&d.counters[cActiveSum * kCounterCopies], act_sum);
         if (denied) atomicAdd(&d.counters[cInsertDenied * kCounterCopies], denied);
         atomicAdd(&d.ctl->n_departed, dep - dep0);
-        if (sm.arrived) sm.arrived[k] = dep - n;
+        if (sm.road) sm.road[k] = (unsigned long long)(uint32_t)(t0 + nsteps) << 32 | (uint32_t)n;
         if (alone) {
             if (grid_steps) d.counters[cGridlock * kCounterCopies] += grid_steps;
             d.ctl->stall_run = run;
@@ -348,6 +357,9 @@ __global__ void __launch_bounds__(kSmallNT) k_small_gather(Dev d, Small sm, int 
 // road is never read again.  The lists of look-ahead records are in LDS, the
 // parts in device memory, gpart: [5 * n_classes][kSmallBwNT], each thread's own.
 constexpr int kSmallBwNT = 512;
+// Vehicles on the road at most, on average over the run.  The re-run and the sweep of 1,200 steps with 700, 1,150, 1,350
+// and 1,700 on the road, three kernels a step 50, 52, 53 and 54 ms, in one workgroup 34, 45, 51 and 62.
+constexpr int kSmallBwActive = 1536;
 
 template <int NC>
 __global__ void __launch_bounds__(kSmallBwNT) k_small_backward(Dev d, const TraceRec* trace, size_t stride,
