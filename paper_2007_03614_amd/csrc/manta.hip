@@ -926,6 +926,10 @@ sim_status create_impl(const sim_network* net, const sim_routes* r, const sim_id
                 w.qmin = h->dev<int>(std::max(NQ, 1));
                 w.qmax = h->dev<int>(std::max(NQ, 1));
                 HIP_OK(hipMemset(w.cnt, 0, sizeof(int) * (size_t)NL));
+                // (vehicles of a lane that holds at most kTileIndexMax are at least 511/512 of a length apart in
+                // binary32; a longer lane has room for every vehicle there is)
+                const double longest = *std::max_element(h->L.begin(), h->L.end());
+                w.lane_max = (int)std::min<double>(N, 1.01 * longest / len_min + 2.0);
                 h->io_dev = h->dev<char>(state_io_at(nullptr, N, nullptr));
             }
             {   // scenarios: edges, lanes, queues, nodes and vehicles in one piece each
@@ -1219,10 +1223,14 @@ sim_status sim_write_state(sim_handle* h, const sim_state* in) {
         hipLaunchKernelGGL(k_io_check, gv, b, 0, s, d, h->iow, dev);
         const int block = 1 << d.lane_shift;
         hipLaunchKernelGGL(block == kManyBlock ? k_io_lanes<kManyBlock> : k_io_lanes<kCommitNT>, dim3(h->n_blk), dim3(block), 0,
-                           s, h->iow);
+                           s, h->iow, dev.head);
         hipLaunchKernelGGL(k_io_blocks, dim3(1), dim3(kBigNT), 0, s, d, h->iow, dev.head);
         hipLaunchKernelGGL(k_io_place, gv, b, 0, s, d, h->iow, dev);
-        hipLaunchKernelGGL(k_io_rank, gv, b, 0, s, d, h->iow, dev, B);
+        const bool sorted = h->iow.lane_max > kIoLong;
+        if (sorted)
+            hipLaunchKernelGGL(k_io_sort, dim3(std::min(4096, (N + kIoChunk - 1) / kIoChunk)), dim3(kIoChunk / 2), 0, s, d,
+                               h->iow, dev);
+        hipLaunchKernelGGL(k_io_rank, gv, b, 0, s, d, h->iow, dev, B, sorted);
         hipLaunchKernelGGL(k_io_verify, gv, b, 0, s, d, h->iow, dev, B);
         hipLaunchKernelGGL(k_io_apply, grid(std::max({(long long)N, (long long)h->n_lanes, (long long)d.n_nodes})), b, 0,
                            s, d, h->iow, dev, B, S);

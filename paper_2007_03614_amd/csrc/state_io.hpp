@@ -64,6 +64,7 @@ struct IoWork {
     const int* q0;            // [queue + 1] first index of each departure queue
     int* list;                // [vehicle] active vehicles by lane, unordered within
     int* cnt;                 // [lane] vehicles still to be placed; zero between calls
+    int lane_max;             // vehicles that a lane can hold without an overlap, at most
     int* off;                 // [lane] first slot, relative to the lane's block
     int* blk;                 // [commit block] vehicles, then first slot
     int* qmin;                // [queue] first index that still waits, last that has left
@@ -144,38 +145,81 @@ __global__ void __launch_bounds__(kNT) k_io_clear(IoWork w, int nq) {
     }
 }
 
+// The vehicles of a wavefront that share a key (their lane, their queue), one
+// key after another: f(key, the set of them), up to kIoKeys keys; returns the
+// set left over.  One atomic for each such group: 32,000 atomics on the one
+// counter of a lane or queue take 0.35 ms.  (All lanes of the wavefront call.)
+constexpr int kIoKeys = 2;
+template <class F>
+__device__ inline unsigned long long io_groups(bool have, int key, F&& f) {
+    unsigned long long todo = __ballot(have);
+    for (int r = 0; r < kIoKeys && todo != 0ull; ++r) {
+        const int k = __builtin_amdgcn_readlane(key, __ffsll((long long)todo) - 1);
+        const unsigned long long m = __ballot(have && key == k);
+        f(k, m);
+        todo &= ~m;
+    }
+    return todo;
+}
+
 // Every check of one vehicle's fields, its lane's count and its queue's bounds.
 __global__ void __launch_bounds__(kNT) k_io_check(Dev d, IoWork w, StateIo in) {
     int left = 0;
     bool bad = false;
-    for (int i = blockIdx.x * kNT + threadIdx.x; i < d.n_veh; i += gridDim.x * kNT) {
-        const uint8_t st = in.status[i];
-        const int cur = in.cursor[i];
-        const int4 vq = d.vq[i];
-        if (st == kWaiting) atomicMin(&w.qmin[vq.x], vq.y);
-        else atomicMax(&w.qmax[vq.x], vq.y);
-        left += st != kWaiting;
-        bool ok = st <= kArrived && cur >= 0 && cur < d.roff[i + 1] - d.roff[i];
-        if (ok && st == kActive) {
-            const int e = route_edge_at(d, w, i, cur), l = in.lane[i], ww = in.ww[i];
-            const EdgeC c = d.ec[e];
-            const float x = in.x[i], v = in.v[i];
-            ok = in.edge[i] == e && l >= 0 && l < c.lanes && x >= 0.0f && x <= c.L && v >= 0.0f && v < INFINITY &&
-                 ww >= 0 && ww <= kPatience;
-            if (ok) atomicAdd(&w.cnt[c.lane_base + l], 1);
+    const int lane = threadIdx.x & 63;
+    for (int i0 = blockIdx.x * kNT; i0 < d.n_veh; i0 += gridDim.x * kNT) {
+        const int i = i0 + threadIdx.x;
+        const bool have = i < d.n_veh;
+        int4 vq = make_int4(0, 0, 0, 0);
+        int waits = -1, gone = -1;                 // place in its queue from the end, or from the front
+        int gl = -1;
+        if (have) {
+            const uint8_t st = in.status[i];
+            const int cur = in.cursor[i];
+            vq = d.vq[i];
+            if (st == kWaiting) waits = INT_MAX - vq.y;
+            else gone = vq.y;
+            left += st != kWaiting;
+            bool ok = st <= kArrived && cur >= 0 && cur < d.roff[i + 1] - d.roff[i];
+            if (ok && st == kActive) {
+                const int e = route_edge_at(d, w, i, cur), l = in.lane[i], ww = in.ww[i];
+                const EdgeC c = d.ec[e];
+                const float x = in.x[i], v = in.v[i];
+                ok = in.edge[i] == e && l >= 0 && l < c.lanes && x >= 0.0f && x <= c.L && v >= 0.0f && v < INFINITY &&
+                     ww >= 0 && ww <= kPatience;
+                if (ok) gl = c.lane_base + l;
+            }
+            bad = bad || !ok;
         }
-        bad = bad || !ok;
+        unsigned long long rest = io_groups(have, vq.x, [&](int q, unsigned long long m) {
+            const bool in_q = (m >> lane) & 1ull;
+            const int a = __builtin_amdgcn_readlane(wave_incl_max(in_q ? waits : -1), 63);
+            const int b = __builtin_amdgcn_readlane(wave_incl_max(in_q ? gone : -1), 63);
+            if (lane == 0 && a >= 0) atomicMin(&w.qmin[q], INT_MAX - a);
+            if (lane == 0 && b >= 0) atomicMax(&w.qmax[q], b);
+        });
+        if ((rest >> lane) & 1ull) {
+            if (waits >= 0) atomicMin(&w.qmin[vq.x], vq.y);
+            else atomicMax(&w.qmax[vq.x], vq.y);
+        }
+        rest = io_groups(gl >= 0, gl, [&](int g, unsigned long long m) {
+            if (lane == 0) atomicAdd(&w.cnt[g], (int)__popcll(m));
+        });
+        if ((rest >> lane) & 1ull) atomicAdd(&w.cnt[gl], 1);
     }
     left = (int)__ockl_wfred_add_u32((unsigned)left);
-    if ((threadIdx.x & 63) == 0 && left) atomicAdd(&in.head->departed, left);
+    if (lane == 0 && left) atomicAdd(&in.head->departed, left);
     if (bad) in.head->bad = 1;
 }
 
+// A lane with more vehicles than it can hold has two that overlap: the state
+// is refused here, before anything is done for each pair of a lane's vehicles.
 template <int NT>
-__global__ void __launch_bounds__(NT) k_io_lanes(IoWork w) {
+__global__ void __launch_bounds__(NT) k_io_lanes(IoWork w, IoHead* head) {
     __shared__ Scan4 wsh4[NT / 64];
     const int gl = blockIdx.x * NT + threadIdx.x;
     const int c = w.cnt[gl];
+    if (c > w.lane_max) head->bad = 1;
     const Scan4 r = wg_exclusive_scan4<NT>(Scan4{c, -1, -1, -1}, wsh4);
     w.off[gl] = r.s;
     if (threadIdx.x == NT - 1) w.blk[blockIdx.x] = r.s + c;
@@ -197,34 +241,118 @@ __device__ inline int io_start(const Dev& d, const IoWork& w, int gl, int n_act)
 // is refused in the end; here its vehicles that passed are placed all the
 // same, which takes every lane's count back to zero).
 __global__ void __launch_bounds__(kNT) k_io_place(Dev d, IoWork w, StateIo in) {
-    for (int i = blockIdx.x * kNT + threadIdx.x; i < d.n_veh; i += gridDim.x * kNT) {
-        const int cur = in.cursor[i];
-        if (in.status[i] != kActive || cur < 0 || cur >= d.roff[i + 1] - d.roff[i]) continue;
-        const int e = route_edge_at(d, w, i, cur), l = in.lane[i], ww = in.ww[i];
-        const EdgeC c = d.ec[e];
-        const float x = in.x[i], v = in.v[i];
-        if (in.edge[i] != e || l < 0 || l >= c.lanes || !(x >= 0.0f && x <= c.L) || !(v >= 0.0f && v < INFINITY) ||
-            ww < 0 || ww > kPatience)
-            continue;
-        const int gl = c.lane_base + l;
-        w.list[w.blk[gl >> d.lane_shift] + w.off[gl] + atomicSub(&w.cnt[gl], 1) - 1] = i;
+    const int lane = threadIdx.x & 63;
+    for (int i0 = blockIdx.x * kNT; i0 < d.n_veh; i0 += gridDim.x * kNT) {
+        const int i = i0 + threadIdx.x;
+        int gl = -1;
+        if (i < d.n_veh && in.status[i] == kActive) {
+            const int cur = in.cursor[i];
+            if (cur >= 0 && cur < d.roff[i + 1] - d.roff[i]) {
+                const int e = route_edge_at(d, w, i, cur), l = in.lane[i], ww = in.ww[i];
+                const EdgeC c = d.ec[e];
+                const float x = in.x[i], v = in.v[i];
+                if (in.edge[i] == e && l >= 0 && l < c.lanes && x >= 0.0f && x <= c.L && v >= 0.0f && v < INFINITY &&
+                    ww >= 0 && ww <= kPatience)
+                    gl = c.lane_base + l;
+            }
+        }
+        int at = 0;                                // vehicles of the lane up to this one
+        const unsigned long long rest = io_groups(gl >= 0, gl, [&](int g, unsigned long long m) {
+            const int n = (int)__popcll(m);
+            int last = 0;
+            if (lane == 0) last = atomicSub(&w.cnt[g], n);
+            last = __builtin_amdgcn_readfirstlane(last);
+            if ((m >> lane) & 1ull) at = last - bits_below(m);
+        });
+        if ((rest >> lane) & 1ull) at = atomicSub(&w.cnt[gl], 1);
+        if (gl >= 0) w.list[w.blk[gl >> d.lane_shift] + w.off[gl] + at - 1] = i;
+    }
+}
+
+// On lanes of more than kIoLong vehicles a rank is looked up in sorted pieces:
+// the list in chunks of kIoChunk, each by lane and then front first, in LDS.
+// (Comparing with every vehicle of the lane takes 0.17 us each: a state of
+// 32,000 vehicles on one lane is written in 5.4 ms, so in 0.35, and sorted on the
+// host in 2.4.  Chunks without such a lane are left as they are, and networks
+// that cannot have one do not launch this.)
+constexpr int kIoLong = 256;
+constexpr int kIoChunk = 1024;
+
+struct IoKey {                // order within a chunk: first slot of the lane, then x and id, both descending
+    int lo;
+    float x;
+    int id;
+};
+__device__ inline bool io_before(const IoKey& a, const IoKey& b) {
+    return a.lo != b.lo ? a.lo < b.lo : a.x != b.x ? a.x > b.x : a.id > b.id;
+}
+
+__global__ void __launch_bounds__(kIoChunk / 2) k_io_sort(Dev d, IoWork w, StateIo in) {
+    __shared__ IoKey key[kIoChunk];
+    const int na = in.head->n_act, tid = threadIdx.x;
+    if (in.head->bad) return;
+    for (int c0 = blockIdx.x * kIoChunk; c0 < na; c0 += gridDim.x * kIoChunk) {
+        bool any = false;
+        for (int k = tid; k < kIoChunk; k += kIoChunk / 2) {
+            key[k] = IoKey{INT_MAX, 0.0f, 0};
+            if (c0 + k >= na) continue;
+            const int i = w.list[c0 + k], gl = d.ec[in.edge[i]].lane_base + in.lane[i], lo = io_start(d, w, gl, na);
+            key[k] = IoKey{lo, in.x[i], i};
+            any = any || io_start(d, w, gl + 1, na) - lo > kIoLong;
+        }
+        if (!__syncthreads_or(any)) continue;
+        for (int m = 2; m <= kIoChunk; m *= 2)                  // bitonic
+            for (int h = m / 2; h > 0; h /= 2) {
+                const int k = 2 * tid - (tid & (h - 1));        // and its partner, h further
+                const IoKey a = key[k], b = key[k + h];
+                const bool up = (k & m) == 0;
+                if (up ? io_before(b, a) : io_before(a, b)) {
+                    key[k] = b;
+                    key[k + h] = a;
+                }
+                __syncthreads();
+            }
+        for (int k = tid; k < kIoChunk && c0 + k < na; k += kIoChunk / 2) w.list[c0 + k] = key[k].id;
+        __syncthreads();
     }
 }
 
 // Each vehicle's rank in its lane (front first: x, then id, descending) and its
-// record in layout B.
-__global__ void __launch_bounds__(kNT) k_io_rank(Dev d, IoWork w, StateIo in, Slots B) {
+// record in layout B.  sorted: k_io_sort has run.
+__global__ void __launch_bounds__(kNT) k_io_rank(Dev d, IoWork w, StateIo in, Slots B, bool sorted) {
     const int na = in.head->n_act;
+    if (in.head->bad) return;
     for (int s = blockIdx.x * kNT + threadIdx.x; s < na; s += gridDim.x * kNT) {
         const int i = w.list[s], e = in.edge[i], l = in.lane[i], cur = in.cursor[i];
         const float x = in.x[i];
         const int gl = d.ec[e].lane_base + l;
         const int lo = io_start(d, w, gl, na), hi = io_start(d, w, gl + 1, na);
-        int dst = lo;
-        for (int k = lo; k < hi; ++k) {
+        const auto ahead = [&](int k) {
             const int j = w.list[k];
             const float xj = in.x[j];
-            dst += (xj > x || (xj == x && j > i)) ? 1 : 0;
+            return xj > x || (xj == x && j > i);
+        };
+        int dst = lo;
+        if (sorted && hi - lo > kIoLong) {
+            // eight chunks' searches at once, so that their loads overlap
+            constexpr int kU = 8;
+            for (int c0 = lo / kIoChunk * kIoChunk; c0 < hi; c0 += kU * kIoChunk) {
+                int at[kU];                       // those before it, of the chunk's part of the lane, end here
+#pragma unroll
+                for (int u = 0; u < kU; ++u) at[u] = max(lo, c0 + u * kIoChunk);
+                for (int h = kIoChunk; h > 0; h /= 2) {
+#pragma unroll
+                    for (int u = 0; u < kU; ++u) {
+                        const int k = at[u] + h - 1;
+                        const bool in_part = k < min(hi, c0 + (u + 1) * kIoChunk);
+                        if (ahead(in_part ? k : lo) && in_part) at[u] += h;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kU; ++u) dst += at[u] - max(lo, c0 + u * kIoChunk);
+            }
+        } else {
+            for (int k = lo; k < hi; ++k) dst += ahead(k) ? 1 : 0;
         }
         const uint32_t rw = d.rnext[d.roff[i] + cur];
         B.x[dst] = x;
@@ -241,6 +369,7 @@ __global__ void __launch_bounds__(kNT) k_io_rank(Dev d, IoWork w, StateIo in, Sl
 // queue are a prefix of it.
 __global__ void __launch_bounds__(kNT) k_io_verify(Dev d, IoWork w, StateIo in, Slots B) {
     const int na = in.head->n_act;
+    if (in.head->bad) return;
     for (int s = blockIdx.x * kNT + threadIdx.x; s < max(na, d.nq); s += gridDim.x * kNT) {
         bool bad = false;
         if (s > 0 && s < na && B.edge[s] == B.edge[s - 1] && m_lane(B.meta[s]) == m_lane(B.meta[s - 1]))
