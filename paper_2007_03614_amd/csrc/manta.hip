@@ -1959,9 +1959,7 @@ void shortest_routes_impl(B& b, const sim_network* net, const float* edge_cost, 
                 b.charge(4 * (size_t)(max_deg <= 4 ? 4 : 8) * V);
                 b.charge(4 * (size_t)(max_deg <= 4 ? 4 : 8) * V);
             }
-            double sum = 0.0;
-            for (int e = 0; e < E; ++e) sum += (double)edge_cost[e];
-            const float step = (float)(kRouteTreeStep * sum / E);
+            const float step = route_tree_step(edge_cost, E);
             std::vector<RouteOut> out(E);
             for (int k = 0; k < E; ++k) out[k] = RouteOut{net->edge_to[out_edge[k]], edge_cost[out_edge[k]]};
             const std::vector<RouteIn> in = route_in_records(net, edge_cost);

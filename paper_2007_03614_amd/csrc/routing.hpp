@@ -83,13 +83,48 @@ __global__ void __launch_bounds__(kRouteNT) k_route_dist(int V, const int* out_o
 constexpr int kRouteTreeNodes = 40400;  // 4 bytes each, and at least 512 entries in each of two lists, in 160 KiB
 constexpr int kRouteTreeDeg = 8;        // bounds the in-edge records by the network's own arrays
 constexpr size_t kRouteTreeLds = 163840 - 64;   // dynamic LDS of one workgroup at most
-// Threshold step, in mean edge costs: small steps rescan the labels for the
+// Threshold step, in mean edge costs (route_tree_step): small steps rescan the labels for the
 // nodes below the next threshold more often, large ones expand more nodes
 // twice.  200,000 routes on a 10,040-node city end to end: 8.9 ms at 3, 7.6 at
 // 8, 7.47 at 16, 7.42 at 24; a 40,000-node lattice 3.14, 3.10, 3.5 at 8, 16, 24.
 constexpr double kRouteTreeStep = 16.0;
+// Edges of more than kRouteTreeDear times the mean are not in it (closed roads, priced far above any time: with 1 %
+// of the edges at 1e6 s in the mean no threshold binds, and the city takes 14.7 ms, the lattice 10.7; without them 7.8
+// and 3.3, and 7.6 and 3.1 with no road closed).
+constexpr double kRouteTreeDear = 16.0;
 constexpr int kRouteTreeList = 1024;    // entries of a frontier list at most
 constexpr unsigned kLabelInf = (0x7f800000u << 1) | 1u;
+
+// The threshold step of n positive costs: kRouteTreeStep times the mean of those that are not dear against it.
+inline float route_tree_step(const float* cost, int n) {
+    constexpr int kU = 8;
+    double mean = 0.0;
+    float cut = INFINITY;
+    for (int pass = 0; pass < 4; ++pass) {
+        double part[kU] = {}, sum = 0.0;         // sums side by side, so that the additions overlap
+        float top[kU] = {}, most = 0.0f;
+        int in[kU] = {}, many = 0;
+        const auto take = [&](const float* from, int j) {
+            const float c = from[j] <= cut ? from[j] : 0.0f;
+            part[j] += c;
+            in[j] += c > 0.0f;
+            top[j] = c > top[j] ? c : top[j];
+        };
+        int e = 0;
+        for (; e + kU <= n; e += kU)
+            for (int j = 0; j < kU; ++j) take(cost + e, j);
+        for (int j = 0; e + j < n; ++j) take(cost + e, j);
+        for (int j = 0; j < kU; ++j) {
+            sum += part[j];
+            many += in[j];
+            most = top[j] > most ? top[j] : most;
+        }
+        mean = sum / many;
+        if (!((double)most > kRouteTreeDear * mean)) break;
+        cut = (float)(kRouteTreeDear * mean);
+    }
+    return (float)(kRouteTreeStep * mean);
+}
 
 // The in-edges of a node, four at a time: tails (-1 unused) and costs.  A node
 // with more links on: tail[3] = -2 - index of the next record.

@@ -93,7 +93,7 @@ void entry() {
 }
 }  // namespace
 
-extern "C" double route_tree_step() { return manta::kRouteTreeStep; }
+extern "C" float route_tree_step(const float* cost, int n) { return manta::route_tree_step(cost, n); }
 
 // order: 1 the lowest thread first, -1 the highest.  0, or -1 with the two source lines that threads wait at.
 extern "C" int route_tree(int nt, int order, int nd, int V, const void* in, const int* out_off, const void* out,

@@ -27,8 +27,12 @@ def lib(tmp_path_factory):
                            "-w", f'-DKERNELS="{d}/kernels.inc"', os.path.join(ROOT, "tests", "route_tree_host.cpp"),
                            "-o", so])
     L = ctypes.CDLL(so)
-    L.route_tree_step.restype = ctypes.c_double
+    L.route_tree_step.restype = ctypes.c_float
     return L
+
+
+def _step(lib, cost):
+    return lib.route_tree_step(cost.ctypes.data_as(ctypes.c_void_p), cost.size)
 
 
 IN = np.dtype([("tail", np.int32, 4), ("cost", np.float32, 4)])
@@ -64,10 +68,9 @@ def _run(lib, net, cost, queries, nt, order):
     tab = np.full((dests.size, V), -9, np.int32)
     length = np.full(len(queries), -9, np.int32)
     jumps, lines = ctypes.c_int(0), (ctypes.c_int * 2)()
-    step = np.float32(lib.route_tree_step() * float(np.sum(cost.astype(np.float64))) / net.n_edges)
     p = lambda a: a.ctypes.data_as(ctypes.c_void_p)
     rc = lib.route_tree(nt, order, dests.size, V, p(rec), p(off), p(out), p(dests), min(V + 1, 1024),
-                        ctypes.c_float(step), p(tab), p(qoff), p(qord), p(origin), p(length), ctypes.byref(jumps), lines)
+                        ctypes.c_float(_step(lib, cost)), p(tab), p(qoff), p(qord), p(origin), p(length), ctypes.byref(jumps), lines)
     assert rc == 0, f"threads wait at the barriers of lines {lines[0]} and {lines[1]}"
     routes = []
     for i, (o, d) in enumerate(queries):
@@ -111,3 +114,19 @@ def test_gaps_above_the_threshold_step(lib, oracle_mod, kind, order):
     assert jumps > 0 or kind == "jams"
     for (o, d), r in zip(queries, routes):
         assert r == oracle_mod.route(net, cost, o, d)
+
+
+@pytest.mark.parametrize("price", [1e6, 1e30])
+def test_step_without_closed_roads(lib, price):
+    """Closed roads leave the threshold step as it is (to the mean's sampling), and costs without any are all in it."""
+    rng = np.random.default_rng(4)
+    for n in (1, 2, 5, 40000):
+        cost = rng.uniform(1.0, 40.0, n).astype(np.float32)
+        plain = _step(lib, cost)
+        assert plain == pytest.approx(16.0 * cost.mean(dtype=np.float64), rel=1e-6)
+        for share in (0.0, 0.01, 0.05):
+            c = cost.copy()
+            c[rng.permutation(n)[:int(share * n)]] = price
+            assert _step(lib, c) == pytest.approx(plain, rel=0.02)
+    two = np.concatenate([cost, [1e3, 1e5, 1e9]]).astype(np.float32)
+    assert _step(lib, two) == pytest.approx(plain, rel=0.02)
