@@ -89,7 +89,7 @@ __device__ inline void small_end_step(const Dev& d, int t) {
 template <int NT, bool kSpread>
 __global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps) {
     extern __shared__ __align__(16) char lds[];
-    __shared__ Scan4 wsh4[NT / 64];
+    __shared__ Totals wsh3[NT / 64];
     __shared__ int wsh[2 * (NT / 64)];
     __shared__ unsigned shc[cNumCounters];
     __shared__ ClassParams scp[16];
@@ -167,7 +167,7 @@ __global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps)
         // an ensemble's scenarios write no buffer that another may still read as its first layout
         const Slots B = alone ? d.s[(t + 1) & 1] : slots_at((nsteps - 1 - j) & 1 ? d.s[par0 ^ 1] : sm.extra, v0);
         if (d.trace && tid == 0) d.nact_hist[t % d.trace_period] = n;
-        tile_pieces<NT, kSpread, false>(d, tb, S, lds, sm.cap, 0, n, t, acc, wsh4, wsh, scp, dq, &smoved);
+        tile_pieces<NT, kSpread, false>(d, tb, S, lds, sm.cap, 0, n, t, acc, wsh3, wsh, scp, dq, &smoved);
         for (int i = tid; i < nl; i += NT) {       // (the tile's space is free after its last barrier)
             ex.vid[i] = ~0u;
             ex.n[i] = 0u;
@@ -224,9 +224,9 @@ __global__ void __launch_bounds__(NT) k_small_steps(Dev d, Small sm, int nsteps)
                 c = (p.stamp == t ? p.cnt : 0) - (tb.exit_stamp[i] == t ? 1 : 0) + (tb.enter_stamp[i] == t ? 1 : 0);
                 tb.lane_newcnt[i] = c;
             }
-            const Scan4 sc = wg_exclusive_scan4<NT>(Scan4{c, -1, -1, -1}, wsh4);
-            if (i < nl) tb.lane_off[i] = nnew + sc.s;
-            if (tid == NT - 1) stot = nnew + sc.s + c;
+            const int o = nnew + wg_exclusive_sum<NT>(c, wsh);
+            if (i < nl) tb.lane_off[i] = o;
+            if (tid == NT - 1) stot = o + c;
             __syncthreads();
             nnew = stot;
         }

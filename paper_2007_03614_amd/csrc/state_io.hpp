@@ -216,20 +216,20 @@ __global__ void __launch_bounds__(kNT) k_io_check(Dev d, IoWork w, StateIo in) {
 // is refused here, before anything is done for each pair of a lane's vehicles.
 template <int NT>
 __global__ void __launch_bounds__(NT) k_io_lanes(IoWork w, IoHead* head) {
-    __shared__ Scan4 wsh4[NT / 64];
+    __shared__ int wsh[NT / 64];
     const int gl = blockIdx.x * NT + threadIdx.x;
     const int c = w.cnt[gl];
     if (c > w.lane_max) head->bad = 1;
-    const Scan4 r = wg_exclusive_scan4<NT>(Scan4{c, -1, -1, -1}, wsh4);
-    w.off[gl] = r.s;
-    if (threadIdx.x == NT - 1) w.blk[blockIdx.x] = r.s + c;
+    const int o = wg_exclusive_sum<NT>(c, wsh);
+    w.off[gl] = o;
+    if (threadIdx.x == NT - 1) w.blk[blockIdx.x] = o + c;
 }
 
 __global__ void __launch_bounds__(kBigNT) k_io_blocks(Dev d, IoWork w, IoHead* head) {
-    __shared__ Scan4 wsh4[kBigNT / 64];
+    __shared__ int wsh[kBigNT / 64];
     __shared__ int tot;
     __shared__ int stage[kScanLdsMax];
-    const int n = scan_block_sums_staged<kBigNT>(w.blk, d.n_blk, w.blk, stage, kScanLdsMax, wsh4, &tot);
+    const int n = scan_block_sums_staged<kBigNT>(w.blk, d.n_blk, w.blk, stage, kScanLdsMax, wsh, &tot);
     if (threadIdx.x == 0) head->n_act = n;
 }
 

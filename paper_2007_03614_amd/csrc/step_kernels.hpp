@@ -407,21 +407,13 @@ __device__ inline int run_insert(const TileBuf& b, int lo, int hi, float x, uint
 }
 
 // ---- workgroup helpers ---------------------------------------------------
-struct Scan4 {
-    int s, a, b, c;     // s: sum; a, b, c: max
-};
-
-__device__ inline Scan4 scan4_op(Scan4 x, Scan4 y) {
-    return Scan4{x.s + y.s, max(x.a, y.a), max(x.b, y.b), max(x.c, y.c)};
-}
-
 // Inclusive wavefront scans with DPP moves (register to register, no LDS
 // round trip): Hillis-Steele over row shifts of 1, 2, 4 and 8 lanes within
 // each row of 16, then the last lane of row 0 broadcast into row 1 and of
 // row 2 into row 3 (row_bcast:15), then lane 31 into rows 2 and 3
 // (row_bcast:31).  A lane whose source is outside its row, or whose row is
 // masked off, takes the identity (the `old` operand).
-constexpr int kDppRowShr = 0x110, kDppRowBcast15 = 0x142, kDppRowBcast31 = 0x143, kDppWaveShr1 = 0x138;
+constexpr int kDppRowShr = 0x110, kDppRowBcast15 = 0x142, kDppRowBcast31 = 0x143;
 
 __device__ inline int wave_incl_sum(int x) {
     x += __builtin_amdgcn_update_dpp(0, x, kDppRowShr + 1, 0xf, 0xf, false);
@@ -460,36 +452,19 @@ __device__ inline int row_incl_max(int x) {
     return x;
 }
 
-// Exclusive workgroup scan of one Scan4 per thread (all NT threads take
-// part); wsh: NT/64 Scan4 in LDS, free again after the caller's next barrier.
-// The waves' totals are scanned by every wave at once, one per lane: a loop
-// over the waves before it would wait for one LDS read after another.
+// Exclusive workgroup scan of one int per thread (all NT threads take part);
+// wsh: NT/64 ints in LDS, free again after the caller's next barrier.  The
+// waves' totals are scanned by every wave at once, one per lane: a loop over the
+// waves before it would wait for one LDS read after another.
 template <int NT = kNT>
-__device__ inline Scan4 wg_exclusive_scan4(Scan4 v, Scan4* wsh) {
+__device__ inline int wg_exclusive_sum(int v, int* wsh) {
     static_assert(NT / 64 <= 16, "the waves' totals fill one row of lanes");
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    Scan4 inc;
-    inc.s = wave_incl_sum(v.s);
-    inc.a = wave_incl_max(v.a);
-    inc.b = wave_incl_max(v.b);
-    inc.c = wave_incl_max(v.c);
+    const int inc = wave_incl_sum(v);
     if (lane == 63) wsh[wave] = inc;
     __syncthreads();
-    const Scan4 tot = wsh[min(lane, NT / 64 - 1)];
-    Scan4 carry{0, -1, -1, -1};
-    const Scan4 upto{row_incl_sum(tot.s), row_incl_max(tot.a), row_incl_max(tot.b), row_incl_max(tot.c)};
-    if (wave > 0) {
-        carry.s = __builtin_amdgcn_readlane(upto.s, wave - 1);
-        carry.a = __builtin_amdgcn_readlane(upto.a, wave - 1);
-        carry.b = __builtin_amdgcn_readlane(upto.b, wave - 1);
-        carry.c = __builtin_amdgcn_readlane(upto.c, wave - 1);
-    }
-    Scan4 exc;
-    exc.s = inc.s - v.s;
-    exc.a = __builtin_amdgcn_update_dpp(-1, inc.a, kDppWaveShr1, 0xf, 0xf, false);   // lane 0 gets -1
-    exc.b = __builtin_amdgcn_update_dpp(-1, inc.b, kDppWaveShr1, 0xf, 0xf, false);
-    exc.c = __builtin_amdgcn_update_dpp(-1, inc.c, kDppWaveShr1, 0xf, 0xf, false);
-    return scan4_op(carry, exc);
+    const int upto = row_incl_sum(wsh[min(lane, NT / 64 - 1)]);
+    return inc - v + (wave > 0 ? __builtin_amdgcn_readlane(upto, wave - 1) : 0);
 }
 
 // Scans of flags, one element a thread: within the wavefront by counting and
@@ -502,30 +477,34 @@ __device__ inline int bits_below(unsigned long long m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// The totals of the wavefronts before this one (s: sum; a, b: maxima) and, in
-// all, of every wavefront; wsh written by the wavefronts, a barrier before.
+struct Totals {
+    int s, a, b;        // s: sum; a, b: maxima (-1: none)
+};
+
+// The totals of the wavefronts before this one and, in all, of every
+// wavefront; wsh written by the wavefronts, a barrier before.
 template <int NT>
-__device__ inline Scan4 totals_before(const Scan4* wsh, Scan4& all) {
+__device__ inline Totals totals_before(const Totals* wsh, Totals& all) {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    Scan4 r{0, -1, -1, -1};
+    Totals r{0, -1, -1};
     all = r;
     if (NT / 64 <= 4) {
 #pragma unroll
         for (int w = 0; w < NT / 64; ++w) {
-            const Scan4 x = wsh[w];
-            if (w < wave) r = Scan4{r.s + x.s, max(r.a, x.a), max(r.b, x.b), -1};
-            all = Scan4{all.s + x.s, max(all.a, x.a), max(all.b, x.b), -1};
+            const Totals x = wsh[w];
+            if (w < wave) r = Totals{r.s + x.s, max(r.a, x.a), max(r.b, x.b)};
+            all = Totals{all.s + x.s, max(all.a, x.a), max(all.b, x.b)};
         }
         return r;
     }
-    // many wavefronts: scanned one a lane, as in wg_exclusive_scan4
-    const Scan4 x = wsh[min((int)(threadIdx.x & 63), NT / 64 - 1)];
-    const Scan4 upto{row_incl_sum(x.s), row_incl_max(x.a), row_incl_max(x.b), -1};
-    all = Scan4{__builtin_amdgcn_readlane(upto.s, NT / 64 - 1), __builtin_amdgcn_readlane(upto.a, NT / 64 - 1),
-                __builtin_amdgcn_readlane(upto.b, NT / 64 - 1), -1};
+    // many wavefronts: scanned one a lane, as in wg_exclusive_sum
+    const Totals x = wsh[min((int)(threadIdx.x & 63), NT / 64 - 1)];
+    const Totals upto{row_incl_sum(x.s), row_incl_max(x.a), row_incl_max(x.b)};
+    all = Totals{__builtin_amdgcn_readlane(upto.s, NT / 64 - 1), __builtin_amdgcn_readlane(upto.a, NT / 64 - 1),
+                 __builtin_amdgcn_readlane(upto.b, NT / 64 - 1)};
     if (wave > 0)
-        r = Scan4{__builtin_amdgcn_readlane(upto.s, wave - 1), __builtin_amdgcn_readlane(upto.a, wave - 1),
-                  __builtin_amdgcn_readlane(upto.b, wave - 1), -1};
+        r = Totals{__builtin_amdgcn_readlane(upto.s, wave - 1), __builtin_amdgcn_readlane(upto.a, wave - 1),
+                   __builtin_amdgcn_readlane(upto.b, wave - 1)};
     return r;
 }
 
@@ -799,7 +778,7 @@ __device__ inline void finish_pending(const TileBuf& b, int q, int dir, const fl
 // loaded already (ahead), as far as they reach.
 template <int NT, bool kSpread, bool kAhead = false>
 __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slots& S, const TileBuf& b, int a0, int n,
-                                    int t, CounterAcc& acc, Scan4* wsh4, const ClassParams* scp, const DrawQ& dq,
+                                    int t, CounterAcc& acc, Totals* wsh3, const ClassParams* scp, const DrawQ& dq,
                                     int* smoved, const AheadRecord& ahead = AheadRecord{}) {
     const int tid = threadIdx.x;
     const int dir = (t % 2 == 0) ? -1 : 1;
@@ -867,16 +846,16 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
     // ---- runs of S_t (tile order: edge, lane, then x and id descending)
     const int lane = tid & 63, wave = tid >> 6;
     {
-        Scan4 from{0, -1, -1, -1};                // runs and the last edge start before the round
+        Totals from{0, -1, -1};                   // runs and the last edge start before the round
         for (int base = 0; base < n; base += NT) {
             const int q = base + tid;
             const uint32_t el = q < n ? b.el[q] : 0u, before = q < n && q > 0 ? b.el[q - 1] : ~0u;
             const unsigned long long runs = __ballot(q < n && el != before);
             const unsigned long long edges = __ballot(q < n && el >> 4 != before >> 4);
-            if (lane == 0) wsh4[wave] = Scan4{(int)__popcll(runs), edges ? q + last_bit(edges) : -1, -1, -1};
+            if (lane == 0) wsh3[wave] = Totals{(int)__popcll(runs), edges ? q + last_bit(edges) : -1, -1};
             __syncthreads();
-            Scan4 all;
-            const Scan4 r = totals_before<NT>(wsh4, all);
+            Totals all;
+            const Totals r = totals_before<NT>(wsh3, all);
             if (q < n) {
                 const bool start = (runs >> lane) & 1ull;
                 const int k = from.s + r.s + bits_below(runs) + (start ? 1 : 0) - 1;
@@ -887,8 +866,8 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
                 if (q == n - 1) b.run_st[k + 1] = (uint32_t)n;
             }
             if (base + NT >= n) break;
-            from = Scan4{from.s + all.s, max(from.a, all.a), -1, -1};
-            __syncthreads();                      // wsh4 is reused by the next round
+            from = Totals{from.s + all.s, max(from.a, all.a), -1};
+            __syncthreads();                      // wsh3 is reused by the next round
         }
         if (n == 0 && tid == 0) b.run_st[0] = 0u;
     }
@@ -1031,7 +1010,7 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
 
     // ---- movers before each vehicle, and the last mover and stayer up to it
     {
-        Scan4 from{0, -1, -1, -1};
+        Totals from{0, -1, -1};
         for (int base = 0; base < n; base += NT) {
             const int q = base + tid;
             // the decisions waiting for noise are finished by the thread that scans them
@@ -1039,11 +1018,11 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
             const int mv = q < n ? b.pm[q] >> 16 : 0;
             const unsigned long long movers = __ballot(q < n && mv), stayers = __ballot(q < n && !mv);
             if (lane == 0)
-                wsh4[wave] = Scan4{(int)__popcll(movers), movers ? q + last_bit(movers) : -1,
-                                   stayers ? q + last_bit(stayers) : -1, -1};
+                wsh3[wave] = Totals{(int)__popcll(movers), movers ? q + last_bit(movers) : -1,
+                                   stayers ? q + last_bit(stayers) : -1};
             __syncthreads();                      // na, nb (mpref, lml) are read up to here
-            Scan4 all;
-            const Scan4 r = totals_before<NT>(wsh4, all);
+            Totals all;
+            const Totals r = totals_before<NT>(wsh3, all);
             if (q < n) {
                 const int s = from.s + r.s + bits_below(movers);
                 const unsigned long long m = movers & bits_upto(lane), st = stayers & bits_upto(lane);
@@ -1054,8 +1033,8 @@ __device__ inline void process_tile(const Dev& d, const LaneTabs& tb, const Slot
                 if (q == n - 1) b.mpref[n] = s + mv;
             }
             if (base + NT >= n) break;
-            from = Scan4{from.s + all.s, max(from.a, all.a), max(from.b, all.b), -1};
-            __syncthreads();                      // wsh4 is reused by the next round
+            from = Totals{from.s + all.s, max(from.a, all.a), max(from.b, all.b)};
+            __syncthreads();                      // wsh3 is reused by the next round
         }
         if (n == 0 && tid == 0) b.mpref[0] = 0;
     }
@@ -1340,7 +1319,7 @@ __device__ inline int tile_window(const Dev& d, int n) {
 template <bool kSpread>
 __device__ inline void tile_step(const Dev& d) {
     __shared__ __align__(16) char lds[kTileCapLds * kTileBytesPerVeh + 64];
-    __shared__ Scan4 wsh4[kTileNT / 64];
+    __shared__ Totals wsh3[kTileNT / 64];
     __shared__ int wsh[4 * (kTileNT / 64)];
     __shared__ int sbig;                        // index of a tile listed as big
     __shared__ unsigned shc[cNumCounters];
@@ -1394,7 +1373,7 @@ __device__ inline void tile_step(const Dev& d) {
             return;
         }
         if (cnt <= kTileCapLds) {
-            process_tile<kTileNT, kSpread, true>(d, lane_tabs(d), S, carve(lds, kTileCapLds), a0, cnt, t, acc, wsh4, scp,
+            process_tile<kTileNT, kSpread, true>(d, lane_tabs(d), S, carve(lds, kTileCapLds), a0, cnt, t, acc, wsh3, scp,
                                                  dq, &smoved, ah);
         } else {
             if (threadIdx.x == 0) {
@@ -1451,7 +1430,7 @@ __global__ void __launch_bounds__(kTileNT) __attribute__((amdgpu_waves_per_eu(6)
 // from the workgroup's global-memory scratch (kScratch: there may be one).
 template <int NT, bool kSpread, bool kScratch>
 __device__ __forceinline__ void tile_pieces(const Dev& d, const LaneTabs& tb, const Slots& S, char* lds, int cap,
-                                            int a0, int a1, int t, CounterAcc& acc, Scan4* wsh4, int* wsh,
+                                            int a0, int a1, int t, CounterAcc& acc, Totals* wsh3, int* wsh,
                                             const ClassParams* scp, const DrawQ& dq, int* smoved) {
     const int32_t* edge = S.edge;
     int pos = a0;
@@ -1480,10 +1459,10 @@ __device__ __forceinline__ void tile_pieces(const Dev& d, const LaneTabs& tb, co
         }
         const int cnt = end - pos;
         if (cnt <= cap) {
-            process_tile<NT, kSpread>(d, tb, S, carve(lds, cap), pos, cnt, t, acc, wsh4, scp, dq, smoved);
+            process_tile<NT, kSpread>(d, tb, S, carve(lds, cap), pos, cnt, t, acc, wsh3, scp, dq, smoved);
         } else if (kScratch && cnt <= d.big_cap) {
             char* mine = d.big + (size_t)blockIdx.x * tile_bytes(d.big_cap);
-            process_tile<NT, kSpread>(d, tb, S, carve(mine, d.big_cap), pos, cnt, t, acc, wsh4, scp, dq, smoved);
+            process_tile<NT, kSpread>(d, tb, S, carve(mine, d.big_cap), pos, cnt, t, acc, wsh3, scp, dq, smoved);
         } else if (threadIdx.x == 0) {             // more vehicles than the edge can physically hold
             atomicOr(&d.ctl->err, kErrTileTooBig);
         }
@@ -1495,7 +1474,7 @@ __device__ __forceinline__ void tile_pieces(const Dev& d, const LaneTabs& tb, co
 // of LDS.
 __device__ __forceinline__ void big_tiles(const Dev& d, int t, int par, int nbig) {
     __shared__ __align__(16) char lds[kBigCapLds * kTileBytesPerVeh + 64];
-    __shared__ Scan4 wsh4[kBigNT / 64];
+    __shared__ Totals wsh3[kBigNT / 64];
     __shared__ int wsh[kBigNT / 64];
     __shared__ unsigned shc[cNumCounters];
     __shared__ ClassParams scp[16];
@@ -1514,7 +1493,7 @@ __device__ __forceinline__ void big_tiles(const Dev& d, int t, int par, int nbig
     for (int k = blockIdx.x; k < nbig; k += gridDim.x) {
         const int a0 = d.big_list[2 * k], a1 = d.big_list[2 * k + 1];
         if (threadIdx.x == 0) atomicAdd(&d.ctl->big_updates, (unsigned long long)(a1 - a0));
-        tile_pieces<kBigNT, true, true>(d, lane_tabs(d), d.s[par], lds, kBigCapLds, a0, a1, t, acc, wsh4, wsh, scp, dq,
+        tile_pieces<kBigNT, true, true>(d, lane_tabs(d), d.s[par], lds, kBigCapLds, a0, a1, t, acc, wsh3, wsh, scp, dq,
                                   &smoved);
     }
     flush_counters_lds(d, acc, shc);
@@ -1953,7 +1932,7 @@ __device__ inline void flush_commit_counters(const Dev& d, const CounterAcc& acc
 // workgroup.
 __global__ void __launch_bounds__(kCommitNT) k_commit(Dev d) {
     __shared__ unsigned shc[cNumCounters];
-    __shared__ Scan4 wsh4[kCommitNT / 64];
+    __shared__ int wsh[kCommitNT / 64];
     __shared__ uint32_t xid[kCommitNT], xn[kCommitNT];
     __shared__ double xtt[kCommitNT];
     __shared__ int smoved;                                // gridlock detector: an exit or a departure here
@@ -1975,9 +1954,9 @@ __global__ void __launch_bounds__(kCommitNT) k_commit(Dev d) {
     acc.zero();
     int c = 0;
     if (le != ~0u) c = commit_lane(d, tb, d.s[par], gl, e, l, tid, t, p, rs, es, acc, ex, &smoved);
-    const Scan4 run = wg_exclusive_scan4<kCommitNT>(Scan4{c, -1, -1, -1}, wsh4);   // a barrier in it
-    d.lane_off[gl] = run.s;
-    if (tid == kCommitNT - 1) d.blk_sum[blockIdx.x] = run.s + c;
+    const int o = wg_exclusive_sum<kCommitNT>(c, wsh);   // a barrier in it
+    d.lane_off[gl] = o;
+    if (tid == kCommitNT - 1) d.blk_sum[blockIdx.x] = o + c;
     if (xid[tid] != ~0u) commit_travel_time<true>(d, e, l, tid, ex);
     flush_commit_counters(d, acc, shc);
     publish_moved(d, &smoved, t);
@@ -1997,7 +1976,7 @@ __device__ inline unsigned lanes_at(const int4& s, int t) {
 // 124k and 33.0 against 32.0 on the 100x100 city, so the line lies at 190k.
 __global__ void __launch_bounds__(kCommitNT) k_commit_many(Dev d) {
     __shared__ unsigned shc[cNumCounters];
-    __shared__ Scan4 wsh4[kCommitNT / 64];
+    __shared__ int wsh[kCommitNT / 64];
     __shared__ __align__(16) uint32_t xid[kManyBlock], xn[kManyBlock];
     __shared__ double xtt[kManyBlock];
     __shared__ __align__(16) int cnts[kManyBlock];          // vehicles of the lane's run
@@ -2079,7 +2058,7 @@ __global__ void __launch_bounds__(kCommitNT) k_commit_many(Dev d) {
     c.w += (int)((in >> 3) & 1u) - (out.w != ~0u);
     ((int4*)tb.lane_newcnt)[i4] = c;
     const int sum = c.x + c.y + c.z + c.w;
-    const int o = wg_exclusive_scan4<kCommitNT>(Scan4{sum, -1, -1, -1}, wsh4).s;
+    const int o = wg_exclusive_sum<kCommitNT>(sum, wsh);
     ((int4*)d.lane_off)[i4] = make_int4(o, o + c.x, o + c.x + c.y, o + c.x + c.y + c.z);
     if (tid == kCommitNT - 1) d.blk_sum[blockIdx.x] = o + sum;
     for (int i = tid; i < nr; i += kCommitNT) {
@@ -2120,12 +2099,12 @@ __device__ inline void stage_block_sums(const int* blk_sum, int m, int* stage) {
 // The staged sums (a barrier before) in place: offsets from `from`; returns the
 // end, in *tot too.  A barrier follows the last write.
 template <int NT>
-__device__ inline int scan_staged_sums(int m, int* stage, int from, Scan4* wsh4, int* tot) {
+__device__ inline int scan_staged_sums(int m, int* stage, int from, int* wsh, int* tot) {
     const int chunk = (m + NT - 1) / NT;
     const int lo = min(m, (int)threadIdx.x * chunk), hi = min(m, lo + chunk);
     int loc = 0;
     for (int i = lo; i < hi; ++i) loc += stage[i];
-    int o = from + wg_exclusive_scan4<NT>(Scan4{loc, -1, -1, -1}, wsh4).s;
+    int o = from + wg_exclusive_sum<NT>(loc, wsh);
     for (int i = lo; i < hi; ++i) {
         const int v = stage[i];
         stage[i] = o;
@@ -2138,13 +2117,13 @@ __device__ inline int scan_staged_sums(int m, int* stage, int from, Scan4* wsh4,
 
 template <int NT>
 __device__ inline int scan_block_sums_staged(const int* blk_sum, int nb, int* off, int* stage, int cap,
-                                             Scan4* wsh4, int* tot) {
+                                             int* wsh, int* tot) {
     int carry = 0;
     for (int r0 = 0; r0 < nb; r0 += cap) {
         const int m = min(cap, nb - r0);
         stage_block_sums<NT>(blk_sum + r0, m, stage);
         __syncthreads();
-        carry = scan_staged_sums<NT>(m, stage, carry, wsh4, tot);
+        carry = scan_staged_sums<NT>(m, stage, carry, wsh, tot);
         for (int i = (int)threadIdx.x; i < m; i += NT) off[r0 + i] = stage[i];
         __syncthreads();                            // stage and *tot are reused by the next round
     }
@@ -2171,11 +2150,11 @@ __device__ inline void finish_step(const Dev& d, int t, int par, int total) {
 // Networks with more commit blocks than kScanLdsMax: one workgroup scans the
 // block offsets into global memory before k_scatter.
 __global__ void __launch_bounds__(kBigNT) k_blkscan(Dev d) {
-    __shared__ Scan4 wsh4[kBigNT / 64];
+    __shared__ int wsh[kBigNT / 64];
     __shared__ int tot;
     __shared__ int stage[kScanLdsMax];
     const int t = d.ctl->t_b, par = t & 1;
-    const int total = scan_block_sums_staged<kBigNT>(d.blk_sum, d.n_blk, d.blk_off, stage, kScanLdsMax, wsh4, &tot);
+    const int total = scan_block_sums_staged<kBigNT>(d.blk_sum, d.n_blk, d.blk_off, stage, kScanLdsMax, wsh, &tot);
     if (threadIdx.x < 64) finish_step(d, t, par, total);
 }
 
@@ -2279,7 +2258,7 @@ __device__ inline void scatter_store(const Dev& d, const LaneTabs& tb, const Slo
 // kScanLdsMax commit blocks), and workgroup 0 finishes the step; otherwise
 // k_blkscan has done both.  kSpread: the records have their drivers' own limits.
 template <bool kLds, bool kSpread>
-__device__ inline void scatter_items(const Dev& d, int* soff, Scan4* wsh4, int* totp, float* slen) {
+__device__ inline void scatter_items(const Dev& d, int* soff, int* wsh, int* totp, float* slen) {
     const float len = d.cp[threadIdx.x & 15].len;   // into slen below, behind the other first loads
     const StepHead sh = step_head(d.ctl);
     const int t = sh.t_b, par = t & 1;
@@ -2315,7 +2294,7 @@ __device__ inline void scatter_items(const Dev& d, int* soff, Scan4* wsh4, int* 
         scatter_load_tables(d, tb, next(k), r);
         if (threadIdx.x < 16) slen[threadIdx.x] = len;
         __syncthreads();
-        nnew = scan_staged_sums<kNT>(d.n_blk, soff, 0, wsh4, totp);
+        nnew = scan_staged_sums<kNT>(d.n_blk, soff, 0, wsh, totp);
         boff = soff;
         // the last workgroup has no items (it would be done later than the others)
         if (blockIdx.x == gridDim.x - 1) {
@@ -2350,10 +2329,10 @@ __global__ void __launch_bounds__(kNT) k_scatter(Dev d) {
     // kLds: the block offsets, d.n_blk ints of dynamic LDS sized at launch
     // (so a network with few commit blocks leaves room for more workgroups)
     extern __shared__ int soff[];
-    __shared__ Scan4 wsh4[kWaves];
+    __shared__ int wsh[kWaves];
     __shared__ int tot;
     __shared__ float slen[16];                    // vehicle length per class
-    scatter_items<kLds, kSpread>(d, soff, wsh4, &tot, slen);
+    scatter_items<kLds, kSpread>(d, soff, wsh, &tot, slen);
     if (d.imode == 1)                             // case 1: nodes free for the next step's crossings
         for (int v = blockIdx.x * kNT + threadIdx.x; v < d.n_nodes; v += gridDim.x * kNT) d.win_node[v] = ~0ull;
 }
