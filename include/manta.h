@@ -314,7 +314,7 @@ const char *sim_last_error(const sim_handle *h);
 
 /* Vehicle-updates done in tiles above one workgroup's LDS (inside
  * k_big_admit) since the handle's state was last written; the rest were done
- * by k_tile_step.  Synchronizes the handle's stream.  For measurement only. */
+ * by k_tile_step, or, on a small network, in the launch that takes many steps.  Synchronizes the handle's stream.  For measurement only. */
 sim_status sim_big_tile_updates(sim_handle *h, int64_t *updates);
 
 /* ------------------------------------------------------------------ diagnostics

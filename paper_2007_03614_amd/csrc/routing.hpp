@@ -90,7 +90,7 @@ constexpr size_t kRouteTreeLds = 163840 - 64;   // dynamic LDS of one workgroup 
 constexpr double kRouteTreeStep = 16.0;
 // Edges of more than kRouteTreeDear times the mean are not in it (closed roads, priced far above any time: with 1 %
 // of the edges at 1e6 s in the mean no threshold binds, and the city takes 14.7 ms, the lattice 10.7; without them 7.8
-// and 3.3, and 7.6 and 3.1 with no road closed).
+// and 3.3, and 7.6 and 3.1 with no road closed.
 constexpr double kRouteTreeDear = 16.0;
 constexpr int kRouteTreeList = 1024;    // entries of a frontier list at most
 constexpr unsigned kLabelInf = (0x7f800000u << 1) | 1u;

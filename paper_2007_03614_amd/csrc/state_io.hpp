@@ -382,7 +382,7 @@ __global__ void __launch_bounds__(kNT) k_io_verify(Dev d, IoWork w, StateIo in, 
 // The checked state becomes the handle's.  B: the layout built above, in the
 // buffer that the current step does not use; S: where step t reads it.
 __global__ void __launch_bounds__(kNT) k_io_apply(Dev d, IoWork w, StateIo in, Slots B, Slots S) {
-    const IoHead h = *in.head;
+    const IoHead& h = *in.head;                // (a copy, its counters indexed, would live in scratch memory)
     if (h.bad) return;
     const int t = h.t, na = h.n_act, nl = d.n_lanes_total, nn = d.imode == 1 ? d.n_nodes : 0;
     const int most = max(max(max(d.n_veh, nl), max(d.nq, nn)), cNumCounters * kCounterCopies);
