@@ -696,9 +696,10 @@ constexpr int kLateA = 16, kLateB = 32;               // a draw that is not in t
 // marked vehicles of the tile (n of them).  One place for the Philox code, and
 // its rounds two at a time in a loop: with copies where a full list was met, all
 // unrolled, the tile kernel was four times its size and spilled 111 scalar
-// registers of keys and pointers (now 29), each read back by a vector
-// instruction, on a kernel whose vector units are 70 % busy on the metropolitan
-// lattice (tile kernel 30.2 -> 28.3 us there, 28.6 -> 27.0 on the dense city).
+// registers of keys and pointers (now 21), each read back by a vector
+// instruction, on a kernel that issues those on half of the cycles of its SIMDs
+// (tile kernel 30.2 -> 28.3 us on the metropolitan lattice, 28.6 -> 27.0 on the
+// dense city).
 template <int NT>
 __device__ inline void draw_run(const Dev& d, const DrawQ& dq, int round, int t, const TileBuf& b, int n, int* u1,
                                 int* na, int* nb) {
